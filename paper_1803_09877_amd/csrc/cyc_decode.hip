@@ -70,11 +70,11 @@ __device__ __forceinline__ void cyc_project_body(const float* __restrict__ Rm, c
             }
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                const float4 l = lo_values<LO>(xl[k], x[k]);
-                xr0[k] = (double)x[k].x + (double)l.x;
-                xi0[k] = (double)x[k].y + (double)l.y;
-                xr1[k] = (double)x[k].z + (double)l.z;
-                xi1[k] = (double)x[k].w + (double)l.w;
+                const wire4 v = wire_value<LO>(x[k], xl[k]);
+                xr0[k] = v.x;
+                xi0[k] = v.y;
+                xr1[k] = v.z;
+                xi1[k] = v.w;
             }
         } else {
 #pragma unroll
@@ -192,7 +192,7 @@ __device__ __forceinline__ void cyc_recombine_body(const float* __restrict__ Rm,
                                                    const int32_t* __restrict__ nu_ptr, float* __restrict__ u,
                                                    bool realout, int64_t d) {
     const int nu = *nu_ptr;  // honest nodes; written by the locator (device) or copied in by the host path
-    const int64_t c0 = lane_column<kSpreadRecombine>();
+    const int64_t c0 = lane_column<kSpreadRecombine>(d);
     if (!FULL && c0 >= d) return;
     const int64_t mlen = 2 * ((d + 1) / 2);
     const int nin = FULL ? 4 : clamp4(mlen - c0);
@@ -212,14 +212,9 @@ __device__ __forceinline__ void cyc_recombine_body(const float* __restrict__ Rm,
         for (int i = 0; i < UN; ++i) {
             if (q0 + i < nu) {
                 const double br = b[q0 + i].x, bi = b[q0 + i].y;
-                if constexpr (LO != kLoNone) {
-                    const float4 l = lo_values<LO>(xl[i], x[i]);
-                    cmac(br, bi, (double)x[i].x + (double)l.x, (double)x[i].y + (double)l.y, are0, aim0);
-                    cmac(br, bi, (double)x[i].z + (double)l.z, (double)x[i].w + (double)l.w, are1, aim1);
-                } else {
-                    cmac(br, bi, (double)x[i].x, (double)x[i].y, are0, aim0);
-                    cmac(br, bi, (double)x[i].z, (double)x[i].w, are1, aim1);
-                }
+                const wire4 v = wire_value<LO>(x[i], xl[LO != kLoNone ? i : 0]);
+                cmac(br, bi, v.x, v.y, are0, aim0);
+                cmac(br, bi, v.z, v.w, are1, aim1);
             }
         }
     }
@@ -243,7 +238,7 @@ __global__ __launch_bounds__(kBlock) void cyc_recombine_kernel(const float* __re
                                                                const int32_t* __restrict__ spec_state, int P,
                                                                float* __restrict__ u, int realout, int64_t d) {
     if (spec_state != nullptr && spec_state[1] != 0 && *nu == P) return;
-    if (block_is_full<kSpreadRecombine>(d)) cyc_recombine_body<true, LO, UN>(Rm, Rlo, ldm, b, idx, nu, u, realout != 0, d);
+    if (block_is_full<kSpreadRecombine>(d, d)) cyc_recombine_body<true, LO, UN>(Rm, Rlo, ldm, b, idx, nu, u, realout != 0, d);
     else cyc_recombine_body<false, LO, UN>(Rm, Rlo, ldm, b, idx, nu, u, realout != 0, d);
 }
 

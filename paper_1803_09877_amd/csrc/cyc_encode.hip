@@ -36,8 +36,8 @@ __global__ __launch_bounds__(kBlock) void encode_cyc_node_kernel(const float* __
                                                                  int64_t lo_off, int lo,
                                                                  const CycTaps tab, int node, int P,
                                                                  int r, int wrap_rows, int m, int64_t d) {
-    const int64_t c0 = lane_column<kSpreadEncodeCyc>();
     const int64_t mlen = 2 * ((d + 1) / 2);
+    const int64_t c0 = lane_column<kSpreadEncodeCyc>(mlen);
     if (c0 >= mlen) return;
     const int nin = clamp4(d - c0);
     const int nout = clamp4(mlen - c0);
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(kBlock) void encode_cyc_real_node_kernel(const floa
                                                                       float* __restrict__ z,
                                                                       const double2* __restrict__ cn, int node,
                                                                       int P, int r, int wrap_rows, int64_t d) {
-    const int64_t c0 = lane_column<kSpreadEncodeCyc>();
+    const int64_t c0 = lane_column<kSpreadEncodeCyc>(d);
     if (c0 >= d) return;
     const int nin = clamp4(d - c0);
     double re[4] = {0.0, 0.0, 0.0, 0.0}, im[4] = {0.0, 0.0, 0.0, 0.0};
@@ -192,12 +192,11 @@ __global__ __launch_bounds__(kBlock) void encode_cyc_real_node_kernel(const floa
 hipError_t launch_encode_cyc(const float* G, int64_t ldg, float* Z, float* Zlo, int lo, int64_t ldm, const CycTaps& tab,
                              int P, int s, int64_t d, hipStream_t stream) {
     const int64_t mlen = 2 * ((d + 1) / 2);
-    const dim3 grid(grid_cols<kSpreadEncodeCyc>(mlen)), block(kBlock);
     const int r = 2 * s + 1;
     const bool one_per_cu = s <= 3 && P >= 32;
     if (s > kMaxCycS && s <= kMaxNarrowS) return launch_narrow(s, false, stream, G, ldg, 1, Z, Zlo, lo, ldm, nullptr, tab, P, d);
 #define DRACO_CASE(S) \
-    case S: return launch_encode_cyc_s<S>(one_per_cu, grid, stream, G, ldg, Z, Zlo, lo, ldm, tab, P, d);
+    case S: return launch_encode_cyc_s<S>(one_per_cu, stream, G, ldg, Z, Zlo, lo, ldm, tab, P, d);
     switch (s) {
         DRACO_CASE(0) DRACO_CASE(1) DRACO_CASE(2) DRACO_CASE(3) DRACO_CASE(4) DRACO_CASE(5) DRACO_CASE(6) DRACO_CASE(7)
         DRACO_CASE(8) DRACO_CASE(9) DRACO_CASE(10)
@@ -212,6 +211,7 @@ hipError_t launch_encode_cyc(const float* G, int64_t ldg, float* Z, float* Zlo, 
                 hipLaunchKernelGGL(encode_cyc_ring_kernel<TB>, g64, dim3(TB), ring_bytes, stream, G, ldg, Z, Zlo, lo,
                                    ldm, tab, P, r, d);
             } else {  // windows too wide for LDS: one launch per node
+                const dim3 grid(grid_cols<kSpreadEncodeCyc>(mlen)), block(kBlock);
                 for (int j = 0; j < P; ++j)
                     hipLaunchKernelGGL(encode_cyc_node_kernel, grid, block, 0, stream, G, ldg, Z + (int64_t)j * ldm,
                                        Zlo, (int64_t)j * ldm, lo, tab, j, P, r, P, 1, d);

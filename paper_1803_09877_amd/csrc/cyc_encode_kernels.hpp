@@ -49,13 +49,26 @@ __device__ __forceinline__ void tap_sum(const CycTaps& tab, int n, const double 
     cmul(A.x, A.y, sr1, si1, are1, aim1);
 }
 
-template <int S, int NB, bool FULL, int LO>
+// Stores a message entry of node n at column c0: the first word and, on the two-word wire, what
+// that rounding lost.
+template <bool FULL, int LO, bool NT>
+__device__ __forceinline__ void store_message(float* __restrict__ Z, float* __restrict__ Zlo, int64_t off, double are0,
+                                              double aim0, double are1, double aim1, int nout) {
+    const float4 hi = make_float4((float)are0, (float)aim0, (float)are1, (float)aim1);
+    stx<FULL, NT>(Z + off, hi, nout);
+    if constexpr (LO != kLoNone) {
+        const float4 lo = make_float4((float)(are0 - (double)hi.x), (float)(aim0 - (double)hi.y),
+                                      (float)(are1 - (double)hi.z), (float)(aim1 - (double)hi.w));
+        st_lo<FULL, LO, NT>(Zlo, off, hi, lo, nout);
+    }
+}
+
+template <int S, int NB, bool FULL, int LO, bool NT>
 __device__ __forceinline__ void encode_cyc_body(const float* __restrict__ G, int64_t ldg, float* __restrict__ Z,
                                                 float* __restrict__ Zlo, int64_t ldm,
-                                                const CycTaps tab, int P, int64_t d,
+                                                const CycTaps tab, int P, int64_t d, int64_t c0,
                                                 float4* head /* LDS [2S][kBlock] */) {
     constexpr int R = 2 * S + 1;
-    const int64_t c0 = lane_column<kSpreadEncodeCyc>();
     const int64_t mlen = 2 * ((d + 1) / 2);
     if (!FULL && c0 >= mlen) return;
     const int nin = FULL ? 4 : clamp4(d - c0);      // gradient floats that exist (the pad of an odd d reads as 0)
@@ -85,13 +98,7 @@ __device__ __forceinline__ void encode_cyc_body(const float* __restrict__ G, int
                 put((uu + 2 * S) % R, buf[uu], n + 2 * S);
                 double are0, aim0, are1, aim1;
                 tap_sum<R>(tab, n, wre, wim, uu % R, are0, aim0, are1, aim1);
-                const float4 hi = make_float4((float)are0, (float)aim0, (float)are1, (float)aim1);
-                stx<FULL>(Z + (int64_t)n * ldm + c0, hi, nout);
-                if constexpr (LO != kLoNone) {  // second word of the wide wire: what the first rounding lost
-                    const float4 lo = make_float4((float)(are0 - (double)hi.x), (float)(aim0 - (double)hi.y),
-                                                  (float)(are1 - (double)hi.z), (float)(aim1 - (double)hi.w));
-                    st_lo<FULL, LO>(Zlo, (int64_t)n * ldm + c0, hi, lo, nout);
-                }
+                store_message<FULL, LO, NT>(Z, Zlo, (int64_t)n * ldm + c0, are0, aim0, are1, aim1, nout);
             }
         }
     };
@@ -119,14 +126,80 @@ __device__ __forceinline__ void encode_cyc_body(const float* __restrict__ G, int
     }
 }
 
-template <int S, int NB, int LO>
+// LINES: workgroups own 4 KiB contiguously, neighbours on the same die, plain stores
+// (device_util.hpp, "rows off the line grid"); else the spread footprint with streaming stores.
+template <int S, int NB, int LO, bool LINES>
 __global__ __launch_bounds__(kBlock) void encode_cyc_kernel(const float* __restrict__ G, int64_t ldg,
                                                             float* __restrict__ Z, float* __restrict__ Zlo,
                                                             int64_t ldm, const CycTaps tab, int P,
                                                             int64_t d) {
     extern __shared__ float4 head[];  // [2S][kBlock]
-    if (block_is_full<kSpreadEncodeCyc>(d)) encode_cyc_body<S, NB, true, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, head);
-    else encode_cyc_body<S, NB, false, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, head);
+    const int64_t mlen = 2 * ((d + 1) / 2);
+    const int64_t tile = LINES ? xcd_tile() : 0;
+    const int64_t c0 = LINES ? (tile * kBlock + threadIdx.x) * 4 : lane_column<kSpreadEncodeCyc>(mlen);
+    const bool full = LINES ? (tile + 1) * (kBlock * 4) <= d : block_is_full<kSpreadEncodeCyc>(mlen, d);
+    if (full) encode_cyc_body<S, NB, true, LO, !LINES>(G, ldg, Z, Zlo, ldm, tab, P, d, c0, head);
+    else encode_cyc_body<S, NB, false, LO, !LINES>(G, ldg, Z, Zlo, ldm, tab, P, d, c0, head);
+}
+
+// The same encoder for rows too short to fill the chip.  There the walk down P rows is
+// latency: a workgroup (4 KiB contiguous, neighbours on one die, plain stores) takes only `seg`
+// nodes, blockIdx.y the segment, and the rows that neighbouring segments share (2s of them) come
+// from the caches; no LDS, so the registers alone bound the workgroups per CU.  The window's rows
+// and the first round are in flight together.  Same taps in the same order: identical bits.
+template <int S, bool FULL, int LO>
+__device__ __forceinline__ void encode_cyc_small_body(const float* __restrict__ G, int64_t ldg, float* __restrict__ Z,
+                                                      float* __restrict__ Zlo, int64_t ldm, const CycTaps tab, int P,
+                                                      int64_t d, int64_t c0, int first, int last) {
+    constexpr int R = 2 * S + 1;
+    const int64_t mlen = 2 * ((d + 1) / 2);
+    if (!FULL && c0 >= mlen) return;
+    const int nin = FULL ? 4 : clamp4(d - c0);
+    const int nout = FULL ? 4 : clamp4(mlen - c0);
+    double wre[R][2], wim[R][2];  // window slot = (row - first) mod R
+    auto fetch = [&](int kappa) -> float4 {   // row of unwrapped index kappa < P + 2S
+        const int k = kappa < P ? kappa : kappa - P;
+        return ldx<FULL, false>(G + (int64_t)k * ldg + c0, nin);
+    };
+    auto put = [&](int slot, const float4& raw, int kappa) {
+        rotate_in(tab, kappa, (double)raw.x, (double)raw.y, (double)raw.z, (double)raw.w, wre[slot], wim[slot]);
+    };
+    float4 head[2 * S > 0 ? 2 * S : 1], buf[R];
+#pragma unroll
+    for (int k = 0; k < 2 * S; ++k) head[k] = fetch(first + k);
+    auto issue = [&](int n0) {
+#pragma unroll
+        for (int uu = 0; uu < R; ++uu)
+            if (n0 + uu < last) buf[uu] = fetch(n0 + uu + 2 * S);
+    };
+    issue(first);
+#pragma unroll
+    for (int k = 0; k < 2 * S; ++k) put(k, head[k], first + k);
+    for (int n0 = first; n0 < last; n0 += R) {
+        if (n0 != first) issue(n0);
+#pragma unroll
+        for (int uu = 0; uu < R; ++uu) {
+            const int n = n0 + uu;
+            if (n < last) {
+                put((uu + 2 * S) % R, buf[uu], n + 2 * S);
+                double are0, aim0, are1, aim1;
+                tap_sum<R>(tab, n, wre, wim, uu % R, are0, aim0, are1, aim1);
+                store_message<FULL, LO, false>(Z, Zlo, (int64_t)n * ldm + c0, are0, aim0, are1, aim1, nout);
+            }
+        }
+    }
+}
+
+template <int S, int LO>
+__global__ __launch_bounds__(kBlock) void encode_cyc_small_kernel(const float* __restrict__ G, int64_t ldg,
+                                                                  float* __restrict__ Z, float* __restrict__ Zlo,
+                                                                  int64_t ldm, const CycTaps tab, int P, int seg,
+                                                                  int64_t d) {
+    const int64_t tile = xcd_tile();
+    const int64_t c0 = (tile * kBlock + threadIdx.x) * 4;
+    const int first = (int)blockIdx.y * seg, last = min(P, first + seg);
+    if ((tile + 1) * (kBlock * 4) <= d) encode_cyc_small_body<S, true, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, c0, first, last);
+    else encode_cyc_small_body<S, false, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, c0, first, last);
 }
 
 // The same encoder with a wider lane: a lane owns C float4 of every row (its wavefront's C
@@ -139,7 +212,7 @@ __global__ __launch_bounds__(kBlock) void encode_cyc_kernel(const float* __restr
 // Measured at (P, s, d) = (45, 3, 25.6 M), one word per float: C = 4, D = 2 runs at 6.1 TB/s
 // against 5.9 for encode_cyc_body on the same footprint window (and 5.65 contiguous); with an
 // 8-bit second word 1750 us against 1770; with a 16- or 32-bit second word it gains nothing.
-template <int S, int C, int D, bool FULL, int LO>
+template <int S, int C, int D, int LO>
 __device__ __forceinline__ void encode_cyc_strip_body(const float* __restrict__ G, int64_t ldg,
                                                       float* __restrict__ Z, float* __restrict__ Zlo, int64_t ldm,
                                                       const CycTaps tab, int P, int64_t d,
@@ -147,13 +220,6 @@ __device__ __forceinline__ void encode_cyc_strip_body(const float* __restrict__ 
                                                       const int64_t (&cq)[C]) {
     constexpr int R = 2 * S + 1;
     constexpr int U = R * ((D + R - 1) / R);  // unroll length and ring size: a multiple of R that holds D rows
-    const int64_t mlen = 2 * ((d + 1) / 2);
-    int nin[C], nout[C];
-#pragma unroll
-    for (int q = 0; q < C; ++q) {
-        nin[q] = FULL ? 4 : clamp4(d - cq[q]);
-        nout[q] = FULL ? 4 : clamp4(mlen - cq[q]);
-    }
     double wre[C][R][2], wim[C][R][2];  // [piece][window slot = row index mod R]
     auto put = [&](int slot, const float4 (&raw)[C], int kappa) {
 #pragma unroll
@@ -165,7 +231,7 @@ __device__ __forceinline__ void encode_cyc_strip_body(const float* __restrict__ 
         if (k < P) {
 #pragma unroll
             for (int q = 0; q < C; ++q)
-                if (FULL || nout[q] > 0) dst[q] = ldx<FULL>(G + (int64_t)k * ldg + cq[q], nin[q]);
+                dst[q] = ld4(G + (int64_t)k * ldg + cq[q]);
         } else {
 #pragma unroll
             for (int q = 0; q < C; ++q) dst[q] = head[((k - P) * C + q) * kBlock + threadIdx.x];
@@ -196,15 +262,7 @@ __device__ __forceinline__ void encode_cyc_strip_body(const float* __restrict__ 
                 for (int q = 0; q < C; ++q) {
                     double are0, aim0, are1, aim1;
                     tap_sum<R>(tab, n, wre[q], wim[q], uu % R, are0, aim0, are1, aim1);
-                    if (FULL || nout[q] > 0) {
-                        const float4 hi = make_float4((float)are0, (float)aim0, (float)are1, (float)aim1);
-                        stx<FULL>(Z + (int64_t)n * ldm + cq[q], hi, nout[q]);
-                        if constexpr (LO != kLoNone) {
-                            const float4 lo = make_float4((float)(are0 - (double)hi.x), (float)(aim0 - (double)hi.y),
-                                                          (float)(are1 - (double)hi.z), (float)(aim1 - (double)hi.w));
-                            st_lo<FULL, LO>(Zlo, (int64_t)n * ldm + cq[q], hi, lo, nout[q]);
-                        }
-                    }
+                    store_message<true, LO, true>(Z, Zlo, (int64_t)n * ldm + cq[q], are0, aim0, are1, aim1, 4);
                 }
             }
         }
@@ -220,17 +278,26 @@ __global__ __launch_bounds__(kBlock) void encode_cyc_strip_kernel(const float* _
     extern __shared__ float4 head[];  // [2S][C][kBlock]
     constexpr int64_t u = kWindow / (4 * C);   // floats between neighbouring pieces of the workgroup
     constexpr int64_t per = u / 256;           // workgroups per window
-    const int64_t base = ((int64_t)blockIdx.x / per) * kWindow + ((int64_t)blockIdx.x % per) * 256;
+    const int64_t windows = d / kWindow;       // whole ones; the rest of the row in contiguous 4 KiB, first
+    const int64_t tile = (int64_t)blockIdx.x - ((int64_t)gridDim.x - windows * per);
+    if (tile < 0) {
+        const int64_t base = windows * kWindow + (int64_t)blockIdx.x * (kBlock * 4);
+        const int64_t c0 = base + threadIdx.x * 4;
+        if (base + kBlock * 4 <= d) encode_cyc_body<S, 3, true, LO, true>(G, ldg, Z, Zlo, ldm, tab, P, d, c0, head);
+        else encode_cyc_body<S, 3, false, LO, true>(G, ldg, Z, Zlo, ldm, tab, P, d, c0, head);
+        return;
+    }
+    const int64_t base = (tile / per) * kWindow + (tile % per) * 256;
     int64_t cq[C];
 #pragma unroll
     for (int q = 0; q < C; ++q) cq[q] = base + ((threadIdx.x >> 6) + 4 * q) * u + (threadIdx.x & 63) * 4;
-    if (base + (4 * C - 1) * u + 256 <= d) encode_cyc_strip_body<S, C, D, true, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, head, cq);
-    else encode_cyc_strip_body<S, C, D, false, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, head, cq);
+    encode_cyc_strip_body<S, C, D, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, head, cq);
 }
-// Workgroups of encode_cyc_strip_kernel<S, C, D> for messages of mlen floats.
+// Workgroups of encode_cyc_strip_kernel<S, C, D> for gradients of d floats.
 template <int C>
-inline unsigned strip_grid(int64_t mlen) {
-    return (unsigned)((mlen + kWindow - 1) / kWindow * (kWindow / (4 * C) / 256));
+inline unsigned strip_grid(int64_t d) {
+    const int64_t windows = d / kWindow, rest = 2 * ((d + 1) / 2) - windows * kWindow;
+    return (unsigned)(windows * (kWindow / (4 * C) / 256)) + grid_for((rest + 3) / 4);
 }
 
 // E^Cyc on the real gradients as Sec. 3 states it, without the packing remark that closes
@@ -247,7 +314,7 @@ __device__ __forceinline__ void encode_cyc_real_body(const float* __restrict__ G
                                                      float4* head /* LDS [2S][kBlock] */) {
     constexpr int R = 2 * S + 1;
     // the wavefront covers 256 consecutive real coordinates; mine are cA, cA+1, cA+128, cA+129
-    const int64_t cA = lane_column<kSpreadEncodeCyc>() - (threadIdx.x & 63) * 2;
+    const int64_t cA = lane_column<kSpreadEncodeCyc>(d) - (threadIdx.x & 63) * 2;
     const int64_t cB = cA + 128;
     if (!FULL && cA >= d) return;
     const int nA = FULL ? 2 : (d - cA >= 2 ? 2 : (int)(d - cA));
@@ -337,7 +404,7 @@ __global__ __launch_bounds__(kBlock) void encode_cyc_real_kernel(const float* __
                                                                  const double2* __restrict__ coef, int P,
                                                                  int64_t d) {
     extern __shared__ float4 head[];  // [2S][kBlock]
-    if (block_is_full<kSpreadEncodeCyc>(d)) encode_cyc_real_body<S, NB, true>(G, ldg, Z, ldm, coef, P, d, head);
+    if (block_is_full<kSpreadEncodeCyc>(d, d)) encode_cyc_real_body<S, NB, true>(G, ldg, Z, ldm, coef, P, d, head);
     else encode_cyc_real_body<S, NB, false>(G, ldg, Z, ldm, coef, P, d, head);
 }
 
@@ -352,8 +419,8 @@ __device__ __forceinline__ void encode_cyc_multi_body(const float* __restrict__ 
                                                       double4* head /* LDS [2S][kBlock] */) {
     constexpr int R = 2 * S + 1;
     constexpr int UN = 4;
-    const int64_t c0 = lane_column<kSpreadEncodeCyc>();
     const int64_t mlen = 2 * ((d + 1) / 2);
+    const int64_t c0 = lane_column<kSpreadEncodeCyc>(mlen);
     if (!FULL && c0 >= mlen) return;
     const int nin = FULL ? 4 : clamp4(d - c0);
     const int nout = FULL ? 4 : clamp4(mlen - c0);
@@ -438,8 +505,8 @@ __device__ __forceinline__ void encode_cyc_multi_ring_body(const float* __restri
                                                            int64_t ldm, const CycTaps tab, int P,
                                                            int64_t d, double4* head /* LDS [2S][kBlock] */) {
     constexpr int R = 2 * S + 1;
-    const int64_t c0 = lane_column<kSpreadEncodeCyc>();
     const int64_t mlen = 2 * ((d + 1) / 2);
+    const int64_t c0 = lane_column<kSpreadEncodeCyc>(mlen);
     if (!FULL && c0 >= mlen) return;
     const int nin = FULL ? 4 : clamp4(d - c0);
     const int nout = FULL ? 4 : clamp4(mlen - c0);
@@ -510,8 +577,8 @@ __device__ __forceinline__ void encode_cyc_multi_four_body(const float* __restri
                                                            int64_t ldm, const CycTaps tab, int P,
                                                            int64_t d, double4* head /* LDS [2S][kBlock] */) {
     constexpr int R = 2 * S + 1;
-    const int64_t c0 = lane_column<kSpreadEncodeCyc>();
     const int64_t mlen = 2 * ((d + 1) / 2);
+    const int64_t c0 = lane_column<kSpreadEncodeCyc>(mlen);
     if (!FULL && c0 >= mlen) return;
     const int nin = FULL ? 4 : clamp4(d - c0);
     const int nout = FULL ? 4 : clamp4(mlen - c0);
@@ -583,7 +650,7 @@ __global__ __launch_bounds__(kBlock) void encode_cyc_multi_four_kernel(const flo
                                                                        int64_t ldm, const CycTaps tab,
                                                                        int P, int64_t d) {
     extern __shared__ double4 head_sums[];  // [2S][kBlock]
-    if (block_is_full<kSpreadEncodeCyc>(d))
+    if (block_is_full<kSpreadEncodeCyc>(2 * ((d + 1) / 2), d))
         encode_cyc_multi_four_body<S, true, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, head_sums);
     else
         encode_cyc_multi_four_body<S, false, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, head_sums);
@@ -595,7 +662,7 @@ __global__ __launch_bounds__(kBlock) void encode_cyc_multi_ring_kernel(const flo
                                                                        int64_t ldm, const CycTaps tab,
                                                                        int P, int64_t d) {
     extern __shared__ double4 head_sums[];  // [2S][kBlock]
-    if (block_is_full<kSpreadEncodeCyc>(d))
+    if (block_is_full<kSpreadEncodeCyc>(2 * ((d + 1) / 2), d))
         encode_cyc_multi_ring_body<S, D, true, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, d, head_sums);
     else
         encode_cyc_multi_ring_body<S, D, false, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, d, head_sums);
@@ -607,16 +674,16 @@ __global__ __launch_bounds__(kBlock) void encode_cyc_multi_kernel(const float* _
                                                                   int64_t ldm, const CycTaps tab,
                                                                   int P, int64_t d) {
     extern __shared__ double4 head_sums[];  // [2S][kBlock]
-    if (block_is_full<kSpreadEncodeCyc>(d)) encode_cyc_multi_body<S, true, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, d, head_sums);
+    if (block_is_full<kSpreadEncodeCyc>(2 * ((d + 1) / 2), d)) encode_cyc_multi_body<S, true, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, d, head_sums);
     else encode_cyc_multi_body<S, false, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, d, head_sums);
 }
 
 
 // Launch of the all-node encoder for one s (defined in the translation unit of that s).
-// one_per_cu selects the launch shape: one workgroup per CU with deep prefetch, or two.
-// lo: format of the second word (kLoF32 / kLoBf16) when Zlo is not null.
+// one_per_cu selects the launch shape of large messages: one workgroup per CU with deep prefetch, or
+// two.  lo: format of the second word when Zlo is not null.
 template <int S>
-hipError_t launch_encode_cyc_s(bool one_per_cu, dim3 grid, hipStream_t stream, const float* G, int64_t ldg, float* Z,
+hipError_t launch_encode_cyc_s(bool one_per_cu, hipStream_t stream, const float* G, int64_t ldg, float* Z,
                                float* Zlo, int lo, int64_t ldm, const CycTaps& tab, int P, int64_t d);
 // Same for the unpacked wire (real gradients in, d complex entries out).
 template <int S>

@@ -15,20 +15,34 @@ namespace draco {
 namespace {
 
 
-// Slabs are streamed: every byte is used once, so 16-byte accesses carry the
-// non-temporal hint (measured on MI355X: +10% on read-dominated passes).
+// Large slabs are streamed: every byte is used once, so 16-byte accesses carry the
+// non-temporal hint (NT; measured on MI355X: +10% on read-dominated passes).  Without it where
+// a slab fits the 256 MiB memory-side cache and is read again soon, and where neighbouring
+// workgroups write parts of the same cache line (see "rows off the line grid").
 typedef float vfloat4 __attribute__((ext_vector_type(4)));
+template <bool NT, class T>
+__device__ __forceinline__ T ld_hint(const T* p) {
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+template <bool NT, class T>
+__device__ __forceinline__ void st_hint(T* p, T v) {
+    if constexpr (NT) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+template <bool NT = true>
 __device__ __forceinline__ float4 ld4(const float* p) {
-    const vfloat4 v = __builtin_nontemporal_load(reinterpret_cast<const vfloat4*>(p));
+    const vfloat4 v = ld_hint<NT>(reinterpret_cast<const vfloat4*>(p));
     return make_float4(v.x, v.y, v.z, v.w);
 }
+template <bool NT = true>
 __device__ __forceinline__ void st4(float* p, float4 v) {
     vfloat4 w;
     w.x = v.x;
     w.y = v.y;
     w.z = v.z;
     w.w = v.w;
-    __builtin_nontemporal_store(w, reinterpret_cast<vfloat4*>(p));
+    st_hint<NT>(reinterpret_cast<vfloat4*>(p), w);
 }
 
 typedef float vfloat2 __attribute__((ext_vector_type(2)));
@@ -44,19 +58,22 @@ __device__ __forceinline__ void st2(float* p, float2 v) {
 }
 // Guarded load of up to 2 floats; missing ones read as 0.
 __device__ __forceinline__ float2 ld2_partial(const float* p, int n) {
+    if (n >= 2) return ld2(p);
     float2 v = make_float2(0.f, 0.f);
     if (n > 0) v.x = p[0];
-    if (n > 1) v.y = p[1];
     return v;
 }
 
 // Guarded load of up to 4 floats; missing ones read as 0.
 __device__ __forceinline__ float4 ld4_partial(const float* p, int n) {
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (n > 0) v.x = p[0];
-    if (n > 1) v.y = p[1];
-    if (n > 2) v.z = p[2];
-    if (n > 3) v.w = p[3];
+    if (n > 0) {   // (indices held below n: no branch per float)
+        const float y = p[n > 1 ? 1 : 0], z = p[n > 2 ? 2 : 0], w = p[n > 3 ? 3 : 0];
+        v.x = p[0];
+        v.y = n > 1 ? y : 0.f;
+        v.z = n > 2 ? z : 0.f;
+        v.w = n > 3 ? w : 0.f;
+    }
     return v;
 }
 __device__ __forceinline__ void st4_partial(float* p, float4 v, int n) {
@@ -68,18 +85,29 @@ __device__ __forceinline__ void st4_partial(float* p, float4 v, int n) {
 
 __device__ __forceinline__ int clamp4(int64_t n) { return n >= 4 ? 4 : (n <= 0 ? 0 : (int)n); }
 
-// Every workgroup but the last of a launch covers whole 16-byte vectors only;
-// the kernels branch ONCE, uniformly, on that, so the common path has no
-// per-access bounds checks (FULL) and the ragged tail takes the guarded path.
-template <bool FULL>
+// Most workgroups of a launch cover whole 16-byte vectors only; the kernels branch ONCE,
+// uniformly, on that, so the common path has no per-access bounds checks (FULL).  In the others
+// (the window of a row's end, where n differs from lane to lane) a lane whose vector is whole
+// still moves it with one access and only the lane that straddles the end takes single floats:
+// with single floats in every lane those few workgroups took longer than the rest of the launch
+// ((P, s, d) = (45, 3, 1 200 000): 8 of the encoder's 296).
+template <bool FULL, bool NT = true>
 __device__ __forceinline__ float4 ldx(const float* p, int n) {
-    if constexpr (FULL) return ld4(p);
-    else return ld4_partial(p, n);
+    if constexpr (FULL) {
+        return ld4<NT>(p);
+    } else {
+        if (n >= 4) return ld4<NT>(p);
+        return ld4_partial(p, n);
+    }
 }
-template <bool FULL>
+template <bool FULL, bool NT = true>
 __device__ __forceinline__ void stx(float* p, float4 v, int n) {
-    if constexpr (FULL) st4(p, v);
-    else st4_partial(p, v, n);
+    if constexpr (FULL) {
+        st4<NT>(p, v);
+    } else {
+        if (n >= 4) st4<NT>(p, v);
+        else if (n > 0) st4_partial(p, v, n);
+    }
 }
 
 // --- second word of the two-word wire ------------------------------------------
@@ -109,8 +137,13 @@ __device__ __forceinline__ unsigned lo8_code(float hi, float lo) {
     const float t = ldexpf(lo * 254.0f, 150 - lo8_field(hi));
     return __float_as_uint(t + 12582912.0f);
 }
-__device__ __forceinline__ float lo8_value(float hi, int q) {
-    return ldexpf((float)q * (1.0f / 254.0f), lo8_field(hi) - 150);
+// hi + q u / 254 in fp64: the factor u / 254 is made from hi's exponent field with integer
+// instructions (the field goes into the upper word of the double 2^(E - 150) / 254), the rest is
+// one conversion of q and one multiply-add.
+__device__ __forceinline__ double lo8_plus(float hi, int q) {
+    const double c = 1.0 / 254.0;
+    const int up = __double2hiint(c) + ((lo8_field(hi) - 150) << 20);
+    return fma((double)q, __hiloint2double(up, __double2loint(c)), (double)hi);
 }
 
 // What one lane holds of the second word for its 4 values, as loaded.
@@ -119,11 +152,11 @@ template <> struct lo_raw<kLoBf16> { typedef vbf4 type; };
 template <> struct lo_raw<kLoI8> { typedef unsigned type; };
 template <int LO> using lo_raw_t = typename lo_raw<LO>::type;
 
-template <bool FULL, int LO>
+template <bool FULL, int LO, bool NT = true>
 __device__ __forceinline__ void st_lo(float* base, int64_t off, float4 hi, float4 v, int n) {
     static_assert(LO == kLoF32 || LO == kLoBf16 || LO == kLoI8, "a second word has a format");
     if constexpr (LO == kLoF32) {
-        stx<FULL>(base + off, v, n);
+        stx<FULL, NT>(base + off, v, n);
     } else if constexpr (LO == kLoBf16) {
         __bf16* p = reinterpret_cast<__bf16*>(base) + off;
         vfloat4 w;
@@ -132,72 +165,72 @@ __device__ __forceinline__ void st_lo(float* base, int64_t off, float4 hi, float
         w.z = v.z;
         w.w = v.w;
         const vbf4 b = __builtin_convertvector(w, vbf4);   // round to nearest even
-        if constexpr (FULL) {
-            __builtin_nontemporal_store(b, reinterpret_cast<vbf4*>(p));
+        if (FULL || n >= 4) {
+            st_hint<NT>(reinterpret_cast<vbf4*>(p), b);
         } else {
             if (n > 0) p[0] = b.x;
             if (n > 1) p[1] = b.y;
             if (n > 2) p[2] = b.z;
-            if (n > 3) p[3] = b.w;
         }
     } else {
         signed char* p = reinterpret_cast<signed char*>(base) + off;
         const unsigned q0 = lo8_code(hi.x, v.x), q1 = lo8_code(hi.y, v.y), q2 = lo8_code(hi.z, v.z),
                        q3 = lo8_code(hi.w, v.w);
-        if constexpr (FULL) {
+        if (FULL || n >= 4) {
             const unsigned w = (q0 & 0xFFu) | ((q1 & 0xFFu) << 8) | ((q2 & 0xFFu) << 16) | (q3 << 24);
-            __builtin_nontemporal_store(w, reinterpret_cast<unsigned*>(p));
+            st_hint<NT>(reinterpret_cast<unsigned*>(p), w);
         } else {
             if (n > 0) p[0] = (signed char)q0;
             if (n > 1) p[1] = (signed char)q1;
             if (n > 2) p[2] = (signed char)q2;
-            if (n > 3) p[3] = (signed char)q3;
         }
     }
 }
 // Load of a lane's 4 second words, unconverted (missing ones read as zero).
-template <bool FULL, int LO>
+template <bool FULL, int LO, bool NT = true>
 __device__ __forceinline__ lo_raw_t<LO> ld_lo(const float* base, int64_t off, int n) {
     static_assert(LO == kLoF32 || LO == kLoBf16 || LO == kLoI8, "a second word has a format");
     if constexpr (LO == kLoF32) {
-        return ldx<FULL>(base + off, n);
+        return ldx<FULL, NT>(base + off, n);
     } else if constexpr (LO == kLoBf16) {
         const __bf16* p = reinterpret_cast<const __bf16*>(base) + off;
-        if constexpr (FULL) {
-            return __builtin_nontemporal_load(reinterpret_cast<const vbf4*>(p));
+        if (FULL || n >= 4) {
+            return ld_hint<NT>(reinterpret_cast<const vbf4*>(p));
         } else {
             vbf4 b = {(__bf16)0.0f, (__bf16)0.0f, (__bf16)0.0f, (__bf16)0.0f};
             if (n > 0) b.x = p[0];
             if (n > 1) b.y = p[1];
             if (n > 2) b.z = p[2];
-            if (n > 3) b.w = p[3];
             return b;
         }
     } else {
         const unsigned char* p = reinterpret_cast<const unsigned char*>(base) + off;
-        if constexpr (FULL) {
-            return __builtin_nontemporal_load(reinterpret_cast<const unsigned*>(p));
+        if (FULL || n >= 4) {
+            return ld_hint<NT>(reinterpret_cast<const unsigned*>(p));
         } else {
             unsigned w = 0;
             if (n > 0) w |= (unsigned)p[0];
             if (n > 1) w |= (unsigned)p[1] << 8;
             if (n > 2) w |= (unsigned)p[2] << 16;
-            if (n > 3) w |= (unsigned)p[3] << 24;
             return w;
         }
     }
 }
-// The values a lane's 4 second words stand for, next to their first words.
+// The 4 values a lane's first and second words stand for, in fp64.
+struct wire4 {
+    double x, y, z, w;
+};
 template <int LO>
-__device__ __forceinline__ float4 lo_values(lo_raw_t<LO> raw, float4 hi) {
-    if constexpr (LO == kLoF32) {
-        return raw;
-    } else if constexpr (LO == kLoBf16) {
-        return make_float4((float)raw.x, (float)raw.y, (float)raw.z, (float)raw.w);
-    } else {
+__device__ __forceinline__ wire4 wire_value(float4 hi, lo_raw_t<LO> raw) {
+    if constexpr (LO == kLoNone) {
+        return {(double)hi.x, (double)hi.y, (double)hi.z, (double)hi.w};
+    } else if constexpr (LO == kLoI8) {
         const int w = (int)raw;
-        return make_float4(lo8_value(hi.x, (w << 24) >> 24), lo8_value(hi.y, (w << 16) >> 24),
-                           lo8_value(hi.z, (w << 8) >> 24), lo8_value(hi.w, w >> 24));
+        return {lo8_plus(hi.x, (w << 24) >> 24), lo8_plus(hi.y, (w << 16) >> 24), lo8_plus(hi.z, (w << 8) >> 24),
+                lo8_plus(hi.w, w >> 24)};
+    } else {   // a floating-point residual: the sum is exact
+        return {(double)hi.x + (double)(float)raw.x, (double)hi.y + (double)(float)raw.y,
+                (double)hi.z + (double)(float)raw.z, (double)hi.w + (double)(float)raw.w};
     }
 }
 // Stores with the format chosen at run time (kernels off the hot path).
@@ -239,24 +272,52 @@ constexpr int64_t kWindow = 32768;             // floats per footprint window (1
 constexpr int64_t kWaveStride = kWindow / 4;   // floats between a workgroup's wavefronts (32 KiB)
 constexpr int64_t kTilesPerWindow = kWaveStride / 256;
 
-// First float of the window piece this workgroup's wavefront 0 owns.
-__device__ __forceinline__ int64_t spread_base() {
-    const int64_t tile = blockIdx.x;
+// What is left of a row behind its last whole window goes to workgroups that own 4 KiB
+// contiguously, the first ones of the launch: cut by a window's pieces, it would leave every
+// workgroup of that window with the guarded path ((P, s, d) = (45, 3, 12 000 000), 0.2 windows left
+// over: the encoder's time falls by 3 %).
+__device__ __forceinline__ int64_t whole_windows(int64_t len) { return len / kWindow; }
+// First float this workgroup's wavefront 0 owns, and whether it owns window pieces.
+__device__ __forceinline__ int64_t spread_base(int64_t len, bool& pieces) {
+    const int64_t windows = whole_windows(len);
+    const int64_t rest = (int64_t)gridDim.x - windows * kTilesPerWindow;   // contiguous workgroups
+    const int64_t tile = (int64_t)blockIdx.x - rest;
+    pieces = tile >= 0;
+    if (!pieces) return windows * kWindow + (int64_t)blockIdx.x * (kBlock * 4);
     return (tile / kTilesPerWindow) * kWindow + (tile % kTilesPerWindow) * 256;
 }
-// Column (float index within a row) of this lane's 4 floats.
+// Column (float index within a row of len floats) of this lane's 4 floats.
 template <bool SPREAD>
-__device__ __forceinline__ int64_t lane_column() {
-    if constexpr (SPREAD)
-        return spread_base() + (int64_t)(threadIdx.x >> 6) * kWaveStride + (threadIdx.x & 63) * 4;
-    else
+__device__ __forceinline__ int64_t lane_column(int64_t len) {
+    if constexpr (SPREAD) {
+        bool pieces;
+        const int64_t base = spread_base(len, pieces);
+        return base + (int64_t)(threadIdx.x >> 6) * (pieces ? kWaveStride : 256) + (threadIdx.x & 63) * 4;
+    } else {
         return ((int64_t)blockIdx.x * kBlock + threadIdx.x) * 4;
+    }
 }
-// True when every lane of the workgroup has its 4 floats inside [0, len).
+// True when every lane of the workgroup has its 4 floats inside [0, need), need <= len.
 template <bool SPREAD>
-__device__ __forceinline__ bool block_is_full(int64_t len) {
-    if constexpr (SPREAD) return spread_base() + 3 * kWaveStride + 256 <= len;
-    else return (int64_t)(blockIdx.x + 1) * (kBlock * 4) <= len;
+__device__ __forceinline__ bool block_is_full(int64_t len, int64_t need) {
+    if constexpr (SPREAD) {
+        bool pieces;
+        const int64_t base = spread_base(len, pieces);
+        return base + 3 * (pieces ? kWaveStride : 256) + 256 <= need;
+    } else {
+        return (int64_t)(blockIdx.x + 1) * (kBlock * 4) <= need;
+    }
+}
+
+// --- rows off the line grid -----------------------------------------------------
+// A row stride that is no multiple of 32 floats puts row starts off the 128-byte lines (and off
+// any grid of the 8-bit slab), so both ends of every contiguous run a wavefront writes are parts
+// of lines.  Runs next to each other are then written by workgroups that share an L2: workgroup b
+// runs on accelerator die b mod 8, and tile xcd_tile() gives each die one contiguous range of
+// tiles, which its L2 merges if the stores carry no non-temporal hint.
+__device__ __forceinline__ int64_t xcd_tile() {
+    const int64_t per = gridDim.x / 8, b = blockIdx.x;
+    return b < per * 8 ? (b % 8) * per + b / 8 : b;
 }
 
 
@@ -286,7 +347,7 @@ inline unsigned grid_for(int64_t units_of_4_floats) {
 // Workgroups that cover a row of len floats with the footprint lane_column<SPREAD>() describes.
 template <bool SPREAD>
 inline unsigned grid_cols(int64_t len) {
-    if constexpr (SPREAD) return (unsigned)((len + kWindow - 1) / kWindow * kTilesPerWindow);
+    if constexpr (SPREAD) return (unsigned)(len / kWindow * kTilesPerWindow) + grid_for((len % kWindow + 3) / 4);
     else return grid_for((len + 3) / 4);
 }
 

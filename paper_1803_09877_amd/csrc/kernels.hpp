@@ -15,6 +15,9 @@ constexpr int kMaxCycS = 10;          // cyclic encoder: two complex per lane up
 constexpr int kProjectLoads = 8;      // float4 loads per lane per message row in the projection kernel
 constexpr int kMaxNodes = 256;        // DRACO_MAX_NODES
 constexpr int kMaskWords = 4;         // 64-bit words of node flags (kMaxNodes / 64)
+// Messages of a whole step (both words, bytes) up to which kernels count on the 256 MiB memory-side
+// cache: measured wins at 216 and 270 MB, losses at 450 MB and beyond.
+constexpr int64_t kSmallMessages = 320ll << 20;
 constexpr int kLocateMaxS = 16;       // largest s the on-device locator handles
 
 // Which kernel families spread a workgroup's wavefronts over a 128 KiB window of each row

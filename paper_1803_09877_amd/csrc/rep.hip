@@ -21,7 +21,7 @@ namespace draco {
 template <int R, int GU, bool FULL>
 __device__ __forceinline__ void encode_rep_body(const float* __restrict__ G, int64_t ldg, float* __restrict__ Z,
                                                 int64_t ldm, int groups, int64_t d) {
-    const int64_t c0 = lane_column<kSpreadEncodeRep>();
+    const int64_t c0 = lane_column<kSpreadEncodeRep>(d);
     if (!FULL && c0 >= d) return;
     const int n = FULL ? 4 : clamp4(d - c0);
     {
@@ -58,7 +58,7 @@ template <int R, int GU>
 __global__ __launch_bounds__(kBlock) void encode_rep_kernel(const float* __restrict__ G, int64_t ldg,
                                                             float* __restrict__ Z, int64_t ldm,
                                                             int groups, int64_t d) {
-    if (block_is_full<kSpreadEncodeRep>(d)) encode_rep_body<R, GU, true>(G, ldg, Z, ldm, groups, d);
+    if (block_is_full<kSpreadEncodeRep>(d, d)) encode_rep_body<R, GU, true>(G, ldg, Z, ldm, groups, d);
     else encode_rep_body<R, GU, false>(G, ldg, Z, ldm, groups, d);
 }
 
@@ -70,7 +70,7 @@ __device__ __forceinline__ void encode_rep_generic_body(const float* __restrict_
                                                         float* __restrict__ Z, int64_t ldm, int groups, int rows,
                                                         int copies, int64_t d) {
     constexpr int UN = 8;
-    const int64_t c0 = lane_column<kSpreadEncodeRep>();
+    const int64_t c0 = lane_column<kSpreadEncodeRep>(d);
     if (!FULL && c0 >= d) return;
     const int n = FULL ? 4 : clamp4(d - c0);
     {
@@ -106,7 +106,7 @@ __device__ __forceinline__ void encode_rep_generic_body(const float* __restrict_
 __global__ __launch_bounds__(kBlock) void encode_rep_generic_kernel(const float* __restrict__ G, int64_t ldg,
                                                                     float* __restrict__ Z, int64_t ldm,
                                                                     int groups, int rows, int copies, int64_t d) {
-    if (block_is_full<kSpreadEncodeRep>(d)) encode_rep_generic_body<true>(G, ldg, Z, ldm, groups, rows, copies, d);
+    if (block_is_full<kSpreadEncodeRep>(d, d)) encode_rep_generic_body<true>(G, ldg, Z, ldm, groups, rows, copies, d);
     else encode_rep_generic_body<false>(G, ldg, Z, ldm, groups, rows, copies, d);
 }
 
@@ -219,7 +219,7 @@ __device__ __forceinline__ uint4 vote_group(const uint4 (&x)[R], int first_node,
 template <int R, int GU, bool FULL>
 __device__ __forceinline__ void decode_rep_body(const float* __restrict__ Rm, int64_t ldm, float* __restrict__ u,
                                                 WaveFlags& wflags, int groups, int64_t d) {
-    const int64_t c0 = lane_column<kSpreadVote>();
+    const int64_t c0 = lane_column<kSpreadVote>(d);
     const bool active = FULL || c0 < d;
     const int n = FULL ? 4 : (active ? clamp4(d - c0) : 0);
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(kBlock) void decode_rep_kernel(const float* __restr
                                                             float* __restrict__ u, uint64_t* __restrict__ flags,
                                                             int groups, int64_t d) {
     WaveFlags wflags;
-    if (block_is_full<kSpreadVote>(d)) decode_rep_body<R, GU, true>(Rm, ldm, u, wflags, groups, d);
+    if (block_is_full<kSpreadVote>(d, d)) decode_rep_body<R, GU, true>(Rm, ldm, u, wflags, groups, d);
     else decode_rep_body<R, GU, false>(Rm, ldm, u, wflags, groups, d);
     publish_flags(wflags, flags);
 }
@@ -271,7 +271,7 @@ __device__ __forceinline__ void decode_rep_stream_body(const float* __restrict__
                                                        float* __restrict__ u, WaveFlags& wflags, int groups,
                                                        int r, int64_t d) {
     constexpr int UN = 8;
-    const int64_t c0 = lane_column<kSpreadVote>();
+    const int64_t c0 = lane_column<kSpreadVote>(d);
     const bool active = FULL || c0 < d;
     const int n = FULL ? 4 : (active ? clamp4(d - c0) : 0);
     auto fetch = [&](const float* p) -> uint4 {
@@ -321,7 +321,7 @@ __global__ __launch_bounds__(kBlock) void decode_rep_generic_kernel(const float*
                                                                     float* __restrict__ u, uint64_t* __restrict__ flags,
                                                                     int groups, int r, int64_t d) {
     WaveFlags wflags;
-    if (block_is_full<kSpreadVote>(d)) decode_rep_stream_body<true>(Rm, ldm, u, wflags, groups, r, d);
+    if (block_is_full<kSpreadVote>(d, d)) decode_rep_stream_body<true>(Rm, ldm, u, wflags, groups, r, d);
     else decode_rep_stream_body<false>(Rm, ldm, u, wflags, groups, r, d);
     publish_flags(wflags, flags);
 }
