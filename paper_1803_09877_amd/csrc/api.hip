@@ -51,7 +51,10 @@ struct draco_plan {
     double2* b_dev = nullptr;        // P
     double2* b0_dev = nullptr;       // P: recombination vector when no node is flagged
     double2* root_dev = nullptr;     // P: exp(2 pi i k / P)
-    int32_t* spec_dev = nullptr;     // 2 words: speculate next / speculated now (see cyc_decode.hip)
+    int32_t* spec_dev = nullptr;     // kSpecWords words (CycSpec::state)
+    uint64_t* spec_mask_dev = nullptr;   // kMaskWords: set located on a sample of the messages
+    double2* spec_b_dev = nullptr;   // P: its recombination vector
+    double2* sample_dev = nullptr;   // kSampleTiles * P
     bool speculation = true;
     uint64_t f_seed = 0;             // base seed of the generated projection vector (f_dev == NULL)
     uint64_t f_calls = 0;            // decodes that generated f since the base seed was set
@@ -86,6 +89,10 @@ bool unpacked(const draco_plan* p) { return p->wire == DRACO_WIRE_UNPACKED; }
 int lo_format(const draco_plan* p) {
     return p->second_word == DRACO_SECOND_WORD_BF16 ? kSecondWordBf16
            : p->second_word == DRACO_SECOND_WORD_I8 ? kSecondWordI8 : kSecondWordF32;
+}
+// Bytes of a value on the two-word wire.
+int wide_bytes(const draco_plan* p) {
+    return p->second_word == DRACO_SECOND_WORD_BF16 ? 6 : p->second_word == DRACO_SECOND_WORD_I8 ? 5 : 8;
 }
 double tau_of(const draco_plan* p, bool wide) {
     if (!wide) return kTauH;
@@ -151,7 +158,10 @@ int prepare(draco_plan* p) {
         HIP_TRY(hipMalloc(&p->gamma_dev, P * sizeof(double2)));
         HIP_TRY(hipMalloc(&p->b_dev, P * sizeof(double2)));
         HIP_TRY(hipMalloc(&p->b0_dev, P * sizeof(double2)));
-        HIP_TRY(hipMalloc(&p->spec_dev, 2 * sizeof(int32_t)));
+        HIP_TRY(hipMalloc(&p->spec_dev, kSpecWords * sizeof(int32_t)));
+        HIP_TRY(hipMalloc(&p->spec_mask_dev, kMaskWords * sizeof(uint64_t)));
+        HIP_TRY(hipMalloc(&p->spec_b_dev, P * sizeof(double2)));
+        HIP_TRY(hipMalloc(&p->sample_dev, (size_t)kSampleTiles * P * sizeof(double2)));
         {
             std::vector<uint8_t> none(P, 0);
             std::vector<cplx_t> b0;
@@ -169,7 +179,7 @@ int prepare(draco_plan* p) {
             }
             HIP_TRY(hipMalloc(&p->root_dev, P * sizeof(double2)));
             HIP_TRY(hipMemcpy(p->root_dev, t0.data(), P * sizeof(double2), hipMemcpyHostToDevice));
-            const int32_t init[2] = {1, 0};  // optimistic: the first decode speculates
+            const int32_t init[kSpecWords] = {1};  // optimistic: the first decode expects no adversary
             HIP_TRY(hipMemcpy(p->spec_dev, init, sizeof(init), hipMemcpyHostToDevice));
         }
         HIP_TRY(hipMalloc(&p->idx_dev, (P + 1) * sizeof(int32_t)));
@@ -273,6 +283,9 @@ void draco_plan_destroy(draco_plan* p) {
         (void)hipFree(p->b0_dev);
         (void)hipFree(p->root_dev);
         (void)hipFree(p->spec_dev);
+        (void)hipFree(p->spec_mask_dev);
+        (void)hipFree(p->spec_b_dev);
+        (void)hipFree(p->sample_dev);
         (void)hipFree(p->idx_dev);
         (void)hipFree(p->flags_dev);
         (void)hipHostFree(p->gamma_pin);
@@ -515,22 +528,34 @@ int decode_cyclic_async_impl(draco_plan* p, const float* hi_dev, const float* lo
     const float* lo = wide ? lo_dev : nullptr;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int P = p->P;
-    int32_t* spec = p->speculation ? p->spec_dev : nullptr;
+    const int64_t d = paired_len(p), tiles = project_tiles(d);
+    const int fmt = lo_format(p);
+    const double tau = tau_of(p, wide);
     const uint64_t seed = f_dev == nullptr ? next_projection_seed(p) : 0;
+    CycSpec spec{p->speculation && project_speculates(d, P) ? p->spec_dev : nullptr, nullptr, nullptr};
     {
         Timed timed(p, kProject, st);
-        HIP_TRY(launch_cyc_project(hi_dev, lo, lo_format(p), ld_m, f_dev, seed, p->partial_dev, p->gamma_dev, p->b0_dev,
-                                   sum_dev, unpacked(p), spec, P, paired_len(p), st));
+        if (spec.state != nullptr && P * message_len(p) * (wide ? wide_bytes(p) : 4) >= kSampledMessages) {
+            spec.mask = p->spec_mask_dev;
+            spec.b = p->spec_b_dev;
+            HIP_TRY(launch_cyc_sample(hi_dev, lo, fmt, ld_m, f_dev, seed, p->sample_dev, P, d, st));
+            HIP_TRY(launch_cyc_locate_sample(p->sample_dev, p->root_dev, P, p->s, tau, p->b0_dev, p->b_dev, p->idx_dev,
+                                             p->idx_dev + P, spec, st));
+        }
+        HIP_TRY(launch_cyc_project(hi_dev, lo, fmt, ld_m, f_dev, seed, p->partial_dev, p->b0_dev, sum_dev, unpacked(p),
+                                   spec, P, d, st));
+        if (tiles > kInlineTiles) HIP_TRY(launch_cyc_reduce(p->partial_dev, p->gamma_dev, P, tiles, st));
     }
     {
         Timed timed(p, kLocateKind, st);
-        HIP_TRY(launch_cyc_locate(p->gamma_dev, p->root_dev, P, p->s, tau_of(p, wide), p->b0_dev, mask_dev, status_dev,
-                                  p->b_dev, p->idx_dev, p->idx_dev + P, spec, st));
+        const bool inlined = tiles <= kInlineTiles;
+        HIP_TRY(launch_cyc_locate(inlined ? p->partial_dev : p->gamma_dev, inlined ? tiles : 0, p->root_dev, P, p->s, tau,
+                                  p->b0_dev, mask_dev, status_dev, p->b_dev, p->idx_dev, p->idx_dev + P, spec, st));
     }
     {
         Timed timed(p, kRecombine, st);
-        HIP_TRY(launch_cyc_recombine(hi_dev, lo, lo_format(p), ld_m, p->b_dev, p->idx_dev, p->idx_dev + P, spec, P, sum_dev,
-                                     unpacked(p), paired_len(p), st));
+        HIP_TRY(launch_cyc_recombine(hi_dev, lo, fmt, ld_m, p->b_dev, p->idx_dev, p->idx_dev + P, spec.state, P, sum_dev,
+                                     unpacked(p), d, st));
     }
     return DRACO_OK;
 }
@@ -546,8 +571,10 @@ int decode_cyclic_hostphi_impl(draco_plan* p, const float* hi_dev, const float* 
     const uint64_t seed = f_dev == nullptr ? next_projection_seed(p) : 0;
     {
         Timed timed(p, kProject, st);
-        HIP_TRY(launch_cyc_project(hi_dev, lo, lo_format(p), ld_m, f_dev, seed, p->partial_dev, p->gamma_dev, p->b0_dev,
-                                   sum_dev, unpacked(p), nullptr, P, paired_len(p), st));
+        const int64_t d = paired_len(p);
+        HIP_TRY(launch_cyc_project(hi_dev, lo, lo_format(p), ld_m, f_dev, seed, p->partial_dev, p->b0_dev, sum_dev,
+                                   unpacked(p), CycSpec{nullptr, nullptr, nullptr}, P, d, st));
+        HIP_TRY(launch_cyc_reduce(p->partial_dev, p->gamma_dev, P, project_tiles(d), st));
     }
     HIP_TRY(hipMemcpyAsync(p->gamma_pin, p->gamma_dev, P * sizeof(double2), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));

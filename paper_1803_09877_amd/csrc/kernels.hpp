@@ -12,7 +12,6 @@ namespace draco {
 constexpr int kBlock = 256;           // threads per workgroup (4 wavefronts of 64)
 constexpr int kMaxS = 7;              // repetition kernels are specialised for r = 2s+1 <= 15; larger r takes the generic path
 constexpr int kMaxCycS = 10;          // cyclic encoder: two complex per lane up to r = 21, one per lane up to r = 33, an LDS ring beyond
-constexpr int kProjectLoads = 8;      // float4 loads per lane per message row in the projection kernel
 constexpr int kMaxNodes = 256;        // DRACO_MAX_NODES
 constexpr int kMaskWords = 4;         // 64-bit words of node flags (kMaxNodes / 64)
 // Messages of a whole step (both words, bytes) up to which kernels count on the 256 MiB memory-side
@@ -78,29 +77,65 @@ hipError_t launch_encode_cyc_real_node(const float* Gn, int64_t ldg, float* z, c
                                        int P, int s, int64_t d, hipStream_t stream);
 hipError_t launch_encode_cyc_node(const float* Gn, int64_t ldg, float* z, float* zlo, int lo,
                                   const CycTaps& tab, int node, int P, int s, int64_t d, hipStream_t stream);
-// Number of workgroups (= rows of `partial`) the projection uses for gradient length d.
+// What a decode expects before it has located anybody (device memory of a plan).
+//   state[kSpecClean]  1 after a clean decode: the next call expects no adversary (unless it samples)
+//   state[kSpecNow]    what the projection pass of this call speculated on: 0, kSpecOnNobody, kSpecOnSample
+//   state[kSpecDone]   1 if the locator found that set: the output holds the sum already
+//   mask, b            the set located on a sample of this call's messages (kMaskWords) and its
+//                      recombination vector (P, dense); mask == nullptr where no sample is taken
+// state == nullptr: never speculate.
+enum : int { kSpecClean = 0, kSpecNow = 1, kSpecDone = 2, kSpecStatus = 3, kSpecWords = 4 };
+enum : int { kSpecOnNobody = 1, kSpecOnSample = 2 };
+struct CycSpec {
+    int32_t* state;
+    uint64_t* mask;
+    double2* b;
+};
+constexpr int kSampleTiles = 64;      // of 1024 floats
+constexpr int kInlineTiles = 64;      // partial sums up to which the locator adds them itself
+// Messages (both words, bytes) from which a decode locates the adversaries on a sample first and
+// then projects and recombines in ONE pass.  The sample and its locator take 15 to 30 us and the
+// joint pass 10 % more than a projection; the second pass they save runs at about 6.3 TB/s, so with
+// adversaries it breaks even near 250 MB.  A lie that the sample does not hold (it need not touch
+// every coordinate) costs the second pass, as it would without.
+constexpr int64_t kSampledMessages = 384ll << 20;
+
+// Number of workgroups (= rows of `partial`) the projection uses for gradient length d, and
+// whether it can speculate there (short rows are split over the nodes: they cannot).
 int64_t project_tiles(int64_t d);
-// partial[tile][P] <- per-tile sums of f_i * R[j][i]; gamma[P] <- their sum in tile order.
-// b0[P]: recombination vector for "no adversary"; u: output written speculatively when
-// spec_state[0] != 0 (spec_state: two device words, see cyc_decode.hip; nullptr = never).
+bool project_speculates(int64_t d, int P);
+// partial[tile][P] <- per-tile sums of f_i * R[j][i].  b0[P]: recombination vector for "no
+// adversary"; u: output written speculatively.
 // f == nullptr: the entries of f are generated from f_seed (projection_rng.hpp).
 // d is the number of floats a message carries (odd d: one more, zero); realout (unpacked
 // wire, messages of d/2 complex entries): u receives only the real parts, d/2 floats.
 hipError_t launch_cyc_project(const float* R, const float* Rlo, int lo, int64_t ldm, const float* f,
-                              uint64_t f_seed, double2* partial, double2* gamma, const double2* b0,
-                              float* u, bool realout, int32_t* spec_state, int P, int64_t d,
-                              hipStream_t stream);
+                              uint64_t f_seed, double2* partial, const double2* b0, float* u, bool realout,
+                              const CycSpec& spec, int P, int64_t d, hipStream_t stream);
+// The same sums for a sample of the columns, partial[kSampleTiles][P].
+hipError_t launch_cyc_sample(const float* R, const float* Rlo, int lo, int64_t ldm, const float* f, uint64_t f_seed,
+                             double2* partial, int P, int64_t d, hipStream_t stream);
+// gamma[P] <- the sum of partial[tiles][P] in tile order.
+hipError_t launch_cyc_reduce(const double2* partial, double2* gamma, int P, int64_t tiles, hipStream_t stream);
 // phi steps 2-4 and the recombination vector on the device (one wavefront, fp64; s <= kLocateMaxS):
-// gamma[P] -> mask words, status, and the honest nodes' (idx, b) compacted in ascending order with
-// their count in *nu_out.  roots[k] = exp(2 pi i k / P), k < P.  tau: relative zero threshold for syndromes.
-// With no located node the coefficients are copied from b0 (bit-identical to the speculative pass);
-// spec_state[0] <- 1 if this decode was clean (the next call speculates), else 0.
-hipError_t launch_cyc_locate(const double2* gamma, const double2* roots, int P, int s, double tau, const double2* b0,
-                             uint64_t* mask_out, int32_t* status_out, double2* b_out, int32_t* idx_out,
-                             int32_t* nu_out, int32_t* spec_state, hipStream_t stream);
-// u <- unpack( sum_{q < *nu} b[q] * R[idx[q]] ); nu is read from device memory.
+// gamma[P] (tiles == 0) or partial[tiles][P] (tiles <= kInlineTiles) -> mask words, status, and the
+// honest nodes' (idx, b) compacted in ascending order with their count in *nu_out.
+// roots[k] = exp(2 pi i k / P), k < P.  tau: relative zero threshold for syndromes.  With no located
+// node the coefficients are copied from b0.  b is a function of the set of flagged nodes.
+// spec.state: kSpecClean <- this decode was clean, kSpecDone <- the set found is the one
+// speculated on.
+hipError_t launch_cyc_locate(const double2* sums, int64_t tiles, const double2* roots, int P, int s, double tau,
+                             const double2* b0, uint64_t* mask_out, int32_t* status_out, double2* b_out,
+                             int32_t* idx_out, int32_t* nu_out, const CycSpec& spec, hipStream_t stream);
+// The same on the sums of a sample: spec.mask and spec.b <- the set found and its coefficients
+// (b_out, idx_out, nu_out are scratch).
+hipError_t launch_cyc_locate_sample(const double2* partial, const double2* roots, int P, int s, double tau,
+                                    const double2* b0, double2* b_out, int32_t* idx_out, int32_t* nu_out,
+                                    const CycSpec& spec, hipStream_t stream);
+// u <- unpack( sum_{q < *nu} b[q] * R[idx[q]] ); nu is read from device memory.  Nothing if
+// state[kSpecDone] is set (state may be nullptr).
 hipError_t launch_cyc_recombine(const float* R, const float* Rlo, int lo, int64_t ldm, const double2* b,
-                                const int32_t* idx, const int32_t* nu, const int32_t* spec_state, int P,
+                                const int32_t* idx, const int32_t* nu, const int32_t* state, int P,
                                 float* u, bool realout, int64_t d, hipStream_t stream);
 
 // params[i] <- params[i] - scale * sum[i], i < d (the model update of mini-batch SGD).

@@ -1,29 +1,110 @@
-// phi and the recombination vector on the device: the one-wavefront kernel around
-// locate_device.hpp.
+// phi and the recombination vector on the device: the kernels around locate_device.hpp.
 #include "locate_device.hpp"
 
 namespace draco {
 
-__global__ __launch_bounds__(kW) void cyc_locate_kernel(const double2* __restrict__ gamma,
-                                                        const double2* __restrict__ roots, int P, int s, double tau,
-                                                        const double2* __restrict__ b0,
-                                                        int32_t* __restrict__ spec_state, LocateOut out) {
-    __shared__ LocateSmem sm;
-    const int lane = threadIdx.x;
-    for (int j = lane; j < P; j += kW) {
-        sm.gam[j] = gamma[j];
-        sm.root[j] = roots[j];
+namespace {
+
+constexpr int kSumWaves = 8;   // wavefronts that add partial sums before the first one locates
+
+// sm.gam <- sums[P], or (TILES) the sum over t < tiles of sums[t][P]: each wavefront adds every
+// kSumWaves-th tile, then their sums are added in order.
+template <bool TILES>
+__device__ __forceinline__ void load_projections(LocateSmem& sm, double2 (*part)[kMaxNodes],
+                                                 const double2* __restrict__ sums, int64_t tiles,
+                                                 const double2* __restrict__ roots, int P) {
+    if constexpr (TILES) {
+        const int wave = threadIdx.x / kW, lane = threadIdx.x % kW;
+        for (int j = lane; j < P; j += kW) {
+            double2 a = make_double2(0.0, 0.0);
+#pragma unroll 8
+            for (int t = wave; t < (int)tiles; t += kSumWaves) {
+                const double2 p = sums[(int64_t)t * P + j];
+                a.x += p.x;
+                a.y += p.y;
+            }
+            part[wave][j] = a;
+        }
+        for (int j = threadIdx.x; j < P; j += kW * kSumWaves) sm.root[j] = roots[j];
+        __syncthreads();
+        for (int j = threadIdx.x; j < P; j += kW * kSumWaves) {
+            double2 a = part[0][j];
+#pragma unroll
+            for (int w = 1; w < kSumWaves; ++w) {
+                a.x += part[w][j].x;
+                a.y += part[w][j].y;
+            }
+            sm.gam[j] = a;
+        }
+        __syncthreads();
+    } else {
+        for (int j = threadIdx.x; j < P; j += kW) {
+            sm.gam[j] = sums[j];
+            sm.root[j] = roots[j];
+        }
+        wave_sync();
     }
-    wave_sync();
-    const bool clean = locate_wave(sm, P, s, tau, b0, out, lane);
-    if (lane == 0 && spec_state != nullptr) spec_state[0] = clean ? 1 : 0;
 }
 
-hipError_t launch_cyc_locate(const double2* gamma, const double2* roots, int P, int s, double tau, const double2* b0,
-                             uint64_t* mask_out, int32_t* status_out, double2* b_out, int32_t* idx_out,
-                             int32_t* nu_out, int32_t* spec_state, hipStream_t stream) {
-    const LocateOut out{mask_out, status_out, b_out, idx_out, nu_out};
-    hipLaunchKernelGGL(cyc_locate_kernel, dim3(1), dim3(kW), 0, stream, gamma, roots, P, s, tau, b0, spec_state, out);
+}  // namespace
+
+template <bool TILES>
+__global__ __launch_bounds__(TILES ? kW * kSumWaves : kW) void cyc_locate_kernel(
+    const double2* __restrict__ sums, int64_t tiles, const double2* __restrict__ roots, int P, int s, double tau,
+    const double2* __restrict__ b0, const CycSpec spec, const LocateOut out) {
+    __shared__ LocateSmem sm;
+    __shared__ double2 part[TILES ? kSumWaves : 1][kMaxNodes];
+    load_projections<TILES>(sm, part, sums, tiles, roots, P);
+    if (threadIdx.x >= kW) return;
+    const int lane = threadIdx.x;
+    const bool clean = locate_wave(sm, P, s, tau, b0, out, lane);
+    if (spec.state != nullptr) {
+        // the flagged nodes are the ones speculated on
+        const int now = spec.state[kSpecNow];
+        bool same = now != 0;
+        for (int c = 0; c < P; c += kW) {
+            const int j = c + lane;
+            const unsigned long long found = __ballot(j < P && sm.mask[j] != 0);
+            const unsigned long long expected = now == kSpecOnSample ? spec.mask[c / kW] : 0ull;
+            same &= found == expected;
+        }
+        if (lane == 0) {
+            spec.state[kSpecDone] = same ? 1 : 0;
+            spec.state[kSpecClean] = clean ? 1 : 0;
+        }
+    }
+}
+
+__global__ __launch_bounds__(kW * kSumWaves) void cyc_locate_sample_kernel(const double2* __restrict__ partial,
+                                                                           const double2* __restrict__ roots, int P, int s,
+                                                                           double tau, const double2* __restrict__ b0,
+                                                                           const LocateOut out) {
+    __shared__ LocateSmem sm;
+    __shared__ double2 part[kSumWaves][kMaxNodes];
+    load_projections<true>(sm, part, partial, kSampleTiles, roots, P);
+    if (threadIdx.x >= kW) return;
+    locate_wave(sm, P, s, tau, b0, out, threadIdx.x);
+}
+
+hipError_t launch_cyc_locate(const double2* sums, int64_t tiles, const double2* roots, int P, int s, double tau,
+                             const double2* b0, uint64_t* mask_out, int32_t* status_out, double2* b_out,
+                             int32_t* idx_out, int32_t* nu_out, const CycSpec& spec, hipStream_t stream) {
+    const LocateOut out{mask_out, status_out, b_out, idx_out, nu_out, nullptr};
+    if (tiles > 0)
+        hipLaunchKernelGGL(cyc_locate_kernel<true>, dim3(1), dim3(kW * kSumWaves), 0, stream, sums, tiles, roots, P, s, tau,
+                           b0, spec, out);
+    else
+        hipLaunchKernelGGL(cyc_locate_kernel<false>, dim3(1), dim3(kW), 0, stream, sums, tiles, roots, P, s, tau, b0, spec,
+                           out);
+    return hipGetLastError();
+}
+
+hipError_t launch_cyc_locate_sample(const double2* partial, const double2* roots, int P, int s, double tau,
+                                    const double2* b0, double2* b_out, int32_t* idx_out, int32_t* nu_out,
+                                    const CycSpec& spec, hipStream_t stream) {
+    const LocateOut out{spec.mask, spec.state + kSpecStatus, b_out, idx_out, nu_out, spec.b};
+    hipLaunchKernelGGL(cyc_locate_sample_kernel, dim3(1), dim3(kW * kSumWaves), 0, stream, partial, roots, P, s, tau, b0,
+                       out);
     return hipGetLastError();
 }
 

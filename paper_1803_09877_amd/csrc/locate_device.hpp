@@ -117,6 +117,7 @@ struct LocateOut {
     double2* b;          // honest nodes' coefficients, one behind the other
     int32_t* idx;        // and their indices
     int32_t* nu;         // how many
+    double2* dense;      // the coefficients by node (flagged ones untouched), or nullptr
 };
 
 template <class F, int... K>
@@ -693,6 +694,7 @@ __device__ __forceinline__ bool locate_wave(LocateSmem& sm, int P, int s, double
             const int pos = nu + __popcll(bal & ((1ull << lane) - 1ull));
             out.idx[pos] = j;
             out.b[pos] = acc;
+            if (out.dense != nullptr) out.dense[j] = acc;
         }
         nu += __popcll(bal);
     }

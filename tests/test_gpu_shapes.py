@@ -1,11 +1,13 @@
-"""Launch shapes: sizes at which the encoders change kernel or footprint (short rows split over the
-nodes, what is left behind the last 128 KiB window, row strides off the 128-byte grid), each
-against a form that does not change with size."""
+"""Launch shapes: sizes at which the encoders and the decoder change kernel, footprint or path (short
+rows split over the nodes, what is left behind the last 128 KiB window, row strides off the 128-byte
+grid, decodes that locate on a sample first), each against a form that does not change with size."""
+import numpy as np
 import pytest
 import torch
 
 from paper_1803_09877_amd import binding as B
 from paper_1803_09877_amd import synth
+from paper_1803_09877_amd.runner import Case
 
 pytestmark = pytest.mark.gpu
 
@@ -55,3 +57,56 @@ def test_all_node_encoder_equals_the_one_node_encoder(P, s, d, wire, line):
             assert bool(torch.isnan(Z[j, mlen:]).all()), j
     finally:
         plan.close()
+
+
+@pytest.mark.parametrize("P,s,d,wide,unpacked", [
+    (45, 3, 1_900_003, "i8", False), (45, 3, 2_400_000, False, False), (32, 4, 2_200_001, "bf16", False),
+    (45, 7, 1_200_001, "f32", False), (16, 2, 3_200_001, False, True),
+])
+def test_sampled_decode_equals_the_two_pass_decode(P, s, d, wide, unpacked):
+    """Messages of more than 384 MiB: a decode that expects adversaries locates them on a sample of
+    the columns and recombines while it projects.  Lies everywhere (the sample finds them), lies in
+    one coordinate that no sample holds (it does not: second pass), a broken message, nobody, and more
+    liars than s: masks, statuses and bits of a plan that never speculates."""
+    w = synth.Workload(name="sampled", code="cyc", P=P, s=s, d=d, sigma=1e-2, attacks=(), placement="any",
+                       seed=synth.SEED_BASE + 5)
+    c = Case(w, wide=wide, unpacked=unpacked)
+    ref = B.Plan(B.CODE_CYCLIC, P, s, d)
+    if unpacked:
+        ref.set_wire(B.WIRE_UNPACKED)
+    if wide:
+        ref.set_second_word(LO[wide][0])
+    ref.set_speculation(False)
+    u_ref = torch.zeros_like(c.u)
+    hidden = 5_000   # tiles of 1024 floats are sampled 18 or more tiles apart, from tile 0 on
+    try:
+        c.encode()
+        big = float(c.Z[:, :c.mlen].abs().max())
+        steps = [[(3, "all")], [(3, "all"), (P - 1, "all")][:s], [(7, "hidden")], [(7, "hidden"), (1, "all")][:s],
+                 [(2, "nan")], [], [], [(j, "all") for j in range(0, 2 * (s + 1), 2)], [(5, "all")]]
+        for step, liars in enumerate(steps):
+            c.receive()
+            for j, how in liars:
+                if how == "all":
+                    c.R[j, :c.mlen] = torch.randn(c.mlen, device="cuda:0") * big
+                elif how == "hidden":
+                    c.R[j, hidden] += 1e4 * big
+                else:
+                    c.R[j, c.mlen - 1] = float("nan")
+            c.u.fill_(float("nan"))
+            u_ref.fill_(float("nan"))
+            mask, status = c.decode()
+            if wide:
+                mask_ref, status_ref = ref.decode_cyclic_wide(c.R, c.Rlo, c.f, u_ref)
+            else:
+                mask_ref, status_ref = ref.decode_cyclic(c.R, c.f, u_ref)
+            torch.cuda.synchronize()
+            assert status == status_ref and np.array_equal(mask, mask_ref), step
+            if len(liars) <= s:
+                assert status == B.OK and sorted(np.flatnonzero(mask)) == sorted(j for j, _ in liars), step
+            else:
+                assert status == B.LOCATE_FAILED, step
+            assert torch.equal(c.u.view(torch.int32), u_ref.view(torch.int32)), step
+    finally:
+        ref.close()
+        c.close()
