@@ -62,7 +62,7 @@ struct draco_plan {
     int wire = DRACO_WIRE_PACKED;    // cyclic code: packed (ceil(d/2) complex) or unpacked (d complex)
     int second_word = DRACO_SECOND_WORD_F32;   // two-word wire: format of the second word
     int32_t* idx_dev = nullptr;      // P, then one more word: the number of honest nodes
-    uint64_t* flags_dev = nullptr;   // kMaskWords, zero between calls
+    uint64_t* flags_dev = nullptr;   // kVoteWords, zero between calls
     // pinned host staging
     double* gamma_pin = nullptr;     // 2P
     double* b_pin = nullptr;         // 2P
@@ -146,8 +146,8 @@ int prepare(draco_plan* p) {
     }
     HIP_TRY(hipGetDevice(&p->device));
     const int P = p->P, r = 2 * p->s + 1;
-    HIP_TRY(hipMalloc(&p->flags_dev, kMaskWords * sizeof(uint64_t)));
-    HIP_TRY(hipMemset(p->flags_dev, 0, kMaskWords * sizeof(uint64_t)));
+    HIP_TRY(hipMalloc(&p->flags_dev, kVoteWords * sizeof(uint64_t)));
+    HIP_TRY(hipMemset(p->flags_dev, 0, kVoteWords * sizeof(uint64_t)));
     // The synchronous decoders let the last kernel write mask and status straight into
     // mapped host memory: the host reads them after the stream wait, no copy commands.
     HIP_TRY(hipHostMalloc(&p->mask_pin, (kMaskWords + 1) * sizeof(uint64_t), hipHostMallocMapped));
@@ -464,11 +464,8 @@ int draco_decode_repetition_async(draco_plan* p, const float* messages_dev, int6
     rc = prepare(p);
     if (rc != DRACO_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    {
-        Timed timed(p, kVote, st);
-        HIP_TRY(launch_decode_rep_vote(messages_dev, ld_m, sum_dev, p->flags_dev, p->P, p->s, p->d, st));
-    }
-    HIP_TRY(launch_decode_rep_finish(p->flags_dev, mask_dev, status_dev, p->P, p->s, st));
+    Timed timed(p, kVote, st);
+    HIP_TRY(launch_decode_rep(messages_dev, ld_m, sum_dev, p->flags_dev, mask_dev, status_dev, p->P, p->s, p->d, st));
     return DRACO_OK;
 }
 

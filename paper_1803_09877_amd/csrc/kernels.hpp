@@ -14,6 +14,7 @@ constexpr int kMaxS = 7;              // repetition kernels are specialised for 
 constexpr int kMaxCycS = 10;          // cyclic encoder: two complex per lane up to r = 21, one per lane up to r = 33, an LDS ring beyond
 constexpr int kMaxNodes = 256;        // DRACO_MAX_NODES
 constexpr int kMaskWords = 4;         // 64-bit words of node flags (kMaxNodes / 64)
+constexpr int kVoteWords = kMaskWords + 1;   // and the vote's count of workgroups
 // Messages of a whole step (both words, bytes) up to which kernels count on the 256 MiB memory-side
 // cache: measured wins at 216 and 270 MB, losses at 450 MB and beyond.
 constexpr int64_t kSmallMessages = 320ll << 20;
@@ -34,13 +35,11 @@ hipError_t launch_encode_rep(const float* G, int64_t ldg, float* Z, int64_t ldm,
                              int64_t d, hipStream_t stream);
 hipError_t launch_encode_rep_node(const float* Gn, int64_t ldg, float* z, int s, int64_t d,
                                   hipStream_t stream);
-// ORs node flags into flags[kMaskWords] (must be zero on entry).
-hipError_t launch_decode_rep_vote(const float* R, int64_t ldm, float* u, uint64_t* flags, int P,
-                                  int s, int64_t d, hipStream_t stream);
-// mask_out <- flags; status_out <- NO_MAJORITY if a group has more than s flags; flags <- 0.
-hipError_t launch_decode_rep_finish(uint64_t* flags, uint64_t* mask_out, int32_t* status_out,
-                                    int P, int s, hipStream_t stream);
-// The vote and its finish on flag words held in a device array of the library itself (one per
+// The vote; mask_out <- node flags; status_out <- NO_MAJORITY if a group has more than s of them.
+// flags[kVoteWords] is scratch, zero on entry and left zero.
+hipError_t launch_decode_rep(const float* R, int64_t ldm, float* u, uint64_t* flags, uint64_t* mask_out,
+                             int32_t* status_out, int P, int s, int64_t d, hipStream_t stream);
+// The same on flag words held in a device array of the library itself (one per
 // GPU, shared by every call on that GPU): no allocation anywhere.
 hipError_t launch_decode_rep_static(const float* R, int64_t ldm, float* u, uint64_t* mask_out,
                                     int32_t* status_out, int P, int s, int64_t d, hipStream_t stream);

@@ -3,6 +3,7 @@
 #include "device_util.hpp"
 
 #include <mutex>
+#include <type_traits>
 
 namespace draco {
 
@@ -20,8 +21,7 @@ namespace draco {
 // flight per lane.
 template <int R, int GU, bool FULL>
 __device__ __forceinline__ void encode_rep_body(const float* __restrict__ G, int64_t ldg, float* __restrict__ Z,
-                                                int64_t ldm, int groups, int64_t d) {
-    const int64_t c0 = lane_column<kSpreadEncodeRep>(d);
+                                                int64_t ldm, int groups, int64_t d, int64_t c0) {
     if (!FULL && c0 >= d) return;
     const int n = FULL ? 4 : clamp4(d - c0);
     {
@@ -54,12 +54,30 @@ __device__ __forceinline__ void encode_rep_body(const float* __restrict__ G, int
     }
 }
 
-template <int R, int GU>
+// Column of this lane and whether its workgroup is whole: contiguous runs with neighbours on one die
+// where the rows written are off the line grid (LINES; device_util.hpp), else the spread footprint.
+// Measured, off the grid: (P, s, B, d) = (45, 2, 180, 1.66 M) 266 us against 282, (45, 2, 45, 11.2 M) 724
+// against 812; on it 257 against 246 and 648 against 609.
+template <bool LINES>
+__device__ __forceinline__ int64_t rep_column(int64_t d, bool& full) {
+    if constexpr (LINES) {
+        const int64_t tile = xcd_tile();
+        full = (tile + 1) * (kBlock * 4) <= d;
+        return (tile * kBlock + threadIdx.x) * 4;
+    } else {
+        full = block_is_full<kSpreadEncodeRep>(d, d);
+        return lane_column<kSpreadEncodeRep>(d);
+    }
+}
+
+template <int R, int GU, bool LINES>
 __global__ __launch_bounds__(kBlock) void encode_rep_kernel(const float* __restrict__ G, int64_t ldg,
                                                             float* __restrict__ Z, int64_t ldm,
                                                             int groups, int64_t d) {
-    if (block_is_full<kSpreadEncodeRep>(d, d)) encode_rep_body<R, GU, true>(G, ldg, Z, ldm, groups, d);
-    else encode_rep_body<R, GU, false>(G, ldg, Z, ldm, groups, d);
+    bool full;
+    const int64_t c0 = rep_column<LINES>(d, full);
+    if (full) encode_rep_body<R, GU, true>(G, ldg, Z, ldm, groups, d, c0);
+    else encode_rep_body<R, GU, false>(G, ldg, Z, ldm, groups, d, c0);
 }
 
 // Any number of rows per group (also the one-node form with groups = 1, copies = 1, and
@@ -68,9 +86,8 @@ __global__ __launch_bounds__(kBlock) void encode_rep_kernel(const float* __restr
 template <bool FULL>
 __device__ __forceinline__ void encode_rep_generic_body(const float* __restrict__ G, int64_t ldg,
                                                         float* __restrict__ Z, int64_t ldm, int groups, int rows,
-                                                        int copies, int64_t d) {
+                                                        int copies, int64_t d, int64_t c0) {
     constexpr int UN = 8;
-    const int64_t c0 = lane_column<kSpreadEncodeRep>(d);
     if (!FULL && c0 >= d) return;
     const int n = FULL ? 4 : clamp4(d - c0);
     {
@@ -78,36 +95,34 @@ __device__ __forceinline__ void encode_rep_generic_body(const float* __restrict_
         if (g >= groups) return;
         const float* src = G + (int64_t)g * rows * ldg + c0;
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        int i0 = 0;
-        for (; i0 + UN <= rows; i0 += UN) {   // whole rounds: no per-row checks
+        for (int i0 = 0; i0 < rows; i0 += UN) {   // (the last round's loads are in flight together too)
             float4 x[UN];
 #pragma unroll
-            for (int i = 0; i < UN; ++i) x[i] = ldx<FULL>(src + (int64_t)(i0 + i) * ldg, n);
+            for (int i = 0; i < UN; ++i)
+                if (i0 + i < rows) x[i] = ldx<FULL>(src + (int64_t)(i0 + i) * ldg, n);
 #pragma unroll
             for (int i = 0; i < UN; ++i) {
-                acc.x += x[i].x;
-                acc.y += x[i].y;
-                acc.z += x[i].z;
-                acc.w += x[i].w;
+                if (i0 + i < rows) {
+                    acc.x += x[i].x;
+                    acc.y += x[i].y;
+                    acc.z += x[i].z;
+                    acc.w += x[i].w;
+                }
             }
-        }
-        for (; i0 < rows; ++i0) {
-            const float4 x = ldx<FULL>(src + (int64_t)i0 * ldg, n);
-            acc.x += x.x;
-            acc.y += x.y;
-            acc.z += x.z;
-            acc.w += x.w;
         }
         float* dst = Z + (int64_t)g * copies * ldm + c0;
         for (int i = 0; i < copies; ++i) stx<FULL>(dst + (int64_t)i * ldm, acc, n);
     }
 }
 
+template <bool LINES>
 __global__ __launch_bounds__(kBlock) void encode_rep_generic_kernel(const float* __restrict__ G, int64_t ldg,
                                                                     float* __restrict__ Z, int64_t ldm,
                                                                     int groups, int rows, int copies, int64_t d) {
-    if (block_is_full<kSpreadEncodeRep>(d, d)) encode_rep_generic_body<true>(G, ldg, Z, ldm, groups, rows, copies, d);
-    else encode_rep_generic_body<false>(G, ldg, Z, ldm, groups, rows, copies, d);
+    bool full;
+    const int64_t c0 = rep_column<LINES>(d, full);
+    if (full) encode_rep_generic_body<true>(G, ldg, Z, ldm, groups, rows, copies, d, c0);
+    else encode_rep_generic_body<false>(G, ldg, Z, ldm, groups, rows, copies, d, c0);
 }
 
 // Majority candidate among R bit patterns of one coordinate (the streaming vote of
@@ -144,11 +159,55 @@ struct WaveFlags {
 };
 static_assert(kMaskWords == 4, "WaveFlags::set spells out four words");
 
-// OR the wavefront-uniform flag words of the four wavefronts of a workgroup
-// into the global flag words, touching global memory only for bits that are
-// not set there yet.
-__device__ __forceinline__ void publish_flags(const WaveFlags& wf, uint64_t* __restrict__ flags) {
+// Where a vote's flags go.  flags: kMaskWords words of node flags and one that counts workgroups, all
+// zero between calls.
+struct VoteOut {
+    uint64_t* flags;
+    uint64_t* mask;     // ceil(P/64) words
+    int32_t* status;
+    int P, s;
+    int finish;         // the last workgroup writes mask and status
+};
+
+// mask and status from the flag words, which are cleared for the next call.  Run by one wavefront
+// (a lane per group).
+__device__ __forceinline__ void finish_vote(const VoteOut& out) {
+    unsigned long long word[kMaskWords];
+    unsigned long long* flags = reinterpret_cast<unsigned long long*>(out.flags);
+#pragma unroll
+    for (int w = 0; w < kMaskWords; ++w) word[w] = __hip_atomic_load(flags + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int r = 2 * out.s + 1;
+    bool bad = false;
+    for (int g = threadIdx.x; g < out.P / r; g += 64) {
+        int cnt = 0;
+        for (int i = 0; i < r; ++i) {
+            const int node = g * r + i, w = node >> 6;
+            const unsigned long long bits = w == 0 ? word[0] : w == 1 ? word[1] : w == 2 ? word[2] : word[3];
+            cnt += (int)((bits >> (node & 63)) & 1ull);
+        }
+        bad |= cnt > out.s;   // DRACO_NO_MAJORITY
+    }
+    const bool any = __ballot(bad) != 0ull;
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int w = 0; w < kMaskWords; ++w) {
+            if (w < (out.P + 63) / 64) out.mask[w] = word[w];
+            __hip_atomic_store(flags + w, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __hip_atomic_store(flags + kMaskWords, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *out.status = any ? 1 : 0;
+    }
+}
+__global__ __launch_bounds__(64) void decode_rep_finish_kernel(const VoteOut out) { finish_vote(out); }
+
+// ORs the wavefront-uniform flag words of the four wavefronts of a workgroup into the global flag
+// words, touching global memory only for bits that are not set there yet.  In a small launch the
+// last workgroup to do so finishes the vote: a kernel of its own for that costs 4 us, an eighth of
+// the smallest step ((P, s, d) = (15, 1, 10 000): 33 us).  A large one cannot: the count is one
+// address, and 11 000 workgroups take 440 us to count themselves.
+__device__ __forceinline__ void publish_flags(const WaveFlags& wf, const VoteOut& out) {
     __shared__ unsigned long long sflags[kMaskWords];
+    __shared__ int last;
     if (threadIdx.x < kMaskWords) sflags[threadIdx.x] = 0ull;
     __syncthreads();
     if ((threadIdx.x & 63) == 0) {
@@ -158,14 +217,30 @@ __device__ __forceinline__ void publish_flags(const WaveFlags& wf, uint64_t* __r
         if (wf.w[3]) atomicOr(&sflags[3], (unsigned long long)wf.w[3]);
     }
     __syncthreads();
-    if (threadIdx.x < kMaskWords) {
-        const unsigned long long mine = sflags[threadIdx.x];
-        if (mine) {
-            unsigned long long* dst = reinterpret_cast<unsigned long long*>(flags) + threadIdx.x;
-            const unsigned long long cur = __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (mine & ~cur) atomicOr(dst, mine);
+    if (threadIdx.x == 0) {
+        unsigned long long* flags = reinterpret_cast<unsigned long long*>(out.flags);
+#pragma unroll
+        for (int w = 0; w < kMaskWords; ++w) {
+            const unsigned long long mine = sflags[w];
+            if (mine) {
+                const unsigned long long cur = __hip_atomic_load(flags + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (mine & ~cur) (void)__hip_atomic_fetch_or(flags + w, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
         }
+        last = 0;
+        if (out.finish == 0) return;
+        // The words and the count are only ever touched by device-scope atomics, which are performed
+        // where all dies see them; the fence waits until this workgroup's have been, before it
+        // counts.  (A device-scope release would write the die's L2 back in every workgroup.)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_waitcnt(0);
+        const unsigned long long before =
+            __hip_atomic_fetch_add(flags + kMaskWords, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last = before + 1 == (unsigned long long)gridDim.x ? 1 : 0;
     }
+    if (out.finish == 0) return;
+    __syncthreads();
+    if (last != 0 && threadIdx.x < 64) finish_vote(out);
 }
 
 // Vote of one group held in registers: returns the winner of each of the
@@ -254,12 +329,12 @@ __device__ __forceinline__ void decode_rep_body(const float* __restrict__ Rm, in
 
 template <int R, int GU>
 __global__ __launch_bounds__(kBlock) void decode_rep_kernel(const float* __restrict__ Rm, int64_t ldm,
-                                                            float* __restrict__ u, uint64_t* __restrict__ flags,
+                                                            float* __restrict__ u, const VoteOut out,
                                                             int groups, int64_t d) {
     WaveFlags wflags;
     if (block_is_full<kSpreadVote>(d, d)) decode_rep_body<R, GU, true>(Rm, ldm, u, wflags, groups, d);
     else decode_rep_body<R, GU, false>(Rm, ldm, u, wflags, groups, d);
-    publish_flags(wflags, flags);
+    publish_flags(wflags, out);
 }
 
 // Any r: the copies of a group stream through the vote's two words of state per
@@ -318,32 +393,13 @@ __device__ __forceinline__ void decode_rep_stream_body(const float* __restrict__
 }
 
 __global__ __launch_bounds__(kBlock) void decode_rep_generic_kernel(const float* __restrict__ Rm, int64_t ldm,
-                                                                    float* __restrict__ u, uint64_t* __restrict__ flags,
+                                                                    float* __restrict__ u, const VoteOut out,
                                                                     int groups, int r, int64_t d) {
     WaveFlags wflags;
     if (block_is_full<kSpreadVote>(d, d)) decode_rep_stream_body<true>(Rm, ldm, u, wflags, groups, r, d);
     else decode_rep_stream_body<false>(Rm, ldm, u, wflags, groups, r, d);
-    publish_flags(wflags, flags);
+    publish_flags(wflags, out);
 }
-
-__global__ void decode_rep_finish_kernel(uint64_t* __restrict__ flags, uint64_t* __restrict__ mask_out,
-                                         int32_t* __restrict__ status_out, int P, int s) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    const int r = 2 * s + 1;
-    int status = 0;
-    for (int g = 0; g < P / r; ++g) {
-        int cnt = 0;
-        for (int i = 0; i < r; ++i) {
-            const int node = g * r + i;
-            cnt += (int)((flags[node >> 6] >> (node & 63)) & 1ull);
-        }
-        if (cnt > s) status = 1;  // DRACO_NO_MAJORITY
-    }
-    for (int w = 0; w < (P + 63) / 64; ++w) mask_out[w] = flags[w];
-    for (int w = 0; w < kMaskWords; ++w) flags[w] = 0;
-    *status_out = status;
-}
-
 
 // ---------------------------------------------------------------------------
 // Launchers
@@ -352,6 +408,14 @@ __global__ void decode_rep_finish_kernel(uint64_t* __restrict__ flags, uint64_t*
 // Groups fetched per round (GU0 for r = 1, GU1 for r = 3, GU2 for r = 5, one group otherwise)
 // and workgroups per CU (BPC2 for r = 5, BPC otherwise):
 // keeps r * groups 16-byte loads in flight per lane.
+// Rows too short to fill the chip (few): more groups in flight instead, workgroups unlimited.
+#define DRACO_REP_FEW(KERNEL)                                                                                \
+    switch (s) {                                                                                             \
+        case 1: KERNEL(3, 5, 0); break;                                                                      \
+        case 2: KERNEL(5, 3, 0); break;                                                                      \
+        case 3: KERNEL(7, 2, 0); break;                                                                      \
+        default: few = false;                                                                                \
+    }
 #define DRACO_REP_DISPATCH(KERNEL, GU0, GU1, GU2, BPC, BPC2)                                          \
     switch (s) {                                                                           \
         case 0: KERNEL(1, GU0, BPC); break;                                        \
@@ -365,73 +429,87 @@ __global__ void decode_rep_finish_kernel(uint64_t* __restrict__ flags, uint64_t*
         default: generic = true;                                                           \
     }
 
+namespace {
+
+// Sums of `rows` rows per group, stored `copies` times.
+void launch_generic(const float* G, int64_t ldg, float* Z, int64_t ldm, int groups, int rows, int copies, int per_cu,
+                    int64_t d, hipStream_t stream) {
+    auto go = [&](auto lines) {
+        constexpr bool LINES = decltype(lines)::value;
+        const dim3 grid(grid_cols<!LINES && kSpreadEncodeRep>(d), (unsigned)groups);
+        allow_large_lds<encode_rep_generic_kernel<LINES>>();
+        hipLaunchKernelGGL(encode_rep_generic_kernel<LINES>, grid, dim3(kBlock), throttle_lds(per_cu, 0, 0), stream, G, ldg,
+                           Z, ldm, groups, rows, copies, d);
+    };
+    if (ldm % 32 != 0) go(std::true_type{});
+    else go(std::false_type{});
+}
+
+}  // namespace
+
 hipError_t launch_encode_rep(const float* G, int64_t ldg, float* Z, int64_t ldm, int P, int s, int64_t d,
                              hipStream_t stream) {
     const int r = 2 * s + 1, groups = P / r;
-    const unsigned tiles = grid_cols<kSpreadEncodeRep>(d);
+    const bool lines = ldm % 32 != 0;
+    const unsigned tiles = lines ? grid_cols<false>(d) : grid_cols<kSpreadEncodeRep>(d);
     const dim3 block(kBlock);
     bool generic = false;
+#define DRACO_LAUNCH_ON(R, GU, BPC, LINES)                                                                   \
+    {                                                                                                        \
+        allow_large_lds<encode_rep_kernel<R, GU, LINES>>();                                                  \
+        hipLaunchKernelGGL((encode_rep_kernel<R, GU, LINES>), dim3(tiles, (unsigned)((groups + GU - 1) / GU)),    \
+                           block, throttle_lds(BPC, 0, 0), stream, G, ldg, Z, ldm, groups, d);               \
+    }
 #define DRACO_LAUNCH(R, GU, BPC)                                                                             \
     {                                                                                                        \
-        allow_large_lds<encode_rep_kernel<R, GU>>();                                                         \
-        hipLaunchKernelGGL((encode_rep_kernel<R, GU>), dim3(tiles, (unsigned)((groups + GU - 1) / GU)),      \
-                           block, throttle_lds(BPC, 0, 0), stream, G, ldg, Z, ldm, groups, d);               \
+        if (lines) DRACO_LAUNCH_ON(R, GU, BPC, true)                                                         \
+        else DRACO_LAUNCH_ON(R, GU, BPC, false)                                                              \
     }
     DRACO_REP_DISPATCH(DRACO_LAUNCH, 8, 2, 1, 1, 2)
 #undef DRACO_LAUNCH
-    if (generic) {
-        allow_large_lds<encode_rep_generic_kernel>();
-        hipLaunchKernelGGL(encode_rep_generic_kernel, dim3(tiles, (unsigned)groups), block, throttle_lds(2, 0, 0),
-                           stream, G, ldg, Z, ldm, groups, r, r, d);
-    }
+#undef DRACO_LAUNCH_ON
+    if (generic) launch_generic(G, ldg, Z, ldm, groups, r, r, 2, d, stream);
     return hipGetLastError();
 }
 
 hipError_t launch_encode_rep_samples(const float* G, int64_t ldg, int m, float* Z, int64_t ldm, int P, int s, int64_t d,
                                      hipStream_t stream) {
-    const int r = 2 * s + 1, groups = P / r;
-    const dim3 grid(grid_cols<kSpreadEncodeRep>(d), (unsigned)groups), block(kBlock);
-    allow_large_lds<encode_rep_generic_kernel>();
-    hipLaunchKernelGGL(encode_rep_generic_kernel, grid, block, throttle_lds(2, 0, 0), stream, G, ldg, Z, ldm, groups,
-                       r * m, r, d);
+    const int r = 2 * s + 1;
+    launch_generic(G, ldg, Z, ldm, P / r, r * m, r, 2, d, stream);
     return hipGetLastError();
 }
 
 hipError_t launch_encode_rep_node(const float* Gn, int64_t ldg, float* z, int s, int64_t d, hipStream_t stream) {
-    const dim3 grid(grid_cols<kSpreadEncodeRep>(d)), block(kBlock);
-    hipLaunchKernelGGL(encode_rep_generic_kernel, grid, block, 0, stream, Gn, ldg, z, (int64_t)0, 1, 2 * s + 1, 1, d);
+    launch_generic(Gn, ldg, z, 0, 1, 2 * s + 1, 1, 0, d, stream);
     return hipGetLastError();
 }
 
-hipError_t launch_decode_rep_vote(const float* R, int64_t ldm, float* u, uint64_t* flags, int P, int s, int64_t d,
-                                  hipStream_t stream) {
+hipError_t launch_decode_rep(const float* R, int64_t ldm, float* u, uint64_t* flags, uint64_t* mask_out,
+                             int32_t* status_out, int P, int s, int64_t d, hipStream_t stream) {
     const int r = 2 * s + 1, groups = P / r;
     const dim3 block(kBlock);
     const dim3 grid(grid_cols<kSpreadVote>(d));
-    bool generic = false;
+    const int finish = grid.x < 256 ? 1 : 0;
+    const VoteOut out{flags, mask_out, status_out, P, s, finish};
+    constexpr size_t fixed = kMaskWords * sizeof(unsigned long long) + 8;   // static LDS of publish_flags
+    bool generic = false, few = grid.x < 256;
 #define DRACO_LAUNCH(R_, GU, BPC)                                                                               \
     {                                                                                                           \
-        allow_large_lds<decode_rep_kernel<R_, GU>>(kMaskWords * sizeof(unsigned long long));                                                           \
-        hipLaunchKernelGGL((decode_rep_kernel<R_, GU>), grid, block,                                            \
-                           throttle_lds(BPC, kMaskWords * sizeof(unsigned long long), 0), stream, R, ldm, u,    \
-                           flags, groups, d);                                                                   \
+        allow_large_lds<decode_rep_kernel<R_, GU>>(fixed);                                                      \
+        hipLaunchKernelGGL((decode_rep_kernel<R_, GU>), grid, block, throttle_lds(BPC, fixed, 0), stream, R, ldm, u,    \
+                           out, groups, d);                                                                     \
     }
+    if (few) DRACO_REP_FEW(DRACO_LAUNCH)
     // the vote over r = 5 copies is the one shape that runs faster with four workgroups per CU
     // (6.4 against 6.25 TB/s; every other r loses 4-5 % there)
-    DRACO_REP_DISPATCH(DRACO_LAUNCH, 4, 1, 1, 2, 4)
+    if (!few) DRACO_REP_DISPATCH(DRACO_LAUNCH, 4, 1, 1, 2, 4)
 #undef DRACO_LAUNCH
     if (generic) {
-        allow_large_lds<decode_rep_generic_kernel>(kMaskWords * sizeof(unsigned long long));
-        hipLaunchKernelGGL(decode_rep_generic_kernel, grid, block,
-                           throttle_lds(2, kMaskWords * sizeof(unsigned long long), 0), stream, R, ldm, u, flags,
+        allow_large_lds<decode_rep_generic_kernel>(fixed);
+        hipLaunchKernelGGL(decode_rep_generic_kernel, grid, block, throttle_lds(2, fixed, 0), stream, R, ldm, u, out,
                            groups, r, d);
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_decode_rep_finish(uint64_t* flags, uint64_t* mask_out, int32_t* status_out, int P, int s,
-                                    hipStream_t stream) {
-    hipLaunchKernelGGL(decode_rep_finish_kernel, dim3(1), dim3(64), 0, stream, flags, mask_out, status_out, P, s);
+    if (finish == 0) hipLaunchKernelGGL(decode_rep_finish_kernel, dim3(1), dim3(64), 0, stream, out);
     return hipGetLastError();
 }
 
@@ -442,16 +520,16 @@ hipError_t launch_decode_rep_finish(uint64_t* flags, uint64_t* mask_out, int32_t
 namespace {
 
 // Node flags of the allocation-free decoder: kMaskWords 64-bit words (one bit per node,
-// kMaxNodes nodes at most).  In host code this name is only a handle for
+// kMaxNodes nodes at most) and the count of workgroups.  In host code this name is only a handle for
 // hipGetSymbolAddress; kernels receive the address that call returns.
-static __device__ __align__(256) unsigned long long scratch[kMaskWords];
+static __device__ __align__(256) unsigned long long scratch[kVoteWords];
 
 constexpr int kMaxDevices = 64;
 uint64_t* g_scratch_ptr[kMaxDevices] = {};  // device address of `scratch` on each GPU, resolved once
 std::mutex g_scratch_mutex;
 
 __global__ void clear_flags_kernel(uint64_t* __restrict__ flags) {
-    if (blockIdx.x == 0 && threadIdx.x < kMaskWords) flags[threadIdx.x] = 0;
+    if (blockIdx.x == 0 && threadIdx.x < kVoteWords) flags[threadIdx.x] = 0;
 }
 
 // Address of the current device's copy of `scratch` (resolved on the first call per device).
@@ -484,9 +562,7 @@ hipError_t launch_decode_rep_static(const float* R, int64_t ldm, float* u, uint6
     hipLaunchKernelGGL(clear_flags_kernel, dim3(1), dim3(64), 0, stream, flags);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    e = launch_decode_rep_vote(R, ldm, u, flags, P, s, d, stream);
-    if (e != hipSuccess) return e;
-    return launch_decode_rep_finish(flags, mask_out, status_out, P, s, stream);
+    return launch_decode_rep(R, ldm, u, flags, mask_out, status_out, P, s, d, stream);
 }
 
 
