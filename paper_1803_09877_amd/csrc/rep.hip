@@ -204,7 +204,7 @@ __global__ __launch_bounds__(64) void decode_rep_finish_kernel(const VoteOut out
 // words, touching global memory only for bits that are not set there yet.  In a small launch the
 // last workgroup to do so finishes the vote: a kernel of its own for that costs 4 us, an eighth of
 // the smallest step ((P, s, d) = (15, 1, 10 000): 33 us).  A large one cannot: the count is one
-// address, and 11 000 workgroups take 440 us to count themselves.
+// address and takes about 40 ns a workgroup, so 11 000 of them would need 440 us.
 __device__ __forceinline__ void publish_flags(const WaveFlags& wf, const VoteOut& out) {
     __shared__ unsigned long long sflags[kMaskWords];
     __shared__ int last;
@@ -489,7 +489,7 @@ hipError_t launch_decode_rep(const float* R, int64_t ldm, float* u, uint64_t* fl
     const int r = 2 * s + 1, groups = P / r;
     const dim3 block(kBlock);
     const dim3 grid(grid_cols<kSpreadVote>(d));
-    const int finish = grid.x < 256 ? 1 : 0;
+    const int finish = grid.x < 64 ? 1 : 0;
     const VoteOut out{flags, mask_out, status_out, P, s, finish};
     constexpr size_t fixed = kMaskWords * sizeof(unsigned long long) + 8;   // static LDS of publish_flags
     bool generic = false, few = grid.x < 256;
