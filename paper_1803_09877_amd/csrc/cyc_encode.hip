@@ -249,7 +249,7 @@ hipError_t launch_encode_cyc_samples(const float* G, int64_t ldg, int m, float* 
     const int r = 2 * s + 1;
     if (s > kMaxCycS && s <= kMaxNarrowS) return launch_narrow(s, false, stream, G, ldg, m, Z, Zlo, lo, ldm, nullptr, tab, P, d);
 #define DRACO_CASE(S) \
-    case S: return launch_encode_cyc_multi_s<S>(grid, stream, G, ldg, m, Z, Zlo, lo, ldm, tab, P, d);
+    case S: return launch_encode_cyc_multi_s<S>(stream, G, ldg, m, Z, Zlo, lo, ldm, tab, P, d);
     switch (s) {
         DRACO_CASE(0) DRACO_CASE(1) DRACO_CASE(2) DRACO_CASE(3) DRACO_CASE(4) DRACO_CASE(5) DRACO_CASE(6) DRACO_CASE(7)
         DRACO_CASE(8) DRACO_CASE(9) DRACO_CASE(10)

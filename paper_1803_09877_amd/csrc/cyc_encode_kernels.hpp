@@ -147,8 +147,8 @@ __global__ __launch_bounds__(kBlock) void encode_cyc_kernel(const float* __restr
 // nodes, blockIdx.y the segment, and the rows that neighbouring segments share (2s of them) come
 // from the caches; no LDS, so the registers alone bound the workgroups per CU.  The window's rows
 // and the first round are in flight together.  Same taps in the same order: identical bits.
-template <int S, bool FULL, int LO>
-__device__ __forceinline__ void encode_cyc_small_body(const float* __restrict__ G, int64_t ldg, float* __restrict__ Z,
+template <int S, bool FULL, int LO, bool MULTI>
+__device__ __forceinline__ void encode_cyc_small_body(const float* __restrict__ G, int64_t ldg, int m, float* __restrict__ Z,
                                                       float* __restrict__ Zlo, int64_t ldm, const CycTaps tab, int P,
                                                       int64_t d, int64_t c0, int first, int last) {
     constexpr int R = 2 * S + 1;
@@ -157,14 +157,37 @@ __device__ __forceinline__ void encode_cyc_small_body(const float* __restrict__ 
     const int nin = FULL ? 4 : clamp4(d - c0);
     const int nout = FULL ? 4 : clamp4(mlen - c0);
     double wre[R][2], wim[R][2];  // window slot = (row - first) mod R
-    auto fetch = [&](int kappa) -> float4 {   // row of unwrapped index kappa < P + 2S
+    using unit_t = typename std::conditional<MULTI, double4, float4>::type;
+    auto fetch = [&](int kappa) -> unit_t {   // unit gradient of unwrapped index kappa < P + 2S
         const int k = kappa < P ? kappa : kappa - P;
-        return ldx<FULL, false>(G + (int64_t)k * ldg + c0, nin);
+        if constexpr (MULTI) {   // the sum of its m sample rows, ascending, in fp64
+            constexpr int UN = 4;
+            double4 acc = make_double4(0.0, 0.0, 0.0, 0.0);
+            const float* src = G + (int64_t)k * m * ldg + c0;
+            for (int i0 = 0; i0 < m; i0 += UN) {
+                float4 x[UN];
+#pragma unroll
+                for (int i = 0; i < UN; ++i)
+                    if (i0 + i < m) x[i] = ldx<FULL, false>(src + (int64_t)(i0 + i) * ldg, nin);
+#pragma unroll
+                for (int i = 0; i < UN; ++i) {
+                    if (i0 + i < m) {
+                        acc.x += (double)x[i].x;
+                        acc.y += (double)x[i].y;
+                        acc.z += (double)x[i].z;
+                        acc.w += (double)x[i].w;
+                    }
+                }
+            }
+            return acc;
+        } else {
+            return ldx<FULL, false>(G + (int64_t)k * ldg + c0, nin);
+        }
     };
-    auto put = [&](int slot, const float4& raw, int kappa) {
-        rotate_in(tab, kappa, (double)raw.x, (double)raw.y, (double)raw.z, (double)raw.w, wre[slot], wim[slot]);
+    auto put = [&](int slot, const unit_t& v, int kappa) {
+        rotate_in(tab, kappa, (double)v.x, (double)v.y, (double)v.z, (double)v.w, wre[slot], wim[slot]);
     };
-    float4 head[2 * S > 0 ? 2 * S : 1], buf[R];
+    unit_t head[2 * S > 0 ? 2 * S : 1], buf[R];
 #pragma unroll
     for (int k = 0; k < 2 * S; ++k) head[k] = fetch(first + k);
     auto issue = [&](int n0) {
@@ -190,16 +213,19 @@ __device__ __forceinline__ void encode_cyc_small_body(const float* __restrict__ 
     }
 }
 
-template <int S, int LO>
-__global__ __launch_bounds__(kBlock) void encode_cyc_small_kernel(const float* __restrict__ G, int64_t ldg,
+// MULTI: a unit gradient is the sum of m sample rows (B > P).
+template <int S, int LO, bool MULTI>
+__global__ __launch_bounds__(kBlock) void encode_cyc_small_kernel(const float* __restrict__ G, int64_t ldg, int m,
                                                                   float* __restrict__ Z, float* __restrict__ Zlo,
                                                                   int64_t ldm, const CycTaps tab, int P, int seg,
                                                                   int64_t d) {
     const int64_t tile = xcd_tile();
     const int64_t c0 = (tile * kBlock + threadIdx.x) * 4;
     const int first = (int)blockIdx.y * seg, last = min(P, first + seg);
-    if ((tile + 1) * (kBlock * 4) <= d) encode_cyc_small_body<S, true, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, c0, first, last);
-    else encode_cyc_small_body<S, false, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, c0, first, last);
+    if ((tile + 1) * (kBlock * 4) <= d)
+        encode_cyc_small_body<S, true, LO, MULTI>(G, ldg, m, Z, Zlo, ldm, tab, P, d, c0, first, last);
+    else
+        encode_cyc_small_body<S, false, LO, MULTI>(G, ldg, m, Z, Zlo, ldm, tab, P, d, c0, first, last);
 }
 
 // The same encoder with a wider lane: a lane owns C float4 of every row (its wavefront's C
@@ -416,11 +442,10 @@ template <int S, bool FULL, int LO>
 __device__ __forceinline__ void encode_cyc_multi_body(const float* __restrict__ G, int64_t ldg, int m,
                                                       float* __restrict__ Z, float* __restrict__ Zlo, int64_t ldm,
                                                       const CycTaps tab, int P, int64_t d,
-                                                      double4* head /* LDS [2S][kBlock] */) {
+                                                      int64_t c0, double4* head /* LDS [2S][kBlock] */) {
     constexpr int R = 2 * S + 1;
     constexpr int UN = 4;
     const int64_t mlen = 2 * ((d + 1) / 2);
-    const int64_t c0 = lane_column<kSpreadEncodeCyc>(mlen);
     if (!FULL && c0 >= mlen) return;
     const int nin = FULL ? 4 : clamp4(d - c0);
     const int nout = FULL ? 4 : clamp4(mlen - c0);
@@ -503,10 +528,9 @@ template <int S, int D, bool FULL, int LO>
 __device__ __forceinline__ void encode_cyc_multi_ring_body(const float* __restrict__ G, int64_t ldg, int m,
                                                            float* __restrict__ Z, float* __restrict__ Zlo,
                                                            int64_t ldm, const CycTaps tab, int P,
-                                                           int64_t d, double4* head /* LDS [2S][kBlock] */) {
+                                                           int64_t d, int64_t c0, double4* head /* LDS [2S][kBlock] */) {
     constexpr int R = 2 * S + 1;
     const int64_t mlen = 2 * ((d + 1) / 2);
-    const int64_t c0 = lane_column<kSpreadEncodeCyc>(mlen);
     if (!FULL && c0 >= mlen) return;
     const int nin = FULL ? 4 : clamp4(d - c0);
     const int nout = FULL ? 4 : clamp4(mlen - c0);
@@ -575,10 +599,9 @@ template <int S, bool FULL, int LO>
 __device__ __forceinline__ void encode_cyc_multi_four_body(const float* __restrict__ G, int64_t ldg,
                                                            float* __restrict__ Z, float* __restrict__ Zlo,
                                                            int64_t ldm, const CycTaps tab, int P,
-                                                           int64_t d, double4* head /* LDS [2S][kBlock] */) {
+                                                           int64_t d, int64_t c0, double4* head /* LDS [2S][kBlock] */) {
     constexpr int R = 2 * S + 1;
     const int64_t mlen = 2 * ((d + 1) / 2);
-    const int64_t c0 = lane_column<kSpreadEncodeCyc>(mlen);
     if (!FULL && c0 >= mlen) return;
     const int nin = FULL ? 4 : clamp4(d - c0);
     const int nout = FULL ? 4 : clamp4(mlen - c0);
@@ -644,38 +667,58 @@ __device__ __forceinline__ void encode_cyc_multi_four_body(const float* __restri
     }
 }
 
+// Column of this lane and whether its workgroup is whole: contiguous runs with neighbours on one die
+// where message rows are off the line grid (device_util.hpp), else the spread footprint.  Measured at
+// (45, 5, B = 180), 6 000 001 floats on the 5-byte wire: 1052 us against 1263 (951-1024 at 6 000 000).
+__device__ __forceinline__ int64_t multi_column(int lines, int64_t d, bool& full) {
+    if (lines != 0) {
+        const int64_t tile = xcd_tile();
+        full = (tile + 1) * (kBlock * 4) <= d;
+        return (tile * kBlock + threadIdx.x) * 4;
+    }
+    const int64_t mlen = 2 * ((d + 1) / 2);
+    full = block_is_full<kSpreadEncodeCyc>(mlen, d);
+    return lane_column<kSpreadEncodeCyc>(mlen);
+}
+
 template <int S, int LO>
 __global__ __launch_bounds__(kBlock) void encode_cyc_multi_four_kernel(const float* __restrict__ G, int64_t ldg,
                                                                        float* __restrict__ Z, float* __restrict__ Zlo,
                                                                        int64_t ldm, const CycTaps tab,
-                                                                       int P, int64_t d) {
+                                                                       int P, int lines, int64_t d) {
     extern __shared__ double4 head_sums[];  // [2S][kBlock]
-    if (block_is_full<kSpreadEncodeCyc>(2 * ((d + 1) / 2), d))
-        encode_cyc_multi_four_body<S, true, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, head_sums);
+    bool full;
+    const int64_t c0 = multi_column(lines, d, full);
+    if (full)
+        encode_cyc_multi_four_body<S, true, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, c0, head_sums);
     else
-        encode_cyc_multi_four_body<S, false, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, head_sums);
+        encode_cyc_multi_four_body<S, false, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, c0, head_sums);
 }
 
 template <int S, int D, int LO>
 __global__ __launch_bounds__(kBlock) void encode_cyc_multi_ring_kernel(const float* __restrict__ G, int64_t ldg, int m,
                                                                        float* __restrict__ Z, float* __restrict__ Zlo,
                                                                        int64_t ldm, const CycTaps tab,
-                                                                       int P, int64_t d) {
+                                                                       int P, int lines, int64_t d) {
     extern __shared__ double4 head_sums[];  // [2S][kBlock]
-    if (block_is_full<kSpreadEncodeCyc>(2 * ((d + 1) / 2), d))
-        encode_cyc_multi_ring_body<S, D, true, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, d, head_sums);
+    bool full;
+    const int64_t c0 = multi_column(lines, d, full);
+    if (full)
+        encode_cyc_multi_ring_body<S, D, true, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, d, c0, head_sums);
     else
-        encode_cyc_multi_ring_body<S, D, false, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, d, head_sums);
+        encode_cyc_multi_ring_body<S, D, false, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, d, c0, head_sums);
 }
 
 template <int S, int LO>
 __global__ __launch_bounds__(kBlock) void encode_cyc_multi_kernel(const float* __restrict__ G, int64_t ldg, int m,
                                                                   float* __restrict__ Z, float* __restrict__ Zlo,
                                                                   int64_t ldm, const CycTaps tab,
-                                                                  int P, int64_t d) {
+                                                                  int P, int lines, int64_t d) {
     extern __shared__ double4 head_sums[];  // [2S][kBlock]
-    if (block_is_full<kSpreadEncodeCyc>(2 * ((d + 1) / 2), d)) encode_cyc_multi_body<S, true, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, d, head_sums);
-    else encode_cyc_multi_body<S, false, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, d, head_sums);
+    bool full;
+    const int64_t c0 = multi_column(lines, d, full);
+    if (full) encode_cyc_multi_body<S, true, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, d, c0, head_sums);
+    else encode_cyc_multi_body<S, false, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, d, c0, head_sums);
 }
 
 
@@ -691,7 +734,7 @@ hipError_t launch_encode_cyc_real_s(bool one_per_cu, dim3 grid, hipStream_t stre
                                     float* Z, int64_t ldm, const double2* coef, int P, int64_t d);
 // Same for the B > P form (m per-sample rows per unit gradient).
 template <int S>
-hipError_t launch_encode_cyc_multi_s(dim3 grid, hipStream_t stream, const float* G, int64_t ldg, int m, float* Z,
+hipError_t launch_encode_cyc_multi_s(hipStream_t stream, const float* G, int64_t ldg, int m, float* Z,
                                      float* Zlo, int lo, int64_t ldm, const CycTaps& tab, int P, int64_t d);
 
 }  // namespace draco

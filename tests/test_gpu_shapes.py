@@ -59,6 +59,35 @@ def test_all_node_encoder_equals_the_one_node_encoder(P, s, d, wire, line):
         plan.close()
 
 
+@pytest.mark.parametrize("P,s,m,wire", [(45, 3, 4, "i8"), (15, 2, 16, "one"), (9, 1, 3, "bf16"), (24, 7, 2, "f32"),
+                                        (16, 0, 8, "one")])
+def test_sample_encoder_does_not_depend_on_row_length_or_stride(P, s, m, wire):
+    """B > P: columns do not mix and every form adds in the same order, so the leading columns of a long
+    row (whole walk; stride on and off the 128-byte grid) and of short ones (split over the nodes)
+    carry the same bits."""
+    long = 300_002
+    G = synth.make_gradients(P * m, long, 1.0, 3, device="cuda:0", ld=synth.padded_len(long))
+    got = []
+    for d, line in ((long, 128), (long, 4), (20_002, 4), (1_022, 128), (6, 4)):
+        plan = B.Plan(B.CODE_CYCLIC, P, s, d)
+        ld = (d + line - 1) // line * line + (line if line == 128 else 0)
+        Z = torch.full((P, ld), float("nan"), device="cuda:0")
+        if wire == "one":
+            plan.encode_samples(G, Z)
+            got.append((d, Z, None))
+        else:
+            plan.set_second_word(LO[wire][0])
+            Zlo = torch.zeros((P, ld), dtype=LO[wire][1], device="cuda:0")
+            plan.encode_samples_wide(G, Z, Zlo)
+            got.append((d, Z, Zlo))
+        torch.cuda.synchronize()
+        plan.close()
+    for d, Z, Zlo in got[1:]:
+        assert torch.equal(Z[:, :d].contiguous().view(torch.int32), got[0][1][:, :d].contiguous().view(torch.int32)), d
+        if Zlo is not None:
+            assert torch.equal(Zlo[:, :d].contiguous().view(torch.uint8), got[0][2][:, :d].contiguous().view(torch.uint8)), d
+
+
 @pytest.mark.parametrize("P,s,d,wide,unpacked", [
     (45, 3, 1_900_003, "i8", False), (45, 3, 2_400_000, False, False), (32, 4, 2_200_001, "bf16", False),
     (45, 7, 1_200_001, "f32", False), (16, 2, 3_200_001, False, True),
