@@ -299,12 +299,14 @@ int draco_projection_vector(const draco_plan* plan, uint64_t seed, float* f_host
 
 /* Speculative single-pass decode (cyclic code, s <= 16; on by default).  While
  * the projection pass of draco_decode_cyclic* has a row in registers it can also
- * accumulate the recombination for "no adversary" and write it to sum_dev; if
- * phi then flags nobody -- the usual case in training -- that is the decoded sum
- * (bit-identical to what the second pass would give) and the second pass over
- * the messages is skipped, which halves the decode.  A plan speculates in a
- * call when its previous decode was clean (the first call does), so a run with
- * persistent adversaries pays for one wasted speculation only.  0 switches it off. */
+ * accumulate the recombination for a predicted set of adversaries and write it to
+ * sum_dev; if phi on the full projection then finds that set, that is the decoded
+ * sum (bit-identical to what the second pass would give) and the second pass over
+ * the messages is skipped, which halves the decode.  Messages below 384 MiB: the
+ * prediction is "nobody", made when the plan's previous decode was clean (the first
+ * call counts as one).  Larger ones: the set that phi finds on a sample of the
+ * columns of this call's messages, so adversaries that lie everywhere cost no second
+ * pass, persistent or not.  0 switches it off. */
 int draco_plan_set_speculation(draco_plan* plan, int enabled);
 
 /* Same, stream-ordered (s <= 16 only, else DRACO_EINVAL): mask_dev
