@@ -229,13 +229,10 @@ __device__ __forceinline__ void publish_flags(const WaveFlags& wf, const VoteOut
         }
         last = 0;
         if (out.finish == 0) return;
-        // The words and the count are only ever touched by device-scope atomics, which are performed
-        // where all dies see them; the fence waits until this workgroup's have been, before it
-        // counts.  (A device-scope release would write the die's L2 back in every workgroup.)
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_s_waitcnt(0);
+        // Releases this workgroup's flags with its count and acquires those of the workgroups before
+        // it, so the last one reads every flag.
         const unsigned long long before =
-            __hip_atomic_fetch_add(flags + kMaskWords, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_fetch_add(flags + kMaskWords, 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
         last = before + 1 == (unsigned long long)gridDim.x ? 1 : 0;
     }
     if (out.finish == 0) return;

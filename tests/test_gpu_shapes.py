@@ -139,3 +139,34 @@ def test_sampled_decode_equals_the_two_pass_decode(P, s, d, wide, unpacked):
     finally:
         ref.close()
         c.close()
+
+
+@pytest.mark.parametrize("P,s,d", [(15, 1, 10_000), (255, 2, 64_512), (45, 7, 40_001), (9, 4, 1)])
+def test_small_votes_flag_what_the_last_workgroups_see(P, s, d):
+    """Votes of fewer than 64 workgroups: the last one to finish writes mask and status.  Two hundred
+    calls one behind the other, each with its liar (a node of its own, one coordinate, hence one
+    workgroup) moved: no flag is lost and none is left for the next call."""
+    n = 200
+    plan = B.Plan(B.CODE_REPETITION, P, s, d)
+    ld = synth.padded_len(d)
+    R = torch.zeros((P, ld), device="cuda:0")
+    row = torch.randn(d, device="cuda:0")
+    R[:, :d] = row
+    u = torch.zeros(ld, device="cuda:0")
+    masks = torch.full((n, 4), -1, dtype=torch.int64, device="cuda:0")
+    status = torch.full((n,), -7, dtype=torch.int32, device="cuda:0")
+    try:
+        for i in range(n):
+            j, c = (7 * i) % P, (1031 * i + 5) % d
+            R[j, c] += 1.0
+            plan.decode_repetition_async(R, u, masks[i], status[i:i + 1])
+            R[j, c] = row[c]
+        torch.cuda.synchronize()
+        got = masks.cpu().numpy().view(np.uint64)
+        for i in range(n):
+            assert np.flatnonzero(B.mask_to_bool(got[i], P)).tolist() == [(7 * i) % P], i
+        assert bool((status == B.OK).all())
+        k = P // (2 * s + 1)   # k - 1 rounded adds of equal values
+        assert bool(((u[:d] - k * row).abs() <= k * 2.0**-24 * (k * row).abs()).all())
+    finally:
+        plan.close()
