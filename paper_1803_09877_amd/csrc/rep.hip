@@ -159,18 +159,18 @@ struct WaveFlags {
 };
 static_assert(kMaskWords == 4, "WaveFlags::set spells out four words");
 
-// Where a vote's flags go.  flags: kMaskWords words of node flags and one that counts workgroups, all
-// zero between calls.
+// Where a vote's flags go.  flags: kMaskWords words of node flags (and, for votes that finish
+// themselves, one that counts workgroups), all zero between calls.
 struct VoteOut {
     uint64_t* flags;
     uint64_t* mask;     // ceil(P/64) words
     int32_t* status;
     int P, s;
-    int finish;         // the last workgroup writes mask and status
 };
 
-// mask and status from the flag words, which are cleared for the next call.  Run by one wavefront
-// (a lane per group).
+// mask and status from the flag words, which are cleared for the next call (COUNTED: with the count).
+// Run by one wavefront (a lane per group).
+template <bool COUNTED>
 __device__ __forceinline__ void finish_vote(const VoteOut& out) {
     unsigned long long word[kMaskWords];
     unsigned long long* flags = reinterpret_cast<unsigned long long*>(out.flags);
@@ -194,20 +194,20 @@ __device__ __forceinline__ void finish_vote(const VoteOut& out) {
             if (w < (out.P + 63) / 64) out.mask[w] = word[w];
             __hip_atomic_store(flags + w, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        __hip_atomic_store(flags + kMaskWords, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if constexpr (COUNTED) __hip_atomic_store(flags + kMaskWords, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         *out.status = any ? 1 : 0;
     }
 }
-__global__ __launch_bounds__(64) void decode_rep_finish_kernel(const VoteOut out) { finish_vote(out); }
+__global__ __launch_bounds__(64) void decode_rep_finish_kernel(const VoteOut out) { finish_vote<false>(out); }
 
 // ORs the wavefront-uniform flag words of the four wavefronts of a workgroup into the global flag
-// words, touching global memory only for bits that are not set there yet.  In a small launch the
-// last workgroup to do so finishes the vote: a kernel of its own for that costs 4 us, an eighth of
-// the smallest step ((P, s, d) = (15, 1, 10 000): 33 us).  A large one cannot: the count is one
-// address and takes about 40 ns a workgroup, so 11 000 of them would need 440 us.
+// words, touching global memory only for bits that are not set there yet.  FINISH (small launches):
+// the last workgroup to do so finishes the vote; a kernel of its own for that costs 4 us, an eighth of
+// the smallest step ((P, s, d) = (15, 1, 10 000): 32 us against 33).  A large launch cannot: the count
+// is one address and takes about 40 ns a workgroup, so 11 000 of them would need 440 us.
+template <bool FINISH>
 __device__ __forceinline__ void publish_flags(const WaveFlags& wf, const VoteOut& out) {
     __shared__ unsigned long long sflags[kMaskWords];
-    __shared__ int last;
     if (threadIdx.x < kMaskWords) sflags[threadIdx.x] = 0ull;
     __syncthreads();
     if ((threadIdx.x & 63) == 0) {
@@ -217,27 +217,30 @@ __device__ __forceinline__ void publish_flags(const WaveFlags& wf, const VoteOut
         if (wf.w[3]) atomicOr(&sflags[3], (unsigned long long)wf.w[3]);
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long* flags = reinterpret_cast<unsigned long long*>(out.flags);
-#pragma unroll
-        for (int w = 0; w < kMaskWords; ++w) {
-            const unsigned long long mine = sflags[w];
-            if (mine) {
-                const unsigned long long cur = __hip_atomic_load(flags + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (mine & ~cur) (void)__hip_atomic_fetch_or(flags + w, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+    unsigned long long* flags = reinterpret_cast<unsigned long long*>(out.flags);
+    auto publish = [&](int w) {
+        const unsigned long long mine = sflags[w];
+        if (mine) {
+            const unsigned long long cur = __hip_atomic_load(flags + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (mine & ~cur) (void)__hip_atomic_fetch_or(flags + w, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        last = 0;
-        if (out.finish == 0) return;
-        // Releases this workgroup's flags with its count and acquires those of the workgroups before
-        // it, so the last one reads every flag.
-        const unsigned long long before =
-            __hip_atomic_fetch_add(flags + kMaskWords, 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        last = before + 1 == (unsigned long long)gridDim.x ? 1 : 0;
+    };
+    if constexpr (!FINISH) {
+        if (threadIdx.x < kMaskWords) publish(threadIdx.x);
+    } else {
+        __shared__ int last;
+        if (threadIdx.x == 0) {
+#pragma unroll
+            for (int w = 0; w < kMaskWords; ++w) publish(w);
+            // Releases this workgroup's flags with its count and acquires those of the workgroups before
+            // it, so the last one reads every flag.
+            const unsigned long long before =
+                __hip_atomic_fetch_add(flags + kMaskWords, 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+            last = before + 1 == (unsigned long long)gridDim.x ? 1 : 0;
+        }
+        __syncthreads();
+        if (last != 0 && threadIdx.x < 64) finish_vote<true>(out);
     }
-    if (out.finish == 0) return;
-    __syncthreads();
-    if (last != 0 && threadIdx.x < 64) finish_vote(out);
 }
 
 // Vote of one group held in registers: returns the winner of each of the
@@ -324,14 +327,14 @@ __device__ __forceinline__ void decode_rep_body(const float* __restrict__ Rm, in
     if (active) stx<FULL>(u + c0, acc, n);
 }
 
-template <int R, int GU>
+template <int R, int GU, bool FINISH>
 __global__ __launch_bounds__(kBlock) void decode_rep_kernel(const float* __restrict__ Rm, int64_t ldm,
                                                             float* __restrict__ u, const VoteOut out,
                                                             int groups, int64_t d) {
     WaveFlags wflags;
     if (block_is_full<kSpreadVote>(d, d)) decode_rep_body<R, GU, true>(Rm, ldm, u, wflags, groups, d);
     else decode_rep_body<R, GU, false>(Rm, ldm, u, wflags, groups, d);
-    publish_flags(wflags, out);
+    publish_flags<FINISH>(wflags, out);
 }
 
 // Any r: the copies of a group stream through the vote's two words of state per
@@ -389,40 +392,33 @@ __device__ __forceinline__ void decode_rep_stream_body(const float* __restrict__
     if (active) stx<FULL>(u + c0, acc, n);
 }
 
+template <bool FINISH>
 __global__ __launch_bounds__(kBlock) void decode_rep_generic_kernel(const float* __restrict__ Rm, int64_t ldm,
                                                                     float* __restrict__ u, const VoteOut out,
                                                                     int groups, int r, int64_t d) {
     WaveFlags wflags;
     if (block_is_full<kSpreadVote>(d, d)) decode_rep_stream_body<true>(Rm, ldm, u, wflags, groups, r, d);
     else decode_rep_stream_body<false>(Rm, ldm, u, wflags, groups, r, d);
-    publish_flags(wflags, out);
+    publish_flags<FINISH>(wflags, out);
 }
 
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
 
-// Groups fetched per round (GU0 for r = 1, GU1 for r = 3, GU2 for r = 5, one group otherwise)
-// and workgroups per CU (BPC2 for r = 5, BPC otherwise):
-// keeps r * groups 16-byte loads in flight per lane.
-// Rows too short to fill the chip (few): more groups in flight instead, workgroups unlimited.
-#define DRACO_REP_FEW(KERNEL)                                                                                \
-    switch (s) {                                                                                             \
-        case 1: KERNEL(3, 5, 0); break;                                                                      \
-        case 2: KERNEL(5, 3, 0); break;                                                                      \
-        case 3: KERNEL(7, 2, 0); break;                                                                      \
-        default: few = false;                                                                                \
-    }
-#define DRACO_REP_DISPATCH(KERNEL, GU0, GU1, GU2, BPC, BPC2)                                          \
+// Groups fetched per round (GU0 .. GU3 for r = 1, 3, 5, 7, one group otherwise) and workgroups per CU
+// (BPC1 .. BPC3 for r = 3, 5, 7, BPC otherwise; 0: unlimited): keeps r * groups 16-byte loads in flight
+// per lane.
+#define DRACO_REP_DISPATCH(KERNEL, GU0, GU1, BPC1, GU2, BPC2, GU3, BPC3, BPC)              \
     switch (s) {                                                                           \
-        case 0: KERNEL(1, GU0, BPC); break;                                        \
-        case 1: KERNEL(3, GU1, BPC); break;                                        \
-        case 2: KERNEL(5, GU2, BPC2); break;                                          \
-        case 3: KERNEL(7, 1, BPC); break;                                          \
-        case 4: KERNEL(9, 1, BPC); break;                                          \
-        case 5: KERNEL(11, 1, BPC); break;                                         \
-        case 6: KERNEL(13, 1, BPC); break;                                         \
-        case 7: KERNEL(15, 1, BPC); break;                                         \
+        case 0: KERNEL(1, GU0, BPC); break;                                                \
+        case 1: KERNEL(3, GU1, BPC1); break;                                               \
+        case 2: KERNEL(5, GU2, BPC2); break;                                               \
+        case 3: KERNEL(7, GU3, BPC3); break;                                               \
+        case 4: KERNEL(9, 1, BPC); break;                                                  \
+        case 5: KERNEL(11, 1, BPC); break;                                                 \
+        case 6: KERNEL(13, 1, BPC); break;                                                 \
+        case 7: KERNEL(15, 1, BPC); break;                                                 \
         default: generic = true;                                                           \
     }
 
@@ -462,7 +458,7 @@ hipError_t launch_encode_rep(const float* G, int64_t ldg, float* Z, int64_t ldm,
         if (lines) DRACO_LAUNCH_ON(R, GU, BPC, true)                                                         \
         else DRACO_LAUNCH_ON(R, GU, BPC, false)                                                              \
     }
-    DRACO_REP_DISPATCH(DRACO_LAUNCH, 8, 2, 1, 1, 2)
+    DRACO_REP_DISPATCH(DRACO_LAUNCH, 8, 2, 1, 1, 2, 1, 1, 1)
 #undef DRACO_LAUNCH
 #undef DRACO_LAUNCH_ON
     if (generic) launch_generic(G, ldg, Z, ldm, groups, r, r, 2, d, stream);
@@ -481,32 +477,47 @@ hipError_t launch_encode_rep_node(const float* Gn, int64_t ldg, float* z, int s,
     return hipGetLastError();
 }
 
-hipError_t launch_decode_rep(const float* R, int64_t ldm, float* u, uint64_t* flags, uint64_t* mask_out,
-                             int32_t* status_out, int P, int s, int64_t d, hipStream_t stream) {
-    const int r = 2 * s + 1, groups = P / r;
-    const dim3 block(kBlock);
-    const dim3 grid(grid_cols<kSpreadVote>(d));
-    const int finish = grid.x < 64 ? 1 : 0;
-    const VoteOut out{flags, mask_out, status_out, P, s, finish};
-    constexpr size_t fixed = kMaskWords * sizeof(unsigned long long) + 8;   // static LDS of publish_flags
-    bool generic = false, few = grid.x < 256;
-#define DRACO_LAUNCH(R_, GU, BPC)                                                                               \
-    {                                                                                                           \
-        allow_large_lds<decode_rep_kernel<R_, GU>>(fixed);                                                      \
-        hipLaunchKernelGGL((decode_rep_kernel<R_, GU>), grid, block, throttle_lds(BPC, fixed, 0), stream, R, ldm, u,    \
-                           out, groups, d);                                                                     \
+namespace {
+
+// The vote, with its finish in the same launch (FINISH) or in a kernel of its own.  FEW: rows too short
+// to fill the chip take more groups at a time, workgroups unlimited.
+template <bool FEW, bool FINISH>
+void launch_vote(const float* R, int64_t ldm, float* u, const VoteOut& out, int64_t d, hipStream_t stream) {
+    const int s = out.s, r = 2 * s + 1, groups = out.P / r;
+    const dim3 grid(grid_cols<kSpreadVote>(d)), block(kBlock);
+    constexpr size_t fixed = kMaskWords * sizeof(unsigned long long) + (FINISH ? 8 : 0);   // static LDS of publish_flags
+    bool generic = false;
+#define DRACO_LAUNCH(R_, GU, BPC)                                                                                  \
+    {                                                                                                              \
+        allow_large_lds<decode_rep_kernel<R_, GU, FINISH>>(fixed);                                                 \
+        hipLaunchKernelGGL((decode_rep_kernel<R_, GU, FINISH>), grid, block, throttle_lds(BPC, fixed, 0), stream,  \
+                           R, ldm, u, out, groups, d);                                                             \
     }
-    if (few) DRACO_REP_FEW(DRACO_LAUNCH)
-    // the vote over r = 5 copies is the one shape that runs faster with four workgroups per CU
-    // (6.4 against 6.25 TB/s; every other r loses 4-5 % there)
-    if (!few) DRACO_REP_DISPATCH(DRACO_LAUNCH, 4, 1, 1, 2, 4)
+    if constexpr (FEW) {
+        DRACO_REP_DISPATCH(DRACO_LAUNCH, 4, 5, 0, 3, 0, 2, 0, 2)
+    } else {
+        // the vote over r = 5 copies is the one shape that runs faster with four workgroups per CU
+        // (6.4 against 6.25 TB/s; every other r loses 4-5 % there)
+        DRACO_REP_DISPATCH(DRACO_LAUNCH, 4, 1, 2, 1, 4, 1, 2, 2)
+    }
 #undef DRACO_LAUNCH
     if (generic) {
-        allow_large_lds<decode_rep_generic_kernel>(fixed);
-        hipLaunchKernelGGL(decode_rep_generic_kernel, grid, block, throttle_lds(2, fixed, 0), stream, R, ldm, u, out,
-                           groups, r, d);
+        allow_large_lds<decode_rep_generic_kernel<FINISH>>(fixed);
+        hipLaunchKernelGGL(decode_rep_generic_kernel<FINISH>, grid, block, throttle_lds(2, fixed, 0), stream, R, ldm, u,
+                           out, groups, r, d);
     }
-    if (finish == 0) hipLaunchKernelGGL(decode_rep_finish_kernel, dim3(1), dim3(64), 0, stream, out);
+    if constexpr (!FINISH) hipLaunchKernelGGL(decode_rep_finish_kernel, dim3(1), dim3(64), 0, stream, out);
+}
+
+}  // namespace
+
+hipError_t launch_decode_rep(const float* R, int64_t ldm, float* u, uint64_t* flags, uint64_t* mask_out,
+                             int32_t* status_out, int P, int s, int64_t d, hipStream_t stream) {
+    const unsigned workgroups = grid_cols<kSpreadVote>(d);
+    const VoteOut out{flags, mask_out, status_out, P, s};
+    if (workgroups < 64) launch_vote<true, true>(R, ldm, u, out, d, stream);
+    else if (workgroups < 256) launch_vote<true, false>(R, ldm, u, out, d, stream);
+    else launch_vote<false, false>(R, ldm, u, out, d, stream);
     return hipGetLastError();
 }
 
