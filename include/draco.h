@@ -234,7 +234,8 @@ int draco_decode_repetition_async(draco_plan* plan, const float* messages_dev, i
  * inside the library's code object: every GPU the library runs on holds one copy until the
  * process ends, and EVERY call on a GPU uses that GPU's copy, so two calls that overlap on
  * one GPU (different streams, or graphs replayed concurrently) race on it and must be
- * ordered by the caller.  The array is cleared by a small kernel at the start of each
+ * ordered by the caller (if they are not, each still writes its mask and status, but one
+ * call's flags may show in the other's or be lost).  The array is cleared by a small kernel at the start of each
  * call.  The first call on a device looks up the array's address (no stream work): make
  * that call outside stream capture.
  *   P, s, d       the code, as for draco_plan_create with DRACO_CODE_REPETITION:

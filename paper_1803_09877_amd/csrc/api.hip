@@ -465,7 +465,8 @@ int draco_decode_repetition_async(draco_plan* p, const float* messages_dev, int6
     if (rc != DRACO_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
     Timed timed(p, kVote, st);
-    HIP_TRY(launch_decode_rep(messages_dev, ld_m, sum_dev, p->flags_dev, mask_dev, status_dev, p->P, p->s, p->d, st));
+    HIP_TRY(launch_decode_rep(messages_dev, ld_m, sum_dev, p->flags_dev, mask_dev, status_dev, true, p->P, p->s, p->d,
+                              st));
     return DRACO_OK;
 }
 

@@ -36,9 +36,10 @@ hipError_t launch_encode_rep(const float* G, int64_t ldg, float* Z, int64_t ldm,
 hipError_t launch_encode_rep_node(const float* Gn, int64_t ldg, float* z, int s, int64_t d,
                                   hipStream_t stream);
 // The vote; mask_out <- node flags; status_out <- NO_MAJORITY if a group has more than s of them.
-// flags[kVoteWords] is scratch, zero on entry and left zero.
+// flags[kMaskWords] is scratch, zero on entry and left zero; counted: it holds one word more, which
+// lets the last workgroup of a small launch write mask and status (flags no other call uses).
 hipError_t launch_decode_rep(const float* R, int64_t ldm, float* u, uint64_t* flags, uint64_t* mask_out,
-                             int32_t* status_out, int P, int s, int64_t d, hipStream_t stream);
+                             int32_t* status_out, bool counted, int P, int s, int64_t d, hipStream_t stream);
 // The same on flag words held in a device array of the library itself (one per
 // GPU, shared by every call on that GPU): no allocation anywhere.
 hipError_t launch_decode_rep_static(const float* R, int64_t ldm, float* u, uint64_t* mask_out,

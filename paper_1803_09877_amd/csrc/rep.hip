@@ -512,10 +512,10 @@ void launch_vote(const float* R, int64_t ldm, float* u, const VoteOut& out, int6
 }  // namespace
 
 hipError_t launch_decode_rep(const float* R, int64_t ldm, float* u, uint64_t* flags, uint64_t* mask_out,
-                             int32_t* status_out, int P, int s, int64_t d, hipStream_t stream) {
+                             int32_t* status_out, bool counted, int P, int s, int64_t d, hipStream_t stream) {
     const unsigned workgroups = grid_cols<kSpreadVote>(d);
     const VoteOut out{flags, mask_out, status_out, P, s};
-    if (workgroups < 64) launch_vote<true, true>(R, ldm, u, out, d, stream);
+    if (counted && workgroups < 64) launch_vote<true, true>(R, ldm, u, out, d, stream);
     else if (workgroups < 256) launch_vote<true, false>(R, ldm, u, out, d, stream);
     else launch_vote<false, false>(R, ldm, u, out, d, stream);
     return hipGetLastError();
@@ -528,16 +528,16 @@ hipError_t launch_decode_rep(const float* R, int64_t ldm, float* u, uint64_t* fl
 namespace {
 
 // Node flags of the allocation-free decoder: kMaskWords 64-bit words (one bit per node,
-// kMaxNodes nodes at most) and the count of workgroups.  In host code this name is only a handle for
+// kMaxNodes nodes at most).  In host code this name is only a handle for
 // hipGetSymbolAddress; kernels receive the address that call returns.
-static __device__ __align__(256) unsigned long long scratch[kVoteWords];
+static __device__ __align__(256) unsigned long long scratch[kMaskWords];
 
 constexpr int kMaxDevices = 64;
 uint64_t* g_scratch_ptr[kMaxDevices] = {};  // device address of `scratch` on each GPU, resolved once
 std::mutex g_scratch_mutex;
 
 __global__ void clear_flags_kernel(uint64_t* __restrict__ flags) {
-    if (blockIdx.x == 0 && threadIdx.x < kVoteWords) flags[threadIdx.x] = 0;
+    if (blockIdx.x == 0 && threadIdx.x < kMaskWords) flags[threadIdx.x] = 0;
 }
 
 // Address of the current device's copy of `scratch` (resolved on the first call per device).
@@ -570,7 +570,9 @@ hipError_t launch_decode_rep_static(const float* R, int64_t ldm, float* u, uint6
     hipLaunchKernelGGL(clear_flags_kernel, dim3(1), dim3(64), 0, stream, flags);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_decode_rep(R, ldm, u, flags, mask_out, status_out, P, s, d, stream);
+    // not counted: another call's workgroups would be counted too, and then neither call's mask and
+    // status might be written
+    return launch_decode_rep(R, ldm, u, flags, mask_out, status_out, false, P, s, d, stream);
 }
 
 

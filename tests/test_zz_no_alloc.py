@@ -132,3 +132,25 @@ def test_static_decoder_inside_a_captured_graph():
             assert torch.equal(u[:w.d].view(torch.int32), ref_u[:w.d].view(torch.int32)), it
     finally:
         c.close()
+
+
+def test_overlapping_static_decoders_each_write_their_outputs():
+    """Calls that overlap race on the library's flag words (the header says so), but every call writes its
+    own mask and status: four streams, small votes (fewer than 64 workgroups) and larger ones, nobody
+    lying, so the only right mask is empty."""
+    dev = torch.device("cuda:0")
+    P, s, n = 9, 1, 64
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    for d in (4_000, 60_000, 200_003):
+        ld = synth.padded_len(d)
+        R = torch.randn(ld, device=dev).repeat(P, 1).contiguous()
+        u = torch.zeros((4, ld), device=dev)
+        mask = torch.full((n, 4), -1, dtype=torch.int64, device=dev)
+        status = torch.full((n,), -7, dtype=torch.int32, device=dev)
+        B.draco_decode_repetition_static(P, s, d, R, u[0], mask[0], status[:1])
+        torch.cuda.synchronize()
+        for i in range(n):
+            B.draco_decode_repetition_static(P, s, d, R, u[i % 4], mask[i], status[i:i + 1], stream=streams[i % 4])
+        torch.cuda.synchronize()
+        assert bool((status == B.OK).all()) and bool((mask[:, 0] == 0).all()), d
+        assert bool((mask[:, 1:] == -1).all()), d
