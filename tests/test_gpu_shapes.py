@@ -59,6 +59,33 @@ def test_all_node_encoder_equals_the_one_node_encoder(P, s, d, wire, line):
         plan.close()
 
 
+@pytest.mark.parametrize("P,s,d,m,wire", [(45, 3, 30_000, 1, "one"), (45, 3, 30_001, 1, "i8"), (9, 1, 700_003, 1, "one"),
+                                          (24, 7, 50_001, 1, "f32"), (15, 2, 20_001, 4, "one"), (45, 3, 1_100_001, 1, "one")])
+def test_encoder_in_place(P, s, d, m, wire):
+    """Messages written over the gradients they are made of (first words over the slab's first P rows):
+    the bits of an encoder with a slab of its own, on short rows too, where the encoder is otherwise
+    split over the nodes."""
+    plan = B.Plan(B.CODE_CYCLIC, P, s, d)
+    if wire != "one":
+        plan.set_second_word(LO[wire][0])
+    mlen = 2 * ((d + 1) // 2)
+    ld = synth.padded_len(mlen)
+    G = synth.make_gradients(P * m, d, 1.0, 17, device="cuda:0", ld=ld)
+    Z = torch.zeros((P, ld), device="cuda:0")
+    try:
+        if wire == "one":
+            plan.encode_samples(G, Z)
+            plan.encode_samples(G, G[:P])
+        else:
+            Zlo, Glo = (torch.zeros((P, ld), dtype=LO[wire][1], device="cuda:0") for _ in range(2))
+            plan.encode_samples_wide(G, Z, Zlo)
+            plan.encode_samples_wide(G, G[:P], Glo)
+            assert torch.equal(Zlo[:, :mlen].contiguous().view(torch.uint8), Glo[:, :mlen].contiguous().view(torch.uint8))
+        assert torch.equal(Z[:, :mlen].contiguous().view(torch.int32), G[:P, :mlen].contiguous().view(torch.int32))
+    finally:
+        plan.close()
+
+
 @pytest.mark.parametrize("P,s,m,wire", [(45, 3, 4, "i8"), (15, 2, 16, "one"), (9, 1, 3, "bf16"), (24, 7, 2, "f32"),
                                         (16, 0, 8, "one")])
 def test_sample_encoder_does_not_depend_on_row_length_or_stride(P, s, m, wire):
