@@ -143,10 +143,13 @@ __global__ __launch_bounds__(kBlock) void encode_cyc_kernel(const float* __restr
 }
 
 // The same encoder for rows too short to fill the chip.  There the walk down P rows is
-// latency: a workgroup (4 KiB contiguous, neighbours on one die, plain stores) takes only `seg`
+// latency: a workgroup (4 KiB contiguous, neighbours on one die) takes only `seg`
 // nodes, blockIdx.y the segment, and the rows that neighbouring segments share (2s of them) come
 // from the caches; no LDS, so the registers alone bound the workgroups per CU.  The window's rows
 // and the first round are in flight together.  Same taps in the same order: identical bits.
+// Streaming stores: plain ones end the kernel sooner but leave the messages for the next kernel to
+// wait for (whole step unsplit, split with plain stores, split: (45, 3, 500 001) on the 5-byte wire 116,
+// 117 and 104 us, (30, 7, 1 000 001) on two fp32 words 155, 186 and 154).
 template <int S, bool FULL, int LO, bool MULTI>
 __device__ __forceinline__ void encode_cyc_small_body(const float* __restrict__ G, int64_t ldg, int m, float* __restrict__ Z,
                                                       float* __restrict__ Zlo, int64_t ldm, const CycTaps tab, int P,
@@ -207,7 +210,7 @@ __device__ __forceinline__ void encode_cyc_small_body(const float* __restrict__ 
                 put((uu + 2 * S) % R, buf[uu], n + 2 * S);
                 double are0, aim0, are1, aim1;
                 tap_sum<R>(tab, n, wre, wim, uu % R, are0, aim0, are1, aim1);
-                store_message<FULL, LO, false>(Z, Zlo, (int64_t)n * ldm + c0, are0, aim0, are1, aim1, nout);
+                store_message<FULL, LO, true>(Z, Zlo, (int64_t)n * ldm + c0, are0, aim0, are1, aim1, nout);
             }
         }
     }
