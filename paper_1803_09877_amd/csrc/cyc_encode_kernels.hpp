@@ -441,17 +441,13 @@ __global__ __launch_bounds__(kBlock) void encode_cyc_real_kernel(const float* __
 // k*m+m-1 of the sample slab): the same sliding window, but a window entry is the fp64
 // sum of m rows, formed as the rows arrive; the first 2s unit sums are parked in LDS in
 // fp64 for the wrap-around.  Units are fetched one round ahead.
-template <int S, bool FULL, int LO>
+template <int S, int LO>
 __device__ __forceinline__ void encode_cyc_multi_body(const float* __restrict__ G, int64_t ldg, int m,
                                                       float* __restrict__ Z, float* __restrict__ Zlo, int64_t ldm,
-                                                      const CycTaps tab, int P, int64_t d,
+                                                      const CycTaps tab, int P,
                                                       int64_t c0, double4* head /* LDS [2S][kBlock] */) {
     constexpr int R = 2 * S + 1;
     constexpr int UN = 4;
-    const int64_t mlen = 2 * ((d + 1) / 2);
-    if (!FULL && c0 >= mlen) return;
-    const int nin = FULL ? 4 : clamp4(d - c0);
-    const int nout = FULL ? 4 : clamp4(mlen - c0);
 
     double wre[R][2], wim[R][2];
     auto put = [&](int slot, const double4& v, int kappa) {
@@ -464,7 +460,7 @@ __device__ __forceinline__ void encode_cyc_multi_body(const float* __restrict__ 
             float4 x[UN];
 #pragma unroll
             for (int i = 0; i < UN; ++i)
-                if (i0 + i < m) x[i] = ldx<FULL>(src + (int64_t)(i0 + i) * ldg, nin);
+                if (i0 + i < m) x[i] = ld4(src + (int64_t)(i0 + i) * ldg);
 #pragma unroll
             for (int i = 0; i < UN; ++i) {
                 if (i0 + i < m) {
@@ -495,13 +491,7 @@ __device__ __forceinline__ void encode_cyc_multi_body(const float* __restrict__ 
                 put((uu + 2 * S) % R, buf[uu], n + 2 * S);
                 double are0, aim0, are1, aim1;
                 tap_sum<R>(tab, n, wre, wim, uu % R, are0, aim0, are1, aim1);
-                const float4 hi = make_float4((float)are0, (float)aim0, (float)are1, (float)aim1);
-                stx<FULL>(Z + (int64_t)n * ldm + c0, hi, nout);
-                if constexpr (LO != kLoNone) {
-                    const float4 lo = make_float4((float)(are0 - (double)hi.x), (float)(aim0 - (double)hi.y),
-                                                  (float)(are1 - (double)hi.z), (float)(aim1 - (double)hi.w));
-                    st_lo<FULL, LO>(Zlo, (int64_t)n * ldm + c0, hi, lo, nout);
-                }
+                store_message<true, LO, true>(Z, Zlo, (int64_t)n * ldm + c0, are0, aim0, are1, aim1, 4);
             }
         }
     };
@@ -527,16 +517,12 @@ __device__ __forceinline__ void encode_cyc_multi_body(const float* __restrict__ 
 // walk with the next D rows always in flight (a ring of D raw rows whose slot is the row
 // index mod D, static because m is a multiple of D), so the loads of the next unit overlap
 // the sums of this one.  Same additions in the same order as above: identical bits.
-template <int S, int D, bool FULL, int LO>
+template <int S, int D, int LO>
 __device__ __forceinline__ void encode_cyc_multi_ring_body(const float* __restrict__ G, int64_t ldg, int m,
                                                            float* __restrict__ Z, float* __restrict__ Zlo,
-                                                           int64_t ldm, const CycTaps tab, int P,
-                                                           int64_t d, int64_t c0, double4* head /* LDS [2S][kBlock] */) {
+                                                           int64_t ldm, const CycTaps tab, int P, int64_t c0,
+                                                           double4* head /* LDS [2S][kBlock] */) {
     constexpr int R = 2 * S + 1;
-    const int64_t mlen = 2 * ((d + 1) / 2);
-    if (!FULL && c0 >= mlen) return;
-    const int nin = FULL ? 4 : clamp4(d - c0);
-    const int nout = FULL ? 4 : clamp4(mlen - c0);
     const int64_t rows = (int64_t)P * m;
 
     float4 ring[D];
@@ -544,7 +530,7 @@ __device__ __forceinline__ void encode_cyc_multi_ring_body(const float* __restri
     const float* src = G + c0;
 #pragma unroll
     for (int t = 0; t < D; ++t) {
-        ring[t] = ldx<FULL>(src + next * ldg, nin);
+        ring[t] = ld4(src + next * ldg);
         ++next;
     }
     auto unit_sum = [&]() -> double4 {  // the next unit gradient: its m rows, ascending, in fp64
@@ -553,7 +539,7 @@ __device__ __forceinline__ void encode_cyc_multi_ring_body(const float* __restri
 #pragma unroll
             for (int t = 0; t < D; ++t) {
                 const float4 x = ring[t];
-                if (next < rows) ring[t] = ldx<FULL>(src + next * ldg, nin);
+                if (next < rows) ring[t] = ld4(src + next * ldg);
                 ++next;
                 acc.x += (double)x.x;
                 acc.y += (double)x.y;
@@ -583,13 +569,7 @@ __device__ __forceinline__ void encode_cyc_multi_ring_body(const float* __restri
                 put((uu + 2 * S) % R, v, kk);
                 double are0, aim0, are1, aim1;
                 tap_sum<R>(tab, n, wre, wim, uu % R, are0, aim0, are1, aim1);
-                const float4 hi = make_float4((float)are0, (float)aim0, (float)are1, (float)aim1);
-                stx<FULL>(Z + (int64_t)n * ldm + c0, hi, nout);
-                if constexpr (LO != kLoNone) {
-                    const float4 lo = make_float4((float)(are0 - (double)hi.x), (float)(aim0 - (double)hi.y),
-                                                  (float)(are1 - (double)hi.z), (float)(aim1 - (double)hi.w));
-                    st_lo<FULL, LO>(Zlo, (int64_t)n * ldm + c0, hi, lo, nout);
-                }
+                store_message<true, LO, true>(Z, Zlo, (int64_t)n * ldm + c0, are0, aim0, are1, aim1, 4);
             }
         }
     }
@@ -598,16 +578,12 @@ __device__ __forceinline__ void encode_cyc_multi_ring_body(const float* __restri
 // m = 4 (the paper's B = 180 on P = 45): two units, eight rows, in flight.  Row i sits in ring
 // slot i mod 8 = 4 (k mod 2) + t for row t of unit k, so the half a unit reads is fixed by the
 // parity of k; the node loop is unrolled over 2R nodes to make that parity static.
-template <int S, bool FULL, int LO>
+template <int S, int LO>
 __device__ __forceinline__ void encode_cyc_multi_four_body(const float* __restrict__ G, int64_t ldg,
                                                            float* __restrict__ Z, float* __restrict__ Zlo,
-                                                           int64_t ldm, const CycTaps tab, int P,
-                                                           int64_t d, int64_t c0, double4* head /* LDS [2S][kBlock] */) {
+                                                           int64_t ldm, const CycTaps tab, int P, int64_t c0,
+                                                           double4* head /* LDS [2S][kBlock] */) {
     constexpr int R = 2 * S + 1;
-    const int64_t mlen = 2 * ((d + 1) / 2);
-    if (!FULL && c0 >= mlen) return;
-    const int nin = FULL ? 4 : clamp4(d - c0);
-    const int nout = FULL ? 4 : clamp4(mlen - c0);
     const int64_t rows = (int64_t)P * 4;
 
     float4 ring[8];
@@ -615,7 +591,7 @@ __device__ __forceinline__ void encode_cyc_multi_four_body(const float* __restri
     const float* src = G + c0;
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
-        if (next < rows) ring[t] = ldx<FULL>(src + next * ldg, nin);
+        if (next < rows) ring[t] = ld4(src + next * ldg);
         ++next;
     }
     auto unit_sum = [&](auto parity) -> double4 {  // the next unit gradient: its 4 rows, ascending, in fp64
@@ -624,7 +600,7 @@ __device__ __forceinline__ void encode_cyc_multi_four_body(const float* __restri
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             const float4 x = ring[H + t];
-            if (next < rows) ring[H + t] = ldx<FULL>(src + next * ldg, nin);
+            if (next < rows) ring[H + t] = ld4(src + next * ldg);
             ++next;
             acc.x += (double)x.x;
             acc.y += (double)x.y;
@@ -658,30 +634,71 @@ __device__ __forceinline__ void encode_cyc_multi_four_body(const float* __restri
                 put((uu + 2 * S) % R, v, kk);
                 double are0, aim0, are1, aim1;
                 tap_sum<R>(tab, n, wre, wim, uu % R, are0, aim0, are1, aim1);
-                const float4 hi = make_float4((float)are0, (float)aim0, (float)are1, (float)aim1);
-                stx<FULL>(Z + (int64_t)n * ldm + c0, hi, nout);
-                if constexpr (LO != kLoNone) {
-                    const float4 lo = make_float4((float)(are0 - (double)hi.x), (float)(aim0 - (double)hi.y),
-                                                  (float)(are1 - (double)hi.z), (float)(aim1 - (double)hi.w));
-                    st_lo<FULL, LO>(Zlo, (int64_t)n * ldm + c0, hi, lo, nout);
-                }
+                store_message<true, LO, true>(Z, Zlo, (int64_t)n * ldm + c0, are0, aim0, are1, aim1, 4);
             }
         }
     }
 }
 
-// Column of this lane and whether its workgroup is whole: contiguous runs with neighbours on one die
-// where message rows are off the line grid (device_util.hpp), else the spread footprint.  Measured at
-// (45, 5, B = 180), 6 000 001 floats on the 5-byte wire: 1052 us against 1263 (951-1024 at 6 000 000).
-__device__ __forceinline__ int64_t multi_column(int lines, int64_t d, bool& full) {
-    if (lines != 0) {
-        const int64_t tile = xcd_tile();
-        full = (tile + 1) * (kBlock * 4) <= d;
-        return (tile * kBlock + threadIdx.x) * 4;
+// The last d mod 4 floats of every row, which no whole vector covers: a workgroup of their own (the
+// last of the launch, only if there are any), a lane per unit gradient, then a lane per node.  As
+// lanes of a row's last workgroup they made that one walk all rows behind guarded loads, one memory
+// latency after the other, longer than the rest of the launch ((45, 2, B = 180, 400 001): 80 us against
+// 67 for 393 216).
+template <int S, int LO>
+__device__ __forceinline__ void encode_cyc_multi_tail(const float* __restrict__ G, int64_t ldg, int m,
+                                                      float* __restrict__ Z, float* __restrict__ Zlo, int64_t ldm,
+                                                      const CycTaps tab, int P, int64_t d,
+                                                      double4* units /* LDS [P] */) {
+    constexpr int R = 2 * S + 1;
+    constexpr int UN = 8;
+    const int64_t c0 = d / 4 * 4;
+    const int nin = (int)(d - c0), k = threadIdx.x;   // 1 .. 3 floats (the pad of an odd d reads as 0)
+    if (k < P) {
+        double4 acc = make_double4(0.0, 0.0, 0.0, 0.0);
+        const float* src = G + (int64_t)k * m * ldg + c0;
+        for (int i0 = 0; i0 < m; i0 += UN) {
+            float x[UN], y[UN], z[UN];
+#pragma unroll
+            for (int i = 0; i < UN; ++i) {
+                const float* row = src + (int64_t)min(i0 + i, m - 1) * ldg;
+                x[i] = row[0];
+                y[i] = nin > 1 ? row[1] : 0.f;
+                z[i] = nin > 2 ? row[2] : 0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < UN; ++i) {
+                if (i0 + i < m) {
+                    acc.x += (double)x[i];
+                    acc.y += (double)y[i];
+                    acc.z += (double)z[i];
+                }
+            }
+        }
+        units[k] = acc;
     }
-    const int64_t mlen = 2 * ((d + 1) / 2);
-    full = block_is_full<kSpreadEncodeCyc>(mlen, d);
-    return lane_column<kSpreadEncodeCyc>(mlen);
+    __syncthreads();
+    if (k < P) {
+        double wre[R][2], wim[R][2], are0, aim0, are1, aim1;
+#pragma unroll
+        for (int t = 0; t < R; ++t) {
+            const double4 v = units[k + t < P ? k + t : k + t - P];
+            rotate_in(tab, k + t, v.x, v.y, v.z, v.w, wre[t], wim[t]);
+        }
+        tap_sum<R>(tab, k, wre, wim, 0, are0, aim0, are1, aim1);
+        store_message<false, LO, true>(Z, Zlo, (int64_t)k * ldm + c0, are0, aim0, are1, aim1, (nin + 1) / 2 * 2);
+    }
+}
+
+// Workgroups that share the whole vectors of a row, and this lane's column among them: contiguous runs
+// with neighbours on one die where message rows are off the line grid (device_util.hpp), else the spread
+// footprint.  Measured at (45, 5, B = 180), 6 000 001 floats on the 5-byte wire: 1052 us against 1263
+// (951-1024 at 6 000 000).
+__device__ __forceinline__ unsigned multi_blocks(int64_t d) { return gridDim.x - (d % 4 != 0 ? 1u : 0u); }
+__device__ __forceinline__ int64_t multi_column(int lines, int64_t d) {
+    const unsigned blocks = multi_blocks(d);
+    if (lines != 0) return (xcd_tile(blocks) * kBlock + threadIdx.x) * 4;
+    return lane_column<kSpreadEncodeCyc>(d / 4 * 4, blocks);
 }
 
 template <int S, int LO>
@@ -689,13 +706,14 @@ __global__ __launch_bounds__(kBlock) void encode_cyc_multi_four_kernel(const flo
                                                                        float* __restrict__ Z, float* __restrict__ Zlo,
                                                                        int64_t ldm, const CycTaps tab,
                                                                        int P, int lines, int64_t d) {
-    extern __shared__ double4 head_sums[];  // [2S][kBlock]
-    bool full;
-    const int64_t c0 = multi_column(lines, d, full);
-    if (full)
-        encode_cyc_multi_four_body<S, true, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, c0, head_sums);
-    else
-        encode_cyc_multi_four_body<S, false, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, c0, head_sums);
+    extern __shared__ double4 head_sums[];  // [2S][kBlock], or a row of units
+    if (blockIdx.x == multi_blocks(d)) {
+        encode_cyc_multi_tail<S, LO>(G, ldg, 4, Z, Zlo, ldm, tab, P, d, head_sums);
+        return;
+    }
+    const int64_t c0 = multi_column(lines, d);
+    if (c0 + 4 > d) return;
+    encode_cyc_multi_four_body<S, LO>(G, ldg, Z, Zlo, ldm, tab, P, c0, head_sums);
 }
 
 template <int S, int D, int LO>
@@ -703,25 +721,29 @@ __global__ __launch_bounds__(kBlock) void encode_cyc_multi_ring_kernel(const flo
                                                                        float* __restrict__ Z, float* __restrict__ Zlo,
                                                                        int64_t ldm, const CycTaps tab,
                                                                        int P, int lines, int64_t d) {
-    extern __shared__ double4 head_sums[];  // [2S][kBlock]
-    bool full;
-    const int64_t c0 = multi_column(lines, d, full);
-    if (full)
-        encode_cyc_multi_ring_body<S, D, true, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, d, c0, head_sums);
-    else
-        encode_cyc_multi_ring_body<S, D, false, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, d, c0, head_sums);
+    extern __shared__ double4 head_sums[];  // [2S][kBlock], or a row of units
+    if (blockIdx.x == multi_blocks(d)) {
+        encode_cyc_multi_tail<S, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, d, head_sums);
+        return;
+    }
+    const int64_t c0 = multi_column(lines, d);
+    if (c0 + 4 > d) return;
+    encode_cyc_multi_ring_body<S, D, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, c0, head_sums);
 }
 
 template <int S, int LO>
 __global__ __launch_bounds__(kBlock) void encode_cyc_multi_kernel(const float* __restrict__ G, int64_t ldg, int m,
-                                                                  float* __restrict__ Z, float* __restrict__ Zlo,
-                                                                  int64_t ldm, const CycTaps tab,
-                                                                  int P, int lines, int64_t d) {
-    extern __shared__ double4 head_sums[];  // [2S][kBlock]
-    bool full;
-    const int64_t c0 = multi_column(lines, d, full);
-    if (full) encode_cyc_multi_body<S, true, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, d, c0, head_sums);
-    else encode_cyc_multi_body<S, false, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, d, c0, head_sums);
+                                                                       float* __restrict__ Z, float* __restrict__ Zlo,
+                                                                       int64_t ldm, const CycTaps tab,
+                                                                       int P, int lines, int64_t d) {
+    extern __shared__ double4 head_sums[];  // [2S][kBlock], or a row of units
+    if (blockIdx.x == multi_blocks(d)) {
+        encode_cyc_multi_tail<S, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, d, head_sums);
+        return;
+    }
+    const int64_t c0 = multi_column(lines, d);
+    if (c0 + 4 > d) return;
+    encode_cyc_multi_body<S, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, c0, head_sums);
 }
 
 

@@ -284,20 +284,21 @@ constexpr int64_t kTilesPerWindow = kWaveStride / 256;
 // over: the encoder's time falls by 3 %).
 __device__ __forceinline__ int64_t whole_windows(int64_t len) { return len / kWindow; }
 // First float this workgroup's wavefront 0 owns, and whether it owns window pieces.
-__device__ __forceinline__ int64_t spread_base(int64_t len, bool& pieces) {
+__device__ __forceinline__ int64_t spread_base(int64_t len, bool& pieces, unsigned blocks) {
     const int64_t windows = whole_windows(len);
-    const int64_t rest = (int64_t)gridDim.x - windows * kTilesPerWindow;   // contiguous workgroups
+    const int64_t rest = (int64_t)blocks - windows * kTilesPerWindow;   // contiguous workgroups
     const int64_t tile = (int64_t)blockIdx.x - rest;
     pieces = tile >= 0;
     if (!pieces) return windows * kWindow + (int64_t)blockIdx.x * (kBlock * 4);
     return (tile / kTilesPerWindow) * kWindow + (tile % kTilesPerWindow) * 256;
 }
-// Column (float index within a row of len floats) of this lane's 4 floats.
+// Column (float index within a row of len floats) of this lane's 4 floats; blocks: workgroups that share
+// the row.
 template <bool SPREAD>
-__device__ __forceinline__ int64_t lane_column(int64_t len) {
+__device__ __forceinline__ int64_t lane_column(int64_t len, unsigned blocks = gridDim.x) {
     if constexpr (SPREAD) {
         bool pieces;
-        const int64_t base = spread_base(len, pieces);
+        const int64_t base = spread_base(len, pieces, blocks);
         return base + (int64_t)(threadIdx.x >> 6) * (pieces ? kWaveStride : 256) + (threadIdx.x & 63) * 4;
     } else {
         return ((int64_t)blockIdx.x * kBlock + threadIdx.x) * 4;
@@ -308,7 +309,7 @@ template <bool SPREAD>
 __device__ __forceinline__ bool block_is_full(int64_t len, int64_t need) {
     if constexpr (SPREAD) {
         bool pieces;
-        const int64_t base = spread_base(len, pieces);
+        const int64_t base = spread_base(len, pieces, gridDim.x);
         return base + 3 * (pieces ? kWaveStride : 256) + 256 <= need;
     } else {
         return (int64_t)(blockIdx.x + 1) * (kBlock * 4) <= need;
@@ -321,8 +322,8 @@ __device__ __forceinline__ bool block_is_full(int64_t len, int64_t need) {
 // of lines.  Runs next to each other are then written by workgroups that share an L2: workgroup b
 // runs on accelerator die b mod 8, and tile xcd_tile() gives each die one contiguous range of
 // tiles, which its L2 merges if the stores carry no non-temporal hint.
-__device__ __forceinline__ int64_t xcd_tile() {
-    const int64_t per = gridDim.x / 8, b = blockIdx.x;
+__device__ __forceinline__ int64_t xcd_tile(unsigned blocks = gridDim.x) {
+    const int64_t per = blocks / 8, b = blockIdx.x;
     return b < per * 8 ? (b % 8) * per + b / 8 : b;
 }
 

@@ -115,6 +115,40 @@ def test_sample_encoder_does_not_depend_on_row_length_or_stride(P, s, m, wire):
             assert torch.equal(Zlo[:, :d].contiguous().view(torch.uint8), got[0][2][:, :d].contiguous().view(torch.uint8)), d
 
 
+@pytest.mark.parametrize("P,s,m,wire,line", [(45, 3, 4, "i8", 4), (45, 2, 16, "one", 128), (9, 1, 3, "bf16", 4), (24, 7, 4, "f32", 4),
+                                             (16, 0, 2, "one", 4), (256, 1, 2, "one", 4), (24, 9, 6, "i8", 128)])
+def test_sample_encoder_row_ends(P, s, m, wire, line):
+    """B > P, rows too long to be split: the last one to three floats of a row (their own workgroup) carry
+    the bits they have in a longer row of the same numbers, whatever lies behind the gradients."""
+    whole = 500_004
+    G = synth.make_gradients(P * m, whole, 1.0, 23, device="cuda:0", ld=synth.padded_len(whole))
+    for d in (whole - 3, whole - 2, whole - 1):
+        out = []
+        for length, behind in ((whole, 0.0), (d, float("nan"))):
+            G[:, d:] = behind
+            plan = B.Plan(B.CODE_CYCLIC, P, s, length)
+            ld = (whole + line - 1) // line * line
+            Z = torch.full((P, ld), 3.0, device="cuda:0")
+            Zlo = None
+            if wire == "one":
+                plan.encode_samples(G, Z)
+            else:
+                plan.set_second_word(LO[wire][0])
+                Zlo = torch.full((P, ld), 3, dtype=LO[wire][1], device="cuda:0")
+                plan.encode_samples_wide(G, Z, Zlo)
+            torch.cuda.synchronize()
+            plan.close()
+            out.append((Z, Zlo))
+        mlen = 2 * ((d + 1) // 2)
+        assert torch.equal(out[0][0][:, :mlen].contiguous().view(torch.int32), out[1][0][:, :mlen].contiguous().view(torch.int32)), d
+        assert bool((out[1][0][:, mlen:] == 3).all()), d
+        if wire != "one":
+            assert torch.equal(out[0][1][:, :mlen].contiguous().view(torch.uint8),
+                               out[1][1][:, :mlen].contiguous().view(torch.uint8)), d
+            assert bool((out[1][1][:, mlen:] == 3).all()), d
+        G[:, d:] = 0.0
+
+
 @pytest.mark.parametrize("P,s,d,wide,unpacked", [
     (45, 3, 1_900_003, "i8", False), (45, 3, 2_400_000, False, False), (32, 4, 2_200_001, "bf16", False),
     (45, 7, 1_200_001, "f32", False), (16, 2, 3_200_001, False, True),
