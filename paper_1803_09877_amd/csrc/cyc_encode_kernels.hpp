@@ -513,6 +513,75 @@ __device__ __forceinline__ void encode_cyc_multi_body(const float* __restrict__ 
     }
 }
 
+// The same one unit at a time, the first UN rows of the next one in flight: 138 registers at s = 5 where
+// two rounds of unit sums take 290 and leave one wavefront per SIMD ((45, 5, 2, 1 998 848): 450 us and 241; the
+// narrower windows fit twice as they are, LDS holds the wider ones to one workgroup per CU).
+template <int S, int LO>
+__device__ __forceinline__ void encode_cyc_multi_ahead_body(const float* __restrict__ G, int64_t ldg, int m,
+                                                            float* __restrict__ Z, float* __restrict__ Zlo,
+                                                            int64_t ldm, const CycTaps tab, int P, int64_t c0,
+                                                            double4* head /* LDS [2S][kBlock] */) {
+    constexpr int R = 2 * S + 1;
+    constexpr int UN = 4;
+
+    double wre[R][2], wim[R][2];
+    auto put = [&](int slot, const double4& v, int kappa) {
+        rotate_in(tab, kappa, v.x, v.y, v.z, v.w, wre[slot], wim[slot]);
+    };
+    // the first UN rows of a unit are fetched while the one before it is encoded
+    float4 ahead[UN];
+    auto fetch = [&](int k) {
+#pragma unroll
+        for (int i = 0; i < UN; ++i)
+            if (i < m) ahead[i] = ld4(G + ((int64_t)k * m + i) * ldg + c0);
+    };
+    auto unit_sum = [&](int k) -> double4 {  // g_k = sum of its m sample rows, ascending, in fp64
+        double4 acc = make_double4(0.0, 0.0, 0.0, 0.0);
+        auto add = [&](const float4& x) {
+            acc.x += (double)x.x;
+            acc.y += (double)x.y;
+            acc.z += (double)x.z;
+            acc.w += (double)x.w;
+        };
+#pragma unroll
+        for (int i = 0; i < UN; ++i)
+            if (i < m) add(ahead[i]);
+        const float* src = G + (int64_t)k * m * ldg + c0;
+        for (int i0 = UN; i0 < m; i0 += UN) {
+            float4 x[UN];
+#pragma unroll
+            for (int i = 0; i < UN; ++i)
+                if (i0 + i < m) x[i] = ld4(src + (int64_t)(i0 + i) * ldg);
+#pragma unroll
+            for (int i = 0; i < UN; ++i)
+                if (i0 + i < m) add(x[i]);
+        }
+        if (k + 1 < P) fetch(k + 1);
+        return acc;
+    };
+    fetch(0);
+#pragma unroll
+    for (int k = 0; k < 2 * S; ++k) {
+        const double4 v = unit_sum(k);
+        head[k * kBlock + threadIdx.x] = v;
+        put(k, v, k);
+    }
+    for (int n0 = 0; n0 < P; n0 += R) {
+#pragma unroll
+        for (int uu = 0; uu < R; ++uu) {
+            const int n = n0 + uu;
+            if (n < P) {
+                const int kk = n + 2 * S;
+                const double4 v = kk < P ? unit_sum(kk) : head[(kk - P) * kBlock + threadIdx.x];
+                put((uu + 2 * S) % R, v, kk);
+                double are0, aim0, are1, aim1;
+                tap_sum<R>(tab, n, wre, wim, uu % R, are0, aim0, are1, aim1);
+                store_message<true, LO, true>(Z, Zlo, (int64_t)n * ldm + c0, are0, aim0, are1, aim1, 4);
+            }
+        }
+    }
+}
+
 // The same when m is a multiple of D: the B = m P sample rows are consumed in one linear
 // walk with the next D rows always in flight (a ring of D raw rows whose slot is the row
 // index mod D, static because m is a multiple of D), so the loads of the next unit overlap
@@ -743,7 +812,8 @@ __global__ __launch_bounds__(kBlock) void encode_cyc_multi_kernel(const float* _
     }
     const int64_t c0 = multi_column(lines, d);
     if (c0 + 4 > d) return;
-    encode_cyc_multi_body<S, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, c0, head_sums);
+    if constexpr (S == 5) encode_cyc_multi_ahead_body<S, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, c0, head_sums);
+    else encode_cyc_multi_body<S, LO>(G, ldg, m, Z, Zlo, ldm, tab, P, c0, head_sums);
 }
 
 
