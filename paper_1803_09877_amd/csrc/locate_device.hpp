@@ -80,6 +80,13 @@ __device__ __forceinline__ double rsqrt_pos(double x) {
     r = r * fma(-hx * r, r, 1.5);
     return r;
 }
+// 1/x likewise
+__device__ __forceinline__ double rcp_pos(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return r;
+}
 // (a + b) mod P for 0 <= a, b < P
 __device__ __forceinline__ int addmod(int a, int b, int P) {
     const int c = a + b;
@@ -277,14 +284,14 @@ __device__ __forceinline__ void solve_beta(LocateSmem& sm, int P, int s, double 
                 const bool skip = !pair || ag2 == 0.0 || ag2 <= 1e-20 * (alpha * bet) || (alpha <= zero2 && bet <= zero2);
                 if (!skip) {
                     // rotation that makes the two columns orthogonal: with zeta = (bet - alpha) / (2 |g|),
-                    // t = sign(zeta) / (|zeta| + sqrt(1 + zeta^2)), c = 1 / sqrt(1 + t^2), sn = c t.  t takes
-                    // the hardware's estimates as they are (an angle off by 1e-7 leaves that much for the next
-                    // sweep); c and the phase are exact to fp64, so the rotation is unitary whatever t is.
+                    // t = sign(zeta) / (|zeta| + sqrt(1 + zeta^2)), c = 1 / sqrt(1 + t^2), sn = c t.  All of it to
+                    // fp64: the last sweep then leaves columns orthogonal to rounding, not to the 1e-10 that ends
+                    // the sweeps.
                     const double inv_ag = rsqrt_pos(ag2);
                     const double2 ph = make_double2(gd.x * inv_ag, -gd.y * inv_ag);
-                    const double zeta = (bet - alpha) * (0.5 * __builtin_amdgcn_rsq(ag2));
+                    const double zeta = (bet - alpha) * (0.5 * inv_ag);
                     const double w2 = fma(zeta, zeta, 1.0);
-                    const double t = (zeta >= 0.0 ? 1.0 : -1.0) * __builtin_amdgcn_rcp(fabs(zeta) + w2 * __builtin_amdgcn_rsq(w2));
+                    const double t = (zeta >= 0.0 ? 1.0 : -1.0) * rcp_pos(fabs(zeta) + w2 * rsqrt_pos(w2));
                     const double c = rsqrt_pos(fma(t, t, 1.0)), sn = c * t;
                     const double2 aqr = cmul(aq, ph);
                     if (live) {
