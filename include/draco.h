@@ -305,9 +305,14 @@ int draco_projection_vector(const draco_plan* plan, uint64_t seed, float* f_host
  * sum (bit-identical to what the second pass would give) and the second pass over
  * the messages is skipped, which halves the decode.  Messages below 384 MiB: the
  * prediction is "nobody", made when the plan's previous decode was clean (the first
- * call counts as one).  Larger ones: the set that phi finds on a sample of the
- * columns of this call's messages, so adversaries that lie everywhere cost no second
- * pass, persistent or not.  0 switches it off. */
+ * call counts as one); rows split over the nodes (fewer than 256 tiles of 1024 floats and
+ * more than 8 nodes) are not speculated on.  Larger ones: the set that phi finds on a
+ * sample of the columns of this call's messages (which columns is drawn from f), so
+ * adversaries that lie everywhere cost no second pass, persistent or not; after 8 clean decodes
+ * in a row "nobody", without a sample, until a decode finds somebody.  A lie that the sample does not
+ * hold costs the sample and the projection's surcharge (3 % of a step at (45, 3, 25.6 M)) on top of
+ * both passes; after the n-th such miss in a row (n <= 8) the next 2^n - 1 decodes make the
+ * two passes at once.  0 switches it off. */
 int draco_plan_set_speculation(draco_plan* plan, int enabled);
 
 /* Same, stream-ordered (s <= 16 only, else DRACO_EINVAL): mask_dev

@@ -179,7 +179,7 @@ int prepare(draco_plan* p) {
             }
             HIP_TRY(hipMalloc(&p->root_dev, P * sizeof(double2)));
             HIP_TRY(hipMemcpy(p->root_dev, t0.data(), P * sizeof(double2), hipMemcpyHostToDevice));
-            const int32_t init[kSpecWords] = {1};  // optimistic: the first decode expects no adversary
+            const int32_t init[kSpecWords] = {1};  // optimistic: as after one clean decode
             HIP_TRY(hipMemcpy(p->spec_dev, init, sizeof(init), hipMemcpyHostToDevice));
         }
         HIP_TRY(hipMalloc(&p->idx_dev, (P + 1) * sizeof(int32_t)));
@@ -536,7 +536,7 @@ int decode_cyclic_async_impl(draco_plan* p, const float* hi_dev, const float* lo
         if (spec.state != nullptr && P * message_len(p) * (wide ? wide_bytes(p) : 4) >= kSampledMessages) {
             spec.mask = p->spec_mask_dev;
             spec.b = p->spec_b_dev;
-            HIP_TRY(launch_cyc_sample(hi_dev, lo, fmt, ld_m, f_dev, seed, p->sample_dev, P, d, st));
+            HIP_TRY(launch_cyc_sample(hi_dev, lo, fmt, ld_m, f_dev, seed, p->sample_dev, spec, P, d, st));
             HIP_TRY(launch_cyc_locate_sample(p->sample_dev, p->root_dev, P, p->s, tau, p->b0_dev, p->b_dev, p->idx_dev,
                                              p->idx_dev + P, spec, st));
         }

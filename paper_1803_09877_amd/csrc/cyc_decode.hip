@@ -10,6 +10,13 @@
 
 namespace draco {
 
+// The set that the projection pass speculates on (run after the sample's locator).
+__device__ __forceinline__ int speculates_on(const CycSpec& spec) {
+    if (spec.mask == nullptr) return spec.state[kSpecClean] != 0 ? kSpecOnNobody : 0;
+    if (takes_sample(spec)) return spec.state[kSpecStatus] == 0 ? kSpecOnSample : 0;
+    return spec.state[kSpecClean] >= kCleanRun ? kSpecOnNobody : 0;
+}
+
 // phi step 1: gamma'_j = sum_i f_i * r_j[i].  A workgroup owns a tile of kBlock * K float4
 // (two complex numbers each) of every row and keeps its slice of f in registers.  RB rows are
 // taken at a time (8 loads of 16 bytes in flight per lane; 16, or a second buffer for the next
@@ -146,14 +153,14 @@ __global__ __launch_bounds__(kBlock) void cyc_project_kernel(const float* __rest
     const double2* b = nullptr;
     const uint64_t* flagged = nullptr;
     if (spec.state != nullptr) {
-        if (spec.mask != nullptr) {
+        const int now = speculates_on(spec);
+        if (now == kSpecOnSample) {
             b = spec.b;
             flagged = spec.mask;
-        } else if (spec.state[kSpecClean] != 0) {
+        } else if (now == kSpecOnNobody) {
             b = b0;
         }
-        if (blockIdx.x == 0 && threadIdx.x == 0)
-            spec.state[kSpecNow] = spec.mask != nullptr ? kSpecOnSample : b != nullptr ? kSpecOnNobody : 0;
+        if (blockIdx.x == 0 && threadIdx.x == 0) spec.state[kSpecNow] = now;
     }
     const bool full = (tile + 1) * (kBlock * K) * 2 <= (d + 1) / 2;
     if (b != nullptr) {
@@ -176,16 +183,22 @@ __global__ __launch_bounds__(kBlock) void cyc_project_kernel(const float* __rest
 }
 
 // The projection of a sample: kSampleTiles tiles of 1024 floats, `step` tiles apart, rows in groups
-// of 8 (blockIdx.y).
+// of 8 (blockIdx.y).  The first one is drawn from f, which is new in every call and unknown to the
+// adversaries, so that no column (but a row's last, partial tile) is safe from the sample.
 template <int LO>
 __global__ __launch_bounds__(kBlock) void cyc_sample_kernel(const float* __restrict__ Rm, const float* __restrict__ Rlo,
                                                             int64_t ldm, const float* __restrict__ f, uint64_t f_seed,
-                                                            double2* __restrict__ partial,
-                                                            int P, int64_t step, int64_t d) {
+                                                            double2* __restrict__ partial, const CycSpec spec,
+                                                            int P, unsigned step, unsigned firsts, int64_t d) {
+    if (!takes_sample(spec)) return;
     __shared__ double2 wsum[kBlock / 64][kMaxNodes];
     const int j0 = (int)blockIdx.y * 8, j1 = min(P, j0 + 8);
+    uint64_t draw = f_seed;
+    if (f != nullptr) draw = ((uint64_t)__float_as_uint(f[0]) << 32) | __float_as_uint(f[1]);
+    draw = (draw ^ (draw >> 29)) * 0x9E3779B97F4A7C15ull;
+    const int64_t first = (unsigned)(draw >> 32) % firsts;
     cyc_project_body<LO, 1, 8, true, false, true>(Rm, Rlo, ldm, f, f_seed, nullptr, nullptr, nullptr, false,
-                                                  blockIdx.x * step, j0, j1, d, wsum);
+                                                  first + (int64_t)blockIdx.x * step, j0, j1, d, wsum);
     __syncthreads();
     if ((int)threadIdx.x < j1 - j0) {
         double2 a = wsum[0][threadIdx.x];
@@ -354,12 +367,14 @@ hipError_t launch_cyc_project(const float* R, const float* Rlo, int lo, int64_t 
 }
 
 hipError_t launch_cyc_sample(const float* R, const float* Rlo, int lo, int64_t ldm, const float* f, uint64_t f_seed,
-                             double2* partial, int P, int64_t d, hipStream_t stream) {
+                             double2* partial, const CycSpec& spec, int P, int64_t d, hipStream_t stream) {
     const int64_t tiles = (d + 1) / 2 * 2 / (kBlock * 4);   // whole ones
     if (tiles < kSampleTiles) return hipErrorInvalidValue;
+    const int64_t step = tiles / kSampleTiles, firsts = tiles - (kSampleTiles - 1) * step;   // first tile < firsts
     with_format(Rlo, lo, [&](auto fmt) {
         hipLaunchKernelGGL((cyc_sample_kernel<decltype(fmt)::value>), dim3(kSampleTiles, (unsigned)((P + 7) / 8)),
-                           dim3(kBlock), 0, stream, R, Rlo, ldm, f, f_seed, partial, P, tiles / kSampleTiles, d);
+                           dim3(kBlock), 0, stream, R, Rlo, ldm, f, f_seed, partial, spec, P, (unsigned)step,
+                           (unsigned)firsts, d);
     });
     return hipGetLastError();
 }

@@ -78,13 +78,15 @@ hipError_t launch_encode_cyc_real_node(const float* Gn, int64_t ldg, float* z, c
 hipError_t launch_encode_cyc_node(const float* Gn, int64_t ldg, float* z, float* zlo, int lo,
                                   const CycTaps& tab, int node, int P, int s, int64_t d, hipStream_t stream);
 // What a decode expects before it has located anybody (device memory of a plan).
-//   state[kSpecClean]  1 after a clean decode: the next call expects no adversary (unless it samples)
-//   state[kSpecNow]    what the projection pass of this call speculated on: 0, kSpecOnNobody, kSpecOnSample
-//   state[kSpecDone]   1 if the locator found that set: the output holds the sum already
-//   mask, b            the set located on a sample of this call's messages (kMaskWords) and its
-//                      recombination vector (P, dense); mask == nullptr where no sample is taken
+//   state[kSpecClean]   clean decodes in a row, up to kCleanRun (a new plan starts with one)
+//   state[kSpecNow]     what the projection pass of this call speculated on: 0, kSpecOnNobody, kSpecOnSample
+//   state[kSpecDone]    1 if the locator found that set: the output holds the sum already
+//   state[kSpecStatus]  of the locator on this call's sample
+//   state[kSpecSkip]    decodes left that take no sample, state[kSpecMisses]: samples in a row that misled
+//   mask, b             the set located on a sample of this call's messages (kMaskWords) and its
+//                       recombination vector (P, dense); mask == nullptr where no sample is taken
 // state == nullptr: never speculate.
-enum : int { kSpecClean = 0, kSpecNow = 1, kSpecDone = 2, kSpecStatus = 3, kSpecWords = 4 };
+enum : int { kSpecClean = 0, kSpecNow = 1, kSpecDone = 2, kSpecStatus = 3, kSpecSkip = 4, kSpecMisses = 5, kSpecWords = 6 };
 enum : int { kSpecOnNobody = 1, kSpecOnSample = 2 };
 struct CycSpec {
     int32_t* state;
@@ -93,12 +95,23 @@ struct CycSpec {
 };
 constexpr int kSampleTiles = 64;      // of 1024 floats
 constexpr int kInlineTiles = 64;      // partial sums up to which the locator adds them itself
-// Messages (both words, bytes) from which a decode locates the adversaries on a sample first and
-// then projects and recombines in ONE pass.  The sample and its locator take 15 to 30 us and the
+// Messages (both words, bytes) from which a decode may locate the adversaries on a sample first and
+// then project and recombine in ONE pass.  The sample and its locator take 15 to 30 us and the
 // joint pass 10 % more than a projection; the second pass they save runs at about 6.3 TB/s, so with
-// adversaries it breaks even near 250 MB.  A lie that the sample does not hold (it need not touch
-// every coordinate) costs the second pass, as it would without.
+// adversaries it breaks even near 250 MB.
 constexpr int64_t kSampledMessages = 384ll << 20;
+// A plan that saw kCleanRun clean decodes in a row expects nobody and takes no sample (15 to 20 us, 8 % of a
+// clean step at (15, 2, 8 M)); until then, and after a decode that found somebody, it samples.  A
+// lie that the sample does not hold (it need not touch every coordinate) costs the sample and the joint pass's
+// surcharge on top of the two passes, 3 % of a step at (45, 3, 25.6 M); after the n-th such miss in a
+// row the next 2^n - 1 decodes project only, so a persistent one costs that in 1 of 256 decodes.
+constexpr int kCleanRun = 8;
+constexpr int kMaxMisses = 8;
+// Whether a call that has room for a sample (mask != nullptr) takes one.  All its kernels ask; the state
+// changes in the last locator only.
+__device__ __forceinline__ bool takes_sample(const CycSpec& spec) {
+    return spec.state[kSpecClean] < kCleanRun && spec.state[kSpecSkip] == 0;
+}
 
 // Number of workgroups (= rows of `partial`) the projection uses for gradient length d, and
 // whether it can speculate there (short rows are split over the nodes: they cannot).
@@ -112,9 +125,10 @@ bool project_speculates(int64_t d, int P);
 hipError_t launch_cyc_project(const float* R, const float* Rlo, int lo, int64_t ldm, const float* f,
                               uint64_t f_seed, double2* partial, const double2* b0, float* u, bool realout,
                               const CycSpec& spec, int P, int64_t d, hipStream_t stream);
-// The same sums for a sample of the columns, partial[kSampleTiles][P].
+// The same sums for a sample of the columns, partial[kSampleTiles][P]: which ones is drawn from f (its
+// first entries, or its seed), which the adversaries do not know.  Nothing if this call takes no sample.
 hipError_t launch_cyc_sample(const float* R, const float* Rlo, int lo, int64_t ldm, const float* f, uint64_t f_seed,
-                             double2* partial, int P, int64_t d, hipStream_t stream);
+                             double2* partial, const CycSpec& spec, int P, int64_t d, hipStream_t stream);
 // gamma[P] <- the sum of partial[tiles][P] in tile order.
 hipError_t launch_cyc_reduce(const double2* partial, double2* gamma, int P, int64_t tiles, hipStream_t stream);
 // phi steps 2-4 and the recombination vector on the device (one wavefront, fp64; s <= kLocateMaxS):
@@ -122,13 +136,13 @@ hipError_t launch_cyc_reduce(const double2* partial, double2* gamma, int P, int6
 // honest nodes' (idx, b) compacted in ascending order with their count in *nu_out.
 // roots[k] = exp(2 pi i k / P), k < P.  tau: relative zero threshold for syndromes.  With no located
 // node the coefficients are copied from b0.  b is a function of the set of flagged nodes.
-// spec.state: kSpecClean <- this decode was clean, kSpecDone <- the set found is the one
-// speculated on.
+// spec.state: kSpecDone <- the set found is the one speculated on; kSpecClean, kSpecSkip and kSpecMisses
+// for the next call.
 hipError_t launch_cyc_locate(const double2* sums, int64_t tiles, const double2* roots, int P, int s, double tau,
                              const double2* b0, uint64_t* mask_out, int32_t* status_out, double2* b_out,
                              int32_t* idx_out, int32_t* nu_out, const CycSpec& spec, hipStream_t stream);
 // The same on the sums of a sample: spec.mask and spec.b <- the set found and its coefficients
-// (b_out, idx_out, nu_out are scratch).
+// (b_out, idx_out, nu_out are scratch).  Nothing if this call takes no sample.
 hipError_t launch_cyc_locate_sample(const double2* partial, const double2* roots, int P, int s, double tau,
                                     const double2* b0, double2* b_out, int32_t* idx_out, int32_t* nu_out,
                                     const CycSpec& spec, hipStream_t stream);

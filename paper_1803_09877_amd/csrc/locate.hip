@@ -70,7 +70,21 @@ __global__ __launch_bounds__(TILES ? kW * kSumWaves : kW) void cyc_locate_kernel
         }
         if (lane == 0) {
             spec.state[kSpecDone] = same ? 1 : 0;
-            spec.state[kSpecClean] = clean ? 1 : 0;
+            if (spec.mask != nullptr) {
+                const int skip = spec.state[kSpecSkip];
+                if (takes_sample(spec)) {
+                    if (!same) {   // misled (or its locator failed): project only, longer each time
+                        const int misses = min(spec.state[kSpecMisses] + 1, kMaxMisses);
+                        spec.state[kSpecMisses] = misses;
+                        spec.state[kSpecSkip] = (1 << misses) - 1;
+                    } else if (!clean) {
+                        spec.state[kSpecMisses] = 0;
+                    }
+                } else if (skip > 0) {
+                    spec.state[kSpecSkip] = skip - 1;
+                }
+            }
+            spec.state[kSpecClean] = clean ? min(spec.state[kSpecClean] + 1, kCleanRun) : 0;
         }
     }
 }
@@ -78,7 +92,8 @@ __global__ __launch_bounds__(TILES ? kW * kSumWaves : kW) void cyc_locate_kernel
 __global__ __launch_bounds__(kW * kSumWaves) void cyc_locate_sample_kernel(const double2* __restrict__ partial,
                                                                            const double2* __restrict__ roots, int P, int s,
                                                                            double tau, const double2* __restrict__ b0,
-                                                                           const LocateOut out) {
+                                                                           const CycSpec spec, const LocateOut out) {
+    if (!takes_sample(spec)) return;
     __shared__ LocateSmem sm;
     __shared__ double2 part[kSumWaves][kMaxNodes];
     load_projections<true>(sm, part, partial, kSampleTiles, roots, P);
@@ -104,7 +119,7 @@ hipError_t launch_cyc_locate_sample(const double2* partial, const double2* roots
                                     const CycSpec& spec, hipStream_t stream) {
     const LocateOut out{spec.mask, spec.state + kSpecStatus, b_out, idx_out, nu_out, spec.b};
     hipLaunchKernelGGL(cyc_locate_sample_kernel, dim3(1), dim3(kW * kSumWaves), 0, stream, partial, roots, P, s, tau, b0,
-                       out);
+                       spec, out);
     return hipGetLastError();
 }
 

@@ -152,12 +152,14 @@ def test_sample_encoder_row_ends(P, s, m, wire, line):
 @pytest.mark.parametrize("P,s,d,wide,unpacked", [
     (45, 3, 1_900_003, "i8", False), (45, 3, 2_400_000, False, False), (32, 4, 2_200_001, "bf16", False),
     (45, 7, 1_200_001, "f32", False), (16, 2, 3_200_001, False, True),
+    (45, 3, 4_000_003, "i8", False), (60, 2, 900_001, "f32", False),     # eight and one float4 per lane
 ])
 def test_sampled_decode_equals_the_two_pass_decode(P, s, d, wide, unpacked):
     """Messages of more than 384 MiB: a decode that expects adversaries locates them on a sample of
     the columns and recombines while it projects.  Lies everywhere (the sample finds them), lies in
-    one coordinate that no sample holds (it does not: second pass), a broken message, nobody, and more
-    liars than s: masks, statuses and bits of a plan that never speculates."""
+    one coordinate that no sample holds (it does not: second pass, and no sample in the next call), a broken
+    message, nobody, and more liars than s: masks, statuses and bits of a plan that never speculates.
+    Where the sample was right the second pass is skipped."""
     w = synth.Workload(name="sampled", code="cyc", P=P, s=s, d=d, sigma=1e-2, attacks=(), placement="any",
                        seed=synth.SEED_BASE + 5)
     c = Case(w, wide=wide, unpacked=unpacked)
@@ -168,7 +170,11 @@ def test_sampled_decode_equals_the_two_pass_decode(P, s, d, wide, unpacked):
         ref.set_second_word(LO[wide][0])
     ref.set_speculation(False)
     u_ref = torch.zeros_like(c.u)
-    hidden = 5_000   # tiles of 1024 floats are sampled 18 or more tiles apart, from tile 0 on
+    hidden = c.mlen - 2   # a row's last, partial tile is in no sample
+    assert c.mlen % 1024 != 0
+    hits = (0, 1, 4, 5, 6)   # steps whose sample finds the set (3 and 8 follow a miss)
+    c.plan.set_timing(16)
+    ref.set_timing(16)
     try:
         c.encode()
         big = float(c.Z[:, :c.mlen].abs().max())
@@ -182,7 +188,7 @@ def test_sampled_decode_equals_the_two_pass_decode(P, s, d, wide, unpacked):
                 elif how == "hidden":
                     c.R[j, hidden] += 1e4 * big
                 else:
-                    c.R[j, c.mlen - 1] = float("nan")
+                    c.R[j, :c.mlen:512] = float("nan")
             c.u.fill_(float("nan"))
             u_ref.fill_(float("nan"))
             mask, status = c.decode()
@@ -197,6 +203,55 @@ def test_sampled_decode_equals_the_two_pass_decode(P, s, d, wide, unpacked):
             else:
                 assert status == B.LOCATE_FAILED, step
             assert torch.equal(c.u.view(torch.int32), u_ref.view(torch.int32)), step
+            second, second_ref = (p.kernel_times(B.KIND_RECOMBINE)[-1] for p in (c.plan, ref))
+            assert (second < 0.5 * second_ref) == (step in hits), (step, second, second_ref)
+    finally:
+        ref.close()
+        c.close()
+
+
+def test_sampling_backs_off_and_comes_back():
+    """A liar whose lie no sample holds misleads a sample once, then the plan projects only, for 1, 3, ...
+    decodes; liars everywhere are found by the next sample and end that; after eight clean decodes
+    in a row none is taken.  What a call did shows in its projection's time beside that of a plan that
+    never speculates (sample and joint pass cost a seventh)."""
+    P, s, d = 45, 3, 12_000_003
+    w = synth.Workload(name="backoff", code="cyc", P=P, s=s, d=d, sigma=1e-2, attacks=(), placement="any",
+                       seed=synth.SEED_BASE + 6)
+    c = Case(w, wide="i8")
+    ref = B.Plan(B.CODE_CYCLIC, P, s, d)
+    ref.set_second_word(B.SECOND_WORD_I8)
+    ref.set_speculation(False)
+    c.plan.set_timing(4)
+    ref.set_timing(4)
+    try:
+        c.encode()
+        big = float(c.Z[:, :c.mlen].abs().max())
+
+        def decode(kind):
+            c.receive()
+            if kind == "hidden":
+                c.R[7, c.mlen - 2] += 1e4 * big
+            elif kind == "all":
+                c.R[3, :c.mlen] *= -100.0
+            ref.decode_cyclic_wide(c.R, c.Rlo, c.f, c.u)   # (the first pass behind the copies takes longer)
+            mask, status = c.decode()
+            ref.decode_cyclic_wide(c.R, c.Rlo, c.f, c.u)
+            torch.cuda.synchronize()
+            assert status == B.OK and np.flatnonzero(mask).tolist() == {"hidden": [7], "all": [3], "": []}[kind]
+            first, second = ([p.kernel_times(k)[-1] for p in (c.plan, ref)] for k in (B.KIND_PROJECT, B.KIND_RECOMBINE))
+            print(f"   {kind or 'nobody'}: project {first[0]:.3f} / {first[1]:.3f} ms  recombine {second[0]:.3f} / {second[1]:.3f}",
+                  flush=True)
+            return first[0] > 1.08 * first[1], second[0] < 0.5 * second[1]   # sampled or speculated; one pass
+
+        decode("all")   # (warm)
+        assert [decode("hidden") for _ in range(7)] == [(i in (0, 2, 6), False) for i in range(7)]
+        assert [decode("all") for _ in range(9)] == [(i >= 7, i >= 7) for i in range(9)]
+        assert decode("hidden") == (True, False)    # the first miss again
+        assert decode("all") == (False, False) and decode("all") == (True, True)
+        assert all(decode("")[1] for _ in range(12))
+        assert not decode("all")[1]                 # nobody was expected, without a sample
+        assert decode("all") == (True, True)
     finally:
         ref.close()
         c.close()
