@@ -55,9 +55,12 @@ __device__ __forceinline__ void encode_rep_body(const float* __restrict__ G, int
 }
 
 // Column of this lane and whether its workgroup is whole: contiguous runs with neighbours on one die
-// where the rows written are off the line grid (LINES; device_util.hpp), else the spread footprint.
-// Measured, off the grid: (P, s, B, d) = (45, 2, 180, 1.66 M) 266 us against 282, (45, 2, 45, 11.2 M) 724
-// against 812; on it 257 against 246 and 648 against 609.
+// (LINES; device_util.hpp), else the spread footprint.  Rows on the line grid lose with runs ((P, s, B, d) =
+// (45, 2, 180, 1.66 M) 257 us against 246, (45, 2, 45, 11.2 M) 648 against 609); off it whole steps, spread over
+// runs: B > P 1.00 to 1.13 for s = 1 .. 7, 1 to 45 / r groups and 50 000 to 5 M floats; B = P 0.98 to 1.09 up to
+// 3 M floats for all s; from there on up to 25.6 M floats 1.00 to 1.10 for s = 2 and three groups or more
+// ((45, 2, 45, 11.2 M) encoder 809 -> 747 us), but 0.91 to 1.04, mostly below 1, for the others ((18, 4, 11.2 M)
+// encoder 307 -> 329).
 template <bool LINES>
 __device__ __forceinline__ int64_t rep_column(int64_t d, bool& full) {
     if constexpr (LINES) {
@@ -425,8 +428,8 @@ __global__ __launch_bounds__(kBlock) void decode_rep_generic_kernel(const float*
 namespace {
 
 // Sums of `rows` rows per group, stored `copies` times.
-void launch_generic(const float* G, int64_t ldg, float* Z, int64_t ldm, int groups, int rows, int copies, int per_cu,
-                    int64_t d, hipStream_t stream) {
+void launch_generic(const float* G, int64_t ldg, float* Z, int64_t ldm, int groups, int rows, int copies, bool lines,
+                    int per_cu, int64_t d, hipStream_t stream) {
     auto go = [&](auto lines) {
         constexpr bool LINES = decltype(lines)::value;
         const dim3 grid(grid_cols<!LINES && kSpreadEncodeRep>(d), (unsigned)groups);
@@ -434,7 +437,7 @@ void launch_generic(const float* G, int64_t ldg, float* Z, int64_t ldm, int grou
         hipLaunchKernelGGL(encode_rep_generic_kernel<LINES>, grid, dim3(kBlock), throttle_lds(per_cu, 0, 0), stream, G, ldg,
                            Z, ldm, groups, rows, copies, d);
     };
-    if (ldm % 32 != 0) go(std::true_type{});
+    if (lines) go(std::true_type{});
     else go(std::false_type{});
 }
 
@@ -443,7 +446,7 @@ void launch_generic(const float* G, int64_t ldg, float* Z, int64_t ldm, int grou
 hipError_t launch_encode_rep(const float* G, int64_t ldg, float* Z, int64_t ldm, int P, int s, int64_t d,
                              hipStream_t stream) {
     const int r = 2 * s + 1, groups = P / r;
-    const bool lines = ldm % 32 != 0;
+    const bool lines = s <= 7 && ldm % 32 != 0 && (d <= 3'000'000 || (s == 2 && groups >= 3));   // see rep_column
     const unsigned tiles = lines ? grid_cols<false>(d) : grid_cols<kSpreadEncodeRep>(d);
     const dim3 block(kBlock);
     bool generic = false;
@@ -461,19 +464,19 @@ hipError_t launch_encode_rep(const float* G, int64_t ldg, float* Z, int64_t ldm,
     DRACO_REP_DISPATCH(DRACO_LAUNCH, 8, 2, 1, 1, 2, 1, 1, 1)
 #undef DRACO_LAUNCH
 #undef DRACO_LAUNCH_ON
-    if (generic) launch_generic(G, ldg, Z, ldm, groups, r, r, 2, d, stream);
+    if (generic) launch_generic(G, ldg, Z, ldm, groups, r, r, lines, 2, d, stream);
     return hipGetLastError();
 }
 
 hipError_t launch_encode_rep_samples(const float* G, int64_t ldg, int m, float* Z, int64_t ldm, int P, int s, int64_t d,
                                      hipStream_t stream) {
     const int r = 2 * s + 1;
-    launch_generic(G, ldg, Z, ldm, P / r, r * m, r, 2, d, stream);
+    launch_generic(G, ldg, Z, ldm, P / r, r * m, r, ldm % 32 != 0, 2, d, stream);
     return hipGetLastError();
 }
 
 hipError_t launch_encode_rep_node(const float* Gn, int64_t ldg, float* z, int s, int64_t d, hipStream_t stream) {
-    launch_generic(Gn, ldg, z, 0, 1, 2 * s + 1, 1, 0, d, stream);
+    launch_generic(Gn, ldg, z, 0, 1, 2 * s + 1, 1, false, 0, d, stream);
     return hipGetLastError();
 }
 
