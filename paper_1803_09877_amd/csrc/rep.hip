@@ -56,11 +56,14 @@ __device__ __forceinline__ void encode_rep_body(const float* __restrict__ G, int
 
 // Column of this lane and whether its workgroup is whole: contiguous runs with neighbours on one die
 // (LINES; device_util.hpp), else the spread footprint.  Rows on the line grid lose with runs ((P, s, B, d) =
-// (45, 2, 180, 1.66 M) 257 us against 246, (45, 2, 45, 11.2 M) 648 against 609); off it whole steps, spread over
-// runs: B > P 1.00 to 1.13 for s = 1 .. 7, 1 to 45 / r groups and 50 000 to 5 M floats; B = P 0.98 to 1.09 up to
-// 3 M floats for all s; from there on up to 25.6 M floats 1.00 to 1.10 for s = 2 and three groups or more
-// ((45, 2, 45, 11.2 M) encoder 809 -> 747 us), but 0.91 to 1.04, mostly below 1, for the others ((18, 4, 11.2 M)
-// encoder 307 -> 329).
+// (45, 2, 180, 1.66 M) 257 us against 246, (45, 2, 45, 11.2 M) 648 against 609).  Off it, encoder with the
+// footprint against runs, B = P:
+//   5 M floats    (9, 1) 73 / 71, (10, 2) 78 / 74, (14, 3) 109 / 107, (18, 4) 141 / 141, (44, 5) 358 / 343,
+//                 (39, 6) 324 / 306, (15, 7) 129 / 120, (45, 7) 379 / 359
+//   8 M           (9, 1) 114 / 117, (14, 3) 172 / 177, (18, 4) 223 / 233, (15, 7) 198 / 203
+//   15 M          (9, 1) 211 / 230, (45, 1) 1021 / 1057, (14, 3) 315 / 357, (18, 4) 414 / 456, (15, 7) 369 / 390
+// so runs up to 5.5 M floats.  At s = 2 with three groups or more they hold on longer rows too ((45, 2), 11.2 M:
+// 805 against 744).  B > P: whole steps 1.00 to 1.13 times faster with runs for s = 1 .. 7 and 50 000 to 5 M.
 template <bool LINES>
 __device__ __forceinline__ int64_t rep_column(int64_t d, bool& full) {
     if constexpr (LINES) {
@@ -446,7 +449,7 @@ void launch_generic(const float* G, int64_t ldg, float* Z, int64_t ldm, int grou
 hipError_t launch_encode_rep(const float* G, int64_t ldg, float* Z, int64_t ldm, int P, int s, int64_t d,
                              hipStream_t stream) {
     const int r = 2 * s + 1, groups = P / r;
-    const bool lines = s <= 7 && ldm % 32 != 0 && (d <= 3'000'000 || (s == 2 && groups >= 3));   // see rep_column
+    const bool lines = s <= 7 && ldm % 32 != 0 && (d <= 5'500'000 || (s == 2 && groups >= 3));   // see rep_column
     const unsigned tiles = lines ? grid_cols<false>(d) : grid_cols<kSpreadEncodeRep>(d);
     const dim3 block(kBlock);
     bool generic = false;
