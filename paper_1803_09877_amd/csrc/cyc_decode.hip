@@ -396,7 +396,7 @@ hipError_t launch_cyc_recombine(const float* R, const float* Rlo, int lo, int64_
                                 int64_t d, hipStream_t stream) {
     const dim3 grid(grid_cols<kSpreadRecombine>(d)), block(kBlock);
     // rows too short to fill the chip: 16 rows in flight per lane, workgroups unlimited ((P, s, d) =
-    // (45, 3, 30 000): 9 us with 8 against 22 with two)
+    // (45, 3, 30 000): 11 us against 22 with two)
     const bool few = grid.x < 512;
     const bool stay = P * d * word_bytes(Rlo, lo) <= kSmallMessages;   // see launch_cyc_project
     with_format(Rlo, lo, [&](auto fmt) {

@@ -62,7 +62,8 @@ __device__ __forceinline__ void encode_rep_body(const float* __restrict__ G, int
 //                 (39, 6) 324 / 306, (15, 7) 129 / 120, (45, 7) 379 / 359
 //   8 M           (9, 1) 114 / 117, (14, 3) 172 / 177, (18, 4) 223 / 233, (15, 7) 198 / 203
 //   15 M          (9, 1) 211 / 230, (45, 1) 1021 / 1057, (14, 3) 315 / 357, (18, 4) 414 / 456, (15, 7) 369 / 390
-// so runs up to 5.5 M floats.  At s = 2 with three groups or more they hold on longer rows too ((45, 2), 11.2 M:
+// so runs up to 5.5 M floats.  At 20 M both occur ((9, 1) 283 / 275, (10, 2) 304 / 289, (39, 6) 1299 / 1266, but
+// (14, 3) 25.6 M 547 / 556): the footprint stays.  At s = 2 with three groups or more they hold on longer rows too ((45, 2), 11.2 M:
 // 805 against 744).  B > P: whole steps 1.00 to 1.13 times faster with runs for s = 1 .. 7 and 50 000 to 5 M.
 template <bool LINES>
 __device__ __forceinline__ int64_t rep_column(int64_t d, bool& full) {
