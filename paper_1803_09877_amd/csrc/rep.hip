@@ -3,7 +3,6 @@
 #include "device_util.hpp"
 
 #include <mutex>
-#include <type_traits>
 
 namespace draco {
 
@@ -54,36 +53,16 @@ __device__ __forceinline__ void encode_rep_body(const float* __restrict__ G, int
     }
 }
 
-// Column of this lane and whether its workgroup is whole: contiguous runs with neighbours on one die
-// (LINES; device_util.hpp), else the spread footprint.  Rows on the line grid lose with runs ((P, s, B, d) =
-// (45, 2, 180, 1.66 M) 257 us against 246, (45, 2, 45, 11.2 M) 648 against 609).  Off it, encoder with the
-// footprint against runs, B = P:
-//   5 M floats    (9, 1) 73 / 71, (10, 2) 78 / 74, (14, 3) 109 / 107, (18, 4) 141 / 141, (44, 5) 358 / 343,
-//                 (39, 6) 324 / 306, (15, 7) 129 / 120, (45, 7) 379 / 359
-//   8 M           (9, 1) 114 / 117, (14, 3) 172 / 177, (18, 4) 223 / 233, (15, 7) 198 / 203
-//   15 M          (9, 1) 211 / 230, (45, 1) 1021 / 1057, (14, 3) 315 / 357, (18, 4) 414 / 456, (15, 7) 369 / 390
-// so runs up to 5.5 M floats.  At 20 M both occur ((9, 1) 283 / 275, (10, 2) 304 / 289, (39, 6) 1299 / 1266, but
-// (14, 3) 25.6 M 547 / 556): the footprint stays.  At s = 2 with three groups or more they hold on longer rows too ((45, 2), 11.2 M:
-// 805 against 744).  B > P: whole steps 1.00 to 1.13 times faster with runs for s = 1 .. 7 and 50 000 to 5 M.
-template <bool LINES>
-__device__ __forceinline__ int64_t rep_column(int64_t d, bool& full) {
-    if constexpr (LINES) {
-        const int64_t tile = xcd_tile();
-        full = (tile + 1) * (kBlock * 4) <= d;
-        return (tile * kBlock + threadIdx.x) * 4;
-    } else {
-        full = block_is_full<kSpreadEncodeRep>(d, d);
-        return lane_column<kSpreadEncodeRep>(d);
-    }
-}
-
-template <int R, int GU, bool LINES>
+// Rows off the line grid keep the spread footprint too.  Contiguous runs with neighbours on one die (xcd_tile)
+// gain 2 to 6 % at many lengths, but lose in narrow ranges of d that no rule on sizes separates: encoder, footprint
+// against runs, (18, 4, 3.7 M + 1) 105 / 150 us, (45, 7, 3.7 M + 1) 276 / 348, (45, 2, 3.7 M + 1) 264 / 282, while
+// (45, 7, 4.2 M + 1) 304 / 282 and (45, 2, 1.47 M + 1) 104 / 97.
+template <int R, int GU>
 __global__ __launch_bounds__(kBlock) void encode_rep_kernel(const float* __restrict__ G, int64_t ldg,
                                                             float* __restrict__ Z, int64_t ldm,
                                                             int groups, int64_t d) {
-    bool full;
-    const int64_t c0 = rep_column<LINES>(d, full);
-    if (full) encode_rep_body<R, GU, true>(G, ldg, Z, ldm, groups, d, c0);
+    const int64_t c0 = lane_column<kSpreadEncodeRep>(d);
+    if (block_is_full<kSpreadEncodeRep>(d, d)) encode_rep_body<R, GU, true>(G, ldg, Z, ldm, groups, d, c0);
     else encode_rep_body<R, GU, false>(G, ldg, Z, ldm, groups, d, c0);
 }
 
@@ -122,13 +101,11 @@ __device__ __forceinline__ void encode_rep_generic_body(const float* __restrict_
     }
 }
 
-template <bool LINES>
 __global__ __launch_bounds__(kBlock) void encode_rep_generic_kernel(const float* __restrict__ G, int64_t ldg,
                                                                     float* __restrict__ Z, int64_t ldm,
                                                                     int groups, int rows, int copies, int64_t d) {
-    bool full;
-    const int64_t c0 = rep_column<LINES>(d, full);
-    if (full) encode_rep_generic_body<true>(G, ldg, Z, ldm, groups, rows, copies, d, c0);
+    const int64_t c0 = lane_column<kSpreadEncodeRep>(d);
+    if (block_is_full<kSpreadEncodeRep>(d, d)) encode_rep_generic_body<true>(G, ldg, Z, ldm, groups, rows, copies, d, c0);
     else encode_rep_generic_body<false>(G, ldg, Z, ldm, groups, rows, copies, d, c0);
 }
 
@@ -432,17 +409,12 @@ __global__ __launch_bounds__(kBlock) void decode_rep_generic_kernel(const float*
 namespace {
 
 // Sums of `rows` rows per group, stored `copies` times.
-void launch_generic(const float* G, int64_t ldg, float* Z, int64_t ldm, int groups, int rows, int copies, bool lines,
-                    int per_cu, int64_t d, hipStream_t stream) {
-    auto go = [&](auto lines) {
-        constexpr bool LINES = decltype(lines)::value;
-        const dim3 grid(grid_cols<!LINES && kSpreadEncodeRep>(d), (unsigned)groups);
-        allow_large_lds<encode_rep_generic_kernel<LINES>>();
-        hipLaunchKernelGGL(encode_rep_generic_kernel<LINES>, grid, dim3(kBlock), throttle_lds(per_cu, 0, 0), stream, G, ldg,
-                           Z, ldm, groups, rows, copies, d);
-    };
-    if (lines) go(std::true_type{});
-    else go(std::false_type{});
+void launch_generic(const float* G, int64_t ldg, float* Z, int64_t ldm, int groups, int rows, int copies, int per_cu,
+                    int64_t d, hipStream_t stream) {
+    const dim3 grid(grid_cols<kSpreadEncodeRep>(d), (unsigned)groups);
+    allow_large_lds<encode_rep_generic_kernel>();
+    hipLaunchKernelGGL(encode_rep_generic_kernel, grid, dim3(kBlock), throttle_lds(per_cu, 0, 0), stream, G, ldg, Z,
+                       ldm, groups, rows, copies, d);
 }
 
 }  // namespace
@@ -450,37 +422,30 @@ void launch_generic(const float* G, int64_t ldg, float* Z, int64_t ldm, int grou
 hipError_t launch_encode_rep(const float* G, int64_t ldg, float* Z, int64_t ldm, int P, int s, int64_t d,
                              hipStream_t stream) {
     const int r = 2 * s + 1, groups = P / r;
-    const bool lines = s <= 7 && ldm % 32 != 0 && (d <= 5'500'000 || (s == 2 && groups >= 3));   // see rep_column
-    const unsigned tiles = lines ? grid_cols<false>(d) : grid_cols<kSpreadEncodeRep>(d);
+    const unsigned tiles = grid_cols<kSpreadEncodeRep>(d);
     const dim3 block(kBlock);
     bool generic = false;
-#define DRACO_LAUNCH_ON(R, GU, BPC, LINES)                                                                   \
-    {                                                                                                        \
-        allow_large_lds<encode_rep_kernel<R, GU, LINES>>();                                                  \
-        hipLaunchKernelGGL((encode_rep_kernel<R, GU, LINES>), dim3(tiles, (unsigned)((groups + GU - 1) / GU)),    \
-                           block, throttle_lds(BPC, 0, 0), stream, G, ldg, Z, ldm, groups, d);               \
-    }
 #define DRACO_LAUNCH(R, GU, BPC)                                                                             \
     {                                                                                                        \
-        if (lines) DRACO_LAUNCH_ON(R, GU, BPC, true)                                                         \
-        else DRACO_LAUNCH_ON(R, GU, BPC, false)                                                              \
+        allow_large_lds<encode_rep_kernel<R, GU>>();                                                         \
+        hipLaunchKernelGGL((encode_rep_kernel<R, GU>), dim3(tiles, (unsigned)((groups + GU - 1) / GU)),      \
+                           block, throttle_lds(BPC, 0, 0), stream, G, ldg, Z, ldm, groups, d);               \
     }
     DRACO_REP_DISPATCH(DRACO_LAUNCH, 8, 2, 1, 1, 2, 1, 1, 1)
 #undef DRACO_LAUNCH
-#undef DRACO_LAUNCH_ON
-    if (generic) launch_generic(G, ldg, Z, ldm, groups, r, r, lines, 2, d, stream);
+    if (generic) launch_generic(G, ldg, Z, ldm, groups, r, r, 2, d, stream);
     return hipGetLastError();
 }
 
 hipError_t launch_encode_rep_samples(const float* G, int64_t ldg, int m, float* Z, int64_t ldm, int P, int s, int64_t d,
                                      hipStream_t stream) {
     const int r = 2 * s + 1;
-    launch_generic(G, ldg, Z, ldm, P / r, r * m, r, ldm % 32 != 0, 2, d, stream);
+    launch_generic(G, ldg, Z, ldm, P / r, r * m, r, 2, d, stream);
     return hipGetLastError();
 }
 
 hipError_t launch_encode_rep_node(const float* Gn, int64_t ldg, float* z, int s, int64_t d, hipStream_t stream) {
-    launch_generic(Gn, ldg, z, 0, 1, 2 * s + 1, 1, false, 0, d, stream);
+    launch_generic(Gn, ldg, z, 0, 1, 2 * s + 1, 1, 0, d, stream);
     return hipGetLastError();
 }
 
