@@ -323,8 +323,8 @@ __device__ __forceinline__ bool block_is_full(int64_t len, int64_t need) {
 // any grid of the 8-bit slab), so both ends of every contiguous run a wavefront writes are parts
 // of lines.  Runs next to each other are then written by workgroups that share an L2: workgroup b
 // runs on accelerator die b mod 8, and tile xcd_tile() gives each die one contiguous range of
-// tiles, which its L2 merges.  The cyclic encoder for B = P uses plain stores there; the repetition encoder and the
-// B > P forms gain with the non-temporal hint as it is.
+// tiles, which its L2 merges.  The cyclic encoder for B = P uses plain stores there; the B > P forms gain with the
+// non-temporal hint as it is.  The repetition encoder does not use it (rep.hip).
 __device__ __forceinline__ int64_t xcd_tile(unsigned blocks = gridDim.x) {
     const int64_t per = blocks / 8, b = blockIdx.x;
     return b < per * 8 ? (b % 8) * per + b / 8 : b;
