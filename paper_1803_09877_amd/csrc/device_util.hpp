@@ -207,7 +207,8 @@ __device__ __forceinline__ void st_lo(float* base, int64_t off, float4 hi, float
         }
     }
 }
-// Load of a lane's 4 second words, unconverted (missing ones read as zero).
+// Load of a lane's 4 second words, unconverted (missing ones read as zero).  A message is an even number of words: n is
+// 4, 2 or 0, and two words are one load (16-bit loads into halves of one register wait for each other).
 template <bool FULL, int LO, bool NT = true>
 __device__ __forceinline__ lo_raw_t<LO> ld_lo(const float* base, int64_t off, int n) {
     static_assert(LO == kLoF32 || LO == kLoBf16 || LO == kLoI8, "a second word has a format");
@@ -219,9 +220,11 @@ __device__ __forceinline__ lo_raw_t<LO> ld_lo(const float* base, int64_t off, in
             return ld_hint<NT>(reinterpret_cast<const vbf4*>(p));
         } else {
             vbf4 b = {(__bf16)0.0f, (__bf16)0.0f, (__bf16)0.0f, (__bf16)0.0f};
-            if (n > 0) b.x = p[0];
-            if (n > 1) b.y = p[1];
-            if (n > 2) b.z = p[2];
+            if (n > 0) {
+                const vbf2 pair = *reinterpret_cast<const vbf2*>(p);
+                b.x = pair.x;
+                b.y = pair.y;
+            }
             return b;
         }
     } else {
@@ -230,9 +233,7 @@ __device__ __forceinline__ lo_raw_t<LO> ld_lo(const float* base, int64_t off, in
             return ld_hint<NT>(reinterpret_cast<const unsigned*>(p));
         } else {
             unsigned w = 0;
-            if (n > 0) w |= (unsigned)p[0];
-            if (n > 1) w |= (unsigned)p[1] << 8;
-            if (n > 2) w |= (unsigned)p[2] << 16;
+            if (n > 0) w = *reinterpret_cast<const unsigned short*>(p);
             return w;
         }
     }
