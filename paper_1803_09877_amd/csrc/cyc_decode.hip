@@ -368,7 +368,9 @@ __global__ __launch_bounds__(kBlock) void cyc_project_reduce_kernel(const double
 // u = R_{.,U} b on packed complex messages, unpacked to reals: honest rows in
 // ascending node order, fp64 accumulation, one rounding to fp32.  Lane l of the wavefront holds the index and the
 // coefficient of the l-th honest row of 64 (a scalar load for each row would be waited for one by one, half of
-// the time on short rows).  UN rows in flight; no load of a whole round is under a condition (cyc_project_body).
+// the time on short rows).  UN rows in flight; no load is under a condition (cyc_project_body): with the last round's
+// under one, rows of no more than two rounds, a dozen nodes, had all of theirs there ((12, 2, 2 M), one word: 21.2 us,
+// 18.0 so).
 template <bool FULL, int LO, int UN, bool NT>
 __device__ __forceinline__ void cyc_recombine_body(const float* __restrict__ Rm, const float* __restrict__ Rlo,
                                                    int64_t ldm,
@@ -401,21 +403,16 @@ __device__ __forceinline__ void cyc_recombine_body(const float* __restrict__ Rm,
 #pragma unroll
         for (int i = 0; i < UN; ++i) fetch(i, min(i, cnt - 1));
         int q = 0;
-        for (; q + 2 * UN <= cnt; q += UN) {
+        for (; q + UN < cnt; q += UN) {   // (behind the last row it is read again)
 #pragma unroll
             for (int i = 0; i < UN; ++i) {
                 use(i, q + i);
-                fetch(i, q + UN + i);
+                fetch(i, min(q + UN + i, cnt - 1));
             }
         }
-        for (; q < cnt; q += UN) {
 #pragma unroll
-            for (int i = 0; i < UN; ++i) {
-                if (q + i < cnt) {
-                    use(i, q + i);
-                    if (q + UN + i < cnt) fetch(i, q + UN + i);
-                }
-            }
+        for (int i = 0; i < UN; ++i) {
+            if (q + i < cnt) use(i, q + i);
         }
     }
     if (realout) {  // unpacked wire: the sum is the real part, one float per complex entry
@@ -659,7 +656,9 @@ hipError_t launch_cyc_recombine(const float* R, const float* Rlo, int lo, int64_
         constexpr int LO = decltype(fmt)::value;
         // Rows in flight and workgroups per CU at (45, 3, 25.6 M): with an 8-bit second word 0.81 of the
         // HBM peak with 4 workgroups x 2 rows (also 2 x 6 and 6 x 1); a 16-bit one wants more wavefronts
-        // for its 8-byte loads (four workgroups 0.82, two 0.69-0.76).
+        // for its 8-byte loads (four workgroups 0.82, two 0.69-0.76).  Two fp32 words of
+        // short rows, which do not fill the chip, want five rows ((45, 3, 150 000): 15.3 us, 16.3 with three; 22.0 and 21.5 at
+        // 300 000).
         constexpr int UN = LO == kLoNone ? 6 : LO == kLoI8 ? 2 : 3;
         const size_t lds = throttle_lds(LO == kLoBf16 || LO == kLoI8 ? 4 : 2, 0, 0);
         auto go = [&](auto un, auto nt, size_t bytes) {
@@ -672,6 +671,7 @@ hipError_t launch_cyc_recombine(const float* R, const float* Rlo, int lo, int64_
         if (few)
             hipLaunchKernelGGL(cyc_recombine_few_kernel<LO>, dim3((unsigned)((d + 255) / 256)), block, 0, stream, R, Rlo, ldm, b,
                                idx, nu, u, realout ? 1 : 0, d);
+        else if (LO == kLoF32 && !project_speculates(d, P)) go(std::integral_constant<int, LO == kLoF32 ? 5 : UN>{}, std::false_type{}, lds);
         else if (stay) go(std::integral_constant<int, UN>{}, std::false_type{}, lds);
         else go(std::integral_constant<int, UN>{}, std::true_type{}, lds);
     });
