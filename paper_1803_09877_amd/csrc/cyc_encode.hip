@@ -228,10 +228,9 @@ hipError_t launch_encode_cyc_real(const float* G, int64_t ldg, float* Z, int64_t
                                   int s, int64_t d, hipStream_t stream) {
     const dim3 grid(grid_cols<kSpreadEncodeCyc>(d)), block(kBlock);
     const int r = 2 * s + 1;
-    const bool one_per_cu = s <= 3 && P >= 32;
     if (s > kMaxCycS && s <= kMaxNarrowS) return launch_narrow(s, true, stream, G, ldg, 1, Z, nullptr, kLoNone, ldm, coef, CycTaps{nullptr, nullptr, nullptr}, P, d);
 #define DRACO_CASE(S) \
-    case S: return launch_encode_cyc_real_s<S>(one_per_cu, stream, G, ldg, Z, ldm, coef, P, d);
+    case S: return launch_encode_cyc_real_s<S>(stream, G, ldg, Z, ldm, coef, P, d);
     switch (s) {
         DRACO_CASE(0) DRACO_CASE(1) DRACO_CASE(2) DRACO_CASE(3) DRACO_CASE(4) DRACO_CASE(5) DRACO_CASE(6) DRACO_CASE(7)
         DRACO_CASE(8) DRACO_CASE(9) DRACO_CASE(10)

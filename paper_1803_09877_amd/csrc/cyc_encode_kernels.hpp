@@ -428,6 +428,7 @@ __device__ __forceinline__ void encode_cyc_real_body(const float* __restrict__ G
         put((uu + 2 * S) % R, ring[uu]);
         ring[(uu + D) % U] = fetch();
         node(uu, n0 + uu);
+        if constexpr (S == 10) __builtin_amdgcn_sched_barrier(0);   // (rows loaded any earlier go to scratch memory)
     };
     if (last >= U) {
 #pragma unroll
@@ -457,11 +458,13 @@ rest:
     }
 }
 
-template <int S, int D, bool LINES>
-__global__ __launch_bounds__(kBlock) void encode_cyc_real_kernel(const float* __restrict__ G, int64_t ldg,
-                                                                 float* __restrict__ Z, int64_t ldm,
-                                                                 const double2* __restrict__ coef, int P,
-                                                                 int64_t d) {
+// Compiled for the workgroups per CU that it is launched with (four wavefronts, one per SIMD, each): left alone the
+// compiler gives windows of 11 rows and more over 256 registers, with which a second workgroup does not fit.
+template <int S, int D, bool LINES, int PER_CU>
+__global__ __launch_bounds__(kBlock, PER_CU) void encode_cyc_real_kernel(const float* __restrict__ G, int64_t ldg,
+                                                                         float* __restrict__ Z, int64_t ldm,
+                                                                         const double2* __restrict__ coef, int P,
+                                                                         int64_t d) {
     extern __shared__ float4 head[];  // [2S][kBlock]
     constexpr bool SPREAD = kSpreadEncodeCyc && !LINES;
     const int64_t c0 = lane_column<SPREAD>(d);
@@ -875,8 +878,8 @@ hipError_t launch_encode_cyc_s(bool many_rows, hipStream_t stream, const float* 
                                float* Zlo, int lo, int64_t ldm, const CycTaps& tab, int P, int64_t d);
 // Same for the unpacked wire (real gradients in, d complex entries out).
 template <int S>
-hipError_t launch_encode_cyc_real_s(bool one_per_cu, hipStream_t stream, const float* G, int64_t ldg,
-                                    float* Z, int64_t ldm, const double2* coef, int P, int64_t d);
+hipError_t launch_encode_cyc_real_s(hipStream_t stream, const float* G, int64_t ldg, float* Z,
+                                    int64_t ldm, const double2* coef, int P, int64_t d);
 // Same for the B > P form (m per-sample rows per unit gradient).
 template <int S>
 hipError_t launch_encode_cyc_multi_s(hipStream_t stream, const float* G, int64_t ldg, int m, float* Z,
