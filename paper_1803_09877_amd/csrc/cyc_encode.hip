@@ -195,10 +195,9 @@ hipError_t launch_encode_cyc(const float* G, int64_t ldg, float* Z, float* Zlo, 
                              int P, int s, int64_t d, hipStream_t stream) {
     const int64_t mlen = 2 * ((d + 1) / 2);
     const int r = 2 * s + 1;
-    const bool many_rows = P >= 32;
     if (s > kMaxCycS && s <= kMaxNarrowS) return launch_narrow(s, false, stream, G, ldg, 1, Z, Zlo, lo, ldm, nullptr, tab, P, d);
 #define DRACO_CASE(S) \
-    case S: return launch_encode_cyc_s<S>(many_rows, stream, G, ldg, Z, Zlo, lo, ldm, tab, P, d);
+    case S: return launch_encode_cyc_s<S>(stream, G, ldg, Z, Zlo, lo, ldm, tab, P, d);
     switch (s) {
         DRACO_CASE(0) DRACO_CASE(1) DRACO_CASE(2) DRACO_CASE(3) DRACO_CASE(4) DRACO_CASE(5) DRACO_CASE(6) DRACO_CASE(7)
         DRACO_CASE(8) DRACO_CASE(9) DRACO_CASE(10)

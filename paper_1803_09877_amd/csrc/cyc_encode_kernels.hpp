@@ -62,6 +62,69 @@ __device__ __forceinline__ void store_message(float* __restrict__ Z, float* __re
     }
 }
 
+// Rows in rounds of R, NB - 1 of them ahead of the arithmetic (a ring of NB register buffers).  Loads and stores alternate
+// R at a time; a store and a load in turn (encode_cyc_body) is slower on the line grid, see launch_all_nodes.
+template <int S, int NB, bool FULL, int LO>
+__device__ __forceinline__ void encode_cyc_rounds_body(const float* __restrict__ G, int64_t ldg, float* __restrict__ Z,
+                                                       float* __restrict__ Zlo, int64_t ldm,
+                                                       const CycTaps tab, int P, int64_t d, int64_t c0,
+                                                       float4* head /* LDS [2S][kBlock] */) {
+    constexpr int R = 2 * S + 1;
+    const int64_t mlen = 2 * ((d + 1) / 2);
+    if (!FULL && c0 >= mlen) return;
+    const int nin = FULL ? 4 : clamp4(d - c0);      // gradient floats that exist (the pad of an odd d reads as 0)
+    const int nout = FULL ? 4 : clamp4(mlen - c0);  // message floats to write
+
+    double wre[R][2], wim[R][2];  // window slot = row index mod R
+    auto put = [&](int slot, const float4& raw, int kappa) {
+        rotate_in(tab, kappa, (double)raw.x, (double)raw.y, (double)raw.z, (double)raw.w, wre[slot], wim[slot]);
+    };
+    // fetch the rows that nodes n0 .. n0+R-1 bring into the window
+    auto issue = [&](int n0, float4 (&buf)[R]) {
+#pragma unroll
+        for (int uu = 0; uu < R; ++uu) {
+            const int kk = n0 + uu + 2 * S;
+            if (n0 + uu < P) {
+                if (kk < P) buf[uu] = ldx<FULL>(G + (int64_t)kk * ldg + c0, nin);
+                else buf[uu] = head[(kk - P) * kBlock + threadIdx.x];
+            }
+        }
+    };
+    auto consume = [&](int n0, const float4 (&buf)[R]) {
+#pragma unroll
+        for (int uu = 0; uu < R; ++uu) {
+            const int n = n0 + uu;
+            if (n < P) {
+                put((uu + 2 * S) % R, buf[uu], n + 2 * S);
+                double are0, aim0, are1, aim1;
+                tap_sum<R>(tab, n, wre, wim, uu % R, are0, aim0, are1, aim1);
+                store_message<FULL, LO>(Z, Zlo, (int64_t)n * ldm + c0, are0, aim0, are1, aim1, nout);
+            }
+        }
+    };
+#pragma unroll
+    for (int k = 0; k < 2 * S; ++k) {
+        const float4 raw = ldx<FULL>(G + (int64_t)k * ldg + c0, nin);
+        head[k * kBlock + threadIdx.x] = raw;
+        put(k, raw, k);
+    }
+    float4 buf[NB][R];
+#pragma unroll
+    for (int b = 0; b < NB - 1; ++b)
+        if (b * R < P) issue(b * R, buf[b]);
+    for (int n0 = 0; n0 < P; n0 += NB * R) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int cur = n0 + b * R;
+            if (cur < P) {
+                const int nxt = cur + (NB - 1) * R;
+                if (nxt < P) issue(nxt, buf[(b + NB - 1) % NB]);
+                consume(cur, buf[b]);
+            }
+        }
+    }
+}
+
 // D rows are in flight: a row's registers are loaded again as soon as it has entered the window.
 template <int S, int D, bool FULL, int LO>
 __device__ __forceinline__ void encode_cyc_body(const float* __restrict__ G, int64_t ldg, float* __restrict__ Z,
@@ -119,6 +182,7 @@ __device__ __forceinline__ void encode_cyc_body(const float* __restrict__ G, int
         put((uu + 2 * S) % R, ring[uu], n0 + uu + 2 * S);
         ring[(uu + D) % U] = fetch();
         node(uu, n0 + uu);
+        if constexpr (S == 6 || S == 7) __builtin_amdgcn_sched_barrier(0);   // (rows loaded any earlier do not fit the registers)
     };
     if (last >= U) {
 #pragma unroll
@@ -148,18 +212,31 @@ rest:   // the other nodes: rows that are in flight, then those parked in LDS
     }
 }
 
+// The kernels are compiled for the workgroups per CU that they are launched with (four wavefronts, one per SIMD, each): left
+// alone the compiler gives windows of 11 rows and more over 256 registers, with which a second workgroup does not fit.
 // LINES: workgroups own 4 KiB contiguously (device_util.hpp, "rows off the line grid"); else the spread footprint.
-template <int S, int D, int LO, bool LINES>
-__global__ __launch_bounds__(kBlock) void encode_cyc_kernel(const float* __restrict__ G, int64_t ldg,
-                                                            float* __restrict__ Z, float* __restrict__ Zlo,
-                                                            int64_t ldm, const CycTaps tab, int P,
-                                                            int64_t d) {
+template <int S, int D, int LO, bool LINES, int PER_CU>
+__global__ __launch_bounds__(kBlock, PER_CU) void encode_cyc_kernel(const float* __restrict__ G, int64_t ldg,
+                                                                    float* __restrict__ Z, float* __restrict__ Zlo,
+                                                                    int64_t ldm, const CycTaps tab, int P,
+                                                                    int64_t d) {
     extern __shared__ float4 head[];  // [2S][kBlock]
     const int64_t mlen = 2 * ((d + 1) / 2);
     constexpr bool SPREAD = kSpreadEncodeCyc && !LINES;
     const int64_t c0 = lane_column<SPREAD>(mlen);
     if (block_is_full<SPREAD>(mlen, d)) encode_cyc_body<S, D, true, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, c0, head);
     else encode_cyc_body<S, D, false, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, c0, head);
+}
+template <int S, int NB, int LO, int PER_CU>
+__global__ __launch_bounds__(kBlock, PER_CU) void encode_cyc_rounds_kernel(const float* __restrict__ G, int64_t ldg,
+                                                                           float* __restrict__ Z, float* __restrict__ Zlo,
+                                                                           int64_t ldm, const CycTaps tab, int P,
+                                                                           int64_t d) {
+    extern __shared__ float4 head[];  // [2S][kBlock]
+    const int64_t mlen = 2 * ((d + 1) / 2);
+    const int64_t c0 = lane_column<kSpreadEncodeCyc>(mlen);
+    if (block_is_full<kSpreadEncodeCyc>(mlen, d)) encode_cyc_rounds_body<S, NB, true, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, c0, head);
+    else encode_cyc_rounds_body<S, NB, false, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, c0, head);
 }
 
 // The same encoder for rows too short to fill the chip.  There the walk down P rows is
@@ -458,8 +535,6 @@ rest:
     }
 }
 
-// Compiled for the workgroups per CU that it is launched with (four wavefronts, one per SIMD, each): left alone the
-// compiler gives windows of 11 rows and more over 256 registers, with which a second workgroup does not fit.
 template <int S, int D, bool LINES, int PER_CU>
 __global__ __launch_bounds__(kBlock, PER_CU) void encode_cyc_real_kernel(const float* __restrict__ G, int64_t ldg,
                                                                          float* __restrict__ Z, int64_t ldm,
@@ -871,10 +946,9 @@ __global__ __launch_bounds__(kBlock) void encode_cyc_multi_kernel(const float* _
 
 
 // Launch of the all-node encoder for one s (defined in the translation unit of that s).
-// many_rows: whether a workgroup lives long enough for the form with four pieces per lane.  lo: format of the
-// second word when Zlo is not null.
+// lo: format of the second word when Zlo is not null.
 template <int S>
-hipError_t launch_encode_cyc_s(bool many_rows, hipStream_t stream, const float* G, int64_t ldg, float* Z,
+hipError_t launch_encode_cyc_s(hipStream_t stream, const float* G, int64_t ldg, float* Z,
                                float* Zlo, int lo, int64_t ldm, const CycTaps& tab, int P, int64_t d);
 // Same for the unpacked wire (real gradients in, d complex entries out).
 template <int S>

@@ -66,3 +66,12 @@ def test_unpacked_encoders_fit_as_often_as_they_are_launched(kernels):
         assert registers <= 512 // per_cu, (s, per_cu, registers)
         assert scratch == 0 or (s, per_cu) == (8, 2), (s, per_cu, scratch)
     assert {s for s, _, _, per_cu in found if per_cu == 2} == set(range(9))
+
+
+def test_packed_encoders_fit_as_often_as_they_are_launched(kernels):
+    ring, rounds = (arguments(kernels, "encode_cyc" + n + "_kernel") for n in ("", "_rounds"))
+    for (s, *_, per_cu), (registers, scratch) in list(ring.items()) + list(rounds.items()):
+        assert registers <= 512 // per_cu, (s, per_cu, registers)
+        assert scratch <= (64 if (s, per_cu) == (7, 2) else 0), (s, per_cu, scratch)
+    for found, widest in ((ring, 7), (rounds, 7)):
+        assert {s for s, *_, per_cu in found if per_cu == 2} == set(range(widest + 1))
