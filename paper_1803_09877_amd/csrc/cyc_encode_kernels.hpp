@@ -758,7 +758,8 @@ __device__ __forceinline__ void encode_cyc_multi_ring_body(const float* __restri
 // Structure, and the reasons for it, as in encode_cyc_body: rounds of R units without a load under a
 // condition, the first one a copy of its own, then the unit whose rows are in flight, then those parked in LDS.
 // At (45, 5, B = 180, 25.6 M) on the 5-byte wire with one workgroup per CU 4247 us; two or three units in flight 4292 and
-// 4399, two workgroups per CU 4445, two units behind conditions (as the ring above) on two workgroups 4309.
+// 4399, two workgroups per CU 4445, two units behind conditions (as the ring above) on two workgroups 4309.  (Those two are
+// still the shorter ones where a launch has two workgroups per CU at most: (45, 5, B = 180, 500 001) 84 us, now 91.)
 template <int S, int LO>
 __device__ __forceinline__ void encode_cyc_multi_four_body(const float* __restrict__ G, int64_t ldg,
                                                            float* __restrict__ Z, float* __restrict__ Zlo,
@@ -888,13 +889,16 @@ __device__ __forceinline__ void encode_cyc_multi_tail(const float* __restrict__ 
     }
 }
 
-// Workgroups that share the whole vectors of a row, and this lane's column among them: contiguous 4 KiB
-// where message rows are off the line grid (device_util.hpp), else the spread footprint.  Encoder in us, contiguous /
-// spread / contiguous with neighbours on one die: (45, 3, B = 4P, 3.7 M + 1) 732 / 793 / 902, (45, 5, B = 4P, 3 M + 1)
-// 569 / 616 / 577, (45, 5, B = 2P, 3.7 M + 1) on two fp32 words 618 / 635 / 776, (45, 3, B = 8P, 1 M + 1) 331 / 344 / 319.
+// Workgroups that share the whole vectors of a row, and this lane's column among them (device_util.hpp, "rows off the line
+// grid").  lines: 0 the spread footprint, on the line grid; off it contiguous 4 KiB (1), with neighbours on one die (2) where
+// two workgroups per CU walk rows that are always in flight, but for long rows on few nodes.  Encoder in us, contiguous /
+// spread / contiguous with neighbours on one die: one workgroup per CU, (45, 3, B = 4P, 3.7 M + 1) 732 / 793 / 902, (45, 5,
+// B = 4P, 3 M + 1) 569 / 616 / 577; two, (45, 3, B = 8P, 1 M + 1) 331 / 344 / 319, (45, 3, B = 4P, 800 001) 155 / 163 / 147, (10, 3,
+// B = 8P, 4 M + 1) 272 / - / 286; rows not always in flight, (45, 5, B = 2P, 3.7 M + 1) on two fp32 words 618 / 635 / 776.
 __device__ __forceinline__ unsigned multi_blocks(int64_t d) { return gridDim.x - (d % 4 != 0 ? 1u : 0u); }
 __device__ __forceinline__ int64_t multi_column(int lines, int64_t d) {
-    if (lines != 0) return ((int64_t)blockIdx.x * kBlock + threadIdx.x) * 4;
+    if (lines == 2) return (xcd_tile(multi_blocks(d)) * kBlock + threadIdx.x) * 4;
+    if (lines == 1) return ((int64_t)blockIdx.x * kBlock + threadIdx.x) * 4;
     return lane_column<kSpreadEncodeCyc>(d / 4 * 4, multi_blocks(d));
 }
 
