@@ -175,7 +175,7 @@ __device__ __forceinline__ void store_wave_sums(const double2 (*wsum)[kMaxNodes]
 // of a few us is bound by latency: all rows of a group are loaded at once.  For second words of 8 and 16 bits straight through,
 // under no condition ((45, 3, 20 000), 5-byte wire: 6.1 us, 7.6 as bursts); the others gain from a row's
 // arithmetic standing behind the row's condition, where its wait is for that row alone (8-byte wire: 7.6 us, 9.5
-// straight through; one word: 6.4 and 6.5).
+// straight through; one word: 6.4 and 6.5; 6-byte wire, (250, 1, 10 000): 7.9 us as bursts, 7.4 straight through).
 template <int LO, int F>
 __global__ __launch_bounds__(kBlock) void cyc_project_short_kernel(const float* __restrict__ Rm, const float* __restrict__ Rlo,
                                                                    int64_t ldm, const float* __restrict__ f, uint64_t f_seed,
@@ -190,7 +190,8 @@ __global__ __launch_bounds__(kBlock) void cyc_project_short_kernel(const float* 
     store_wave_sums(wsum, partial + (int64_t)blockIdx.x * P, j0, j1);
 }
 
-// Rows in bursts of 8.
+// Rows in bursts of 8.  (A group of 8 nodes is one burst.  As cyc_project_body with its rows under conditions these kernels
+// take 107 registers for 82 and 10 to 40 % longer: the loop is what keeps a row's conversions behind its load.)
 template <int LO, bool FULL>
 __device__ __forceinline__ void cyc_project_burst_body(const float* __restrict__ Rm, const float* __restrict__ Rlo,
                                                        int64_t ldm, const float* __restrict__ f, uint64_t f_seed, int64_t col,

@@ -15,34 +15,27 @@ namespace draco {
 namespace {
 
 
-// Large slabs are streamed: every byte is used once, so 16-byte accesses carry the
-// non-temporal hint (NT; measured on MI355X: +10% on read-dominated passes).  Without it where
-// a slab fits the 256 MiB memory-side cache and is read again soon, and where neighbouring
-// workgroups write parts of the same cache line (see "rows off the line grid").
+// Large slabs are streamed: every byte is used once, so accesses carry the non-temporal hint
+// (measured on MI355X: +10% on read-dominated passes); loads do without it (NT = false) where a slab
+// fits the 256 MiB memory-side cache and is read again soon.
 typedef float vfloat4 __attribute__((ext_vector_type(4)));
 template <bool NT, class T>
 __device__ __forceinline__ T ld_hint(const T* p) {
     if constexpr (NT) return __builtin_nontemporal_load(p);
     else return *p;
 }
-template <bool NT, class T>
-__device__ __forceinline__ void st_hint(T* p, T v) {
-    if constexpr (NT) __builtin_nontemporal_store(v, p);
-    else *p = v;
-}
 template <bool NT = true>
 __device__ __forceinline__ float4 ld4(const float* p) {
     const vfloat4 v = ld_hint<NT>(reinterpret_cast<const vfloat4*>(p));
     return make_float4(v.x, v.y, v.z, v.w);
 }
-template <bool NT = true>
 __device__ __forceinline__ void st4(float* p, float4 v) {
     vfloat4 w;
     w.x = v.x;
     w.y = v.y;
     w.z = v.z;
     w.w = v.w;
-    st_hint<NT>(reinterpret_cast<vfloat4*>(p), w);
+    __builtin_nontemporal_store(w, reinterpret_cast<vfloat4*>(p));
 }
 
 typedef float vfloat2 __attribute__((ext_vector_type(2)));
@@ -56,7 +49,8 @@ __device__ __forceinline__ void st2(float* p, float2 v) {
     w.y = v.y;
     __builtin_nontemporal_store(w, reinterpret_cast<vfloat2*>(p));
 }
-// Entry i of a table that the kernel does not write, i the same in every lane: a scalar load.  Without the
+// Entry i of a table that the kernel does not write: a scalar load where i is the same in every lane (where each lane has
+// its own, as at the row ends of the encoder for B > P, the compiler makes it a vector load).  Without the
 // address space the compiler must assume that the kernel's stores may reach the table, takes a vector load and
 // waits for it with s_waitcnt vmcnt(0), which also waits for every row in flight and for the stores before it.
 typedef double vdouble2 __attribute__((ext_vector_type(2)));
@@ -121,12 +115,12 @@ __device__ __forceinline__ float4 ldx(const float* p, int n) {
         return v;
     }
 }
-template <bool FULL, bool NT = true>
+template <bool FULL>
 __device__ __forceinline__ void stx(float* p, float4 v, int n) {
     if constexpr (FULL) {
-        st4<NT>(p, v);
+        st4(p, v);
     } else {
-        if (n >= 4) st4<NT>(p, v);
+        if (n >= 4) st4(p, v);
         else if (n > 0) st4_partial(p, v, n);
     }
 }
@@ -173,11 +167,11 @@ template <> struct lo_raw<kLoBf16> { typedef vbf4 type; };
 template <> struct lo_raw<kLoI8> { typedef unsigned type; };
 template <int LO> using lo_raw_t = typename lo_raw<LO>::type;
 
-template <bool FULL, int LO, bool NT = true>
+template <bool FULL, int LO>
 __device__ __forceinline__ void st_lo(float* base, int64_t off, float4 hi, float4 v, int n) {
     static_assert(LO == kLoF32 || LO == kLoBf16 || LO == kLoI8, "a second word has a format");
     if constexpr (LO == kLoF32) {
-        stx<FULL, NT>(base + off, v, n);
+        stx<FULL>(base + off, v, n);
     } else if constexpr (LO == kLoBf16) {
         __bf16* p = reinterpret_cast<__bf16*>(base) + off;
         vfloat4 w;
@@ -187,7 +181,7 @@ __device__ __forceinline__ void st_lo(float* base, int64_t off, float4 hi, float
         w.w = v.w;
         const vbf4 b = __builtin_convertvector(w, vbf4);   // round to nearest even
         if (FULL || n >= 4) {
-            st_hint<NT>(reinterpret_cast<vbf4*>(p), b);
+            __builtin_nontemporal_store(b, reinterpret_cast<vbf4*>(p));
         } else {
             if (n > 0) p[0] = b.x;
             if (n > 1) p[1] = b.y;
@@ -199,7 +193,7 @@ __device__ __forceinline__ void st_lo(float* base, int64_t off, float4 hi, float
                        q3 = lo8_code(hi.w, v.w);
         if (FULL || n >= 4) {
             const unsigned w = (q0 & 0xFFu) | ((q1 & 0xFFu) << 8) | ((q2 & 0xFFu) << 16) | (q3 << 24);
-            st_hint<NT>(reinterpret_cast<unsigned*>(p), w);
+            __builtin_nontemporal_store(w, reinterpret_cast<unsigned*>(p));
         } else {
             if (n > 0) p[0] = (signed char)q0;
             if (n > 1) p[1] = (signed char)q1;
@@ -342,7 +336,9 @@ __device__ __forceinline__ bool block_is_full(int64_t len, int64_t need) {
 //
 // Neighbours on one die (workgroup b runs on accelerator die b mod 8; tile xcd_tile() gives each die one
 // contiguous range of tiles) share such lines in its L2.  That helps where all workgroups of a launch are resident, as in
-// the kernels for short rows; in longer launches it gains at some lengths and loses as much at others.
+// the kernels for short rows, and with several rows of loads for one of stores (B a multiple of 4P); in longer launches for
+// B = P it gains at some lengths and loses as much at others.  (Time alone says that shared lines are the cause; no run of
+// the byte counters has compared the two footprints.)
 __device__ __forceinline__ int64_t xcd_tile(unsigned blocks = gridDim.x) {
     const int64_t per = blocks / 8, b = blockIdx.x;
     return b < per * 8 ? (b % 8) * per + b / 8 : b;

@@ -21,9 +21,9 @@ constexpr int64_t kSmallMessages = 320ll << 20;
 constexpr int kLocateMaxS = 16;       // largest s the on-device locator handles
 
 // Which kernel families spread a workgroup's wavefronts over a 128 KiB window of each row
-// (device_util.hpp, "workgroup footprint"); chosen per family by measurement.
+// (device_util.hpp, "workgroup footprint"); chosen per family by measurement.  The repetition encoder goes by its rows'
+// stride alone (rep.hip).
 constexpr bool kSpreadEncodeCyc = true;
-constexpr bool kSpreadEncodeRep = true;
 constexpr bool kSpreadVote = true;
 constexpr bool kSpreadRecombine = true;
 constexpr bool kSpreadUpdate = true;
