@@ -39,6 +39,16 @@ int draco_plan_kernel_time(draco_plan* plan, int kind, double* total_ms, int* la
 int draco_plan_kernel_times(draco_plan* plan, int kind, double* ms_host, int capacity,
                             int* launches);
 
+/* What a cyclic plan that has been prepared expects of its next decode and what
+ * became of the last one (waits for the device): words_host[0] clean decodes in
+ * a row, up to the number from which no sample is taken; [1] what the last
+ * decode's projection speculated on: 0 nothing, 1 nobody, 2 the set located on a
+ * sample; [2] 1 if that was the set found, so that the second pass was left out;
+ * [3] the status of the last sample's locator; [4] decodes left that take no
+ * sample after samples that misled; [5] samples in a row that misled.
+ * DRACO_EINVAL for other plans. */
+int draco_plan_speculation_state(draco_plan* plan, int32_t* words_host);
+
 #ifdef __cplusplus
 }
 #endif

@@ -53,7 +53,8 @@ EXPORTS = [
     "draco_plan_set_second_word", "draco_encode_node_wide",
 ]
 # the measuring instruments of include/draco_bench.h
-BENCH_EXPORTS = ["draco_copy_probe", "draco_plan_set_timing", "draco_plan_kernel_time", "draco_plan_kernel_times"]
+BENCH_EXPORTS = ["draco_copy_probe", "draco_plan_set_timing", "draco_plan_kernel_time", "draco_plan_kernel_times",
+                 "draco_plan_speculation_state"]
 
 
 def build(verbose: bool = False) -> str:
@@ -174,6 +175,8 @@ def lib() -> ctypes.CDLL:
     L.draco_plan_kernel_time.restype = i32
     L.draco_plan_kernel_times.argtypes = [vp, i32, vp, i32, ctypes.POINTER(i32)]
     L.draco_plan_kernel_times.restype = i32
+    L.draco_plan_speculation_state.argtypes = [vp, vp]
+    L.draco_plan_speculation_state.restype = i32
     L.draco_plan_last_projection_seed.argtypes = [vp, ctypes.POINTER(ctypes.c_uint64)]
     L.draco_plan_last_projection_seed.restype = i32
     L.draco_encode_oneshot.argtypes = [vp, i32, i32, i64, vp, i64, i64, vp, i64, vp]
@@ -415,6 +418,12 @@ class Plan:
         n = ctypes.c_int()
         _check(lib().draco_plan_kernel_times(self._h, kind, out.ctypes.data, capacity, ctypes.byref(n)))
         return out[:min(n.value, capacity)].copy()
+
+    def speculation_state(self) -> np.ndarray:
+        """The six words of draco_plan_speculation_state."""
+        out = np.zeros(6, dtype=np.int32)
+        _check(lib().draco_plan_speculation_state(self._h, out.ctypes.data))
+        return out
 
 
 def draco_copy_probe(src, dst, rows: int, row_len: int, ld: int, stream=None) -> None:

@@ -782,6 +782,13 @@ int draco_plan_set_timing(draco_plan* p, int max_records) {
     return DRACO_OK;
 }
 
+int draco_plan_speculation_state(draco_plan* p, int32_t* words_host) {
+    if (p == nullptr || words_host == nullptr || p->spec_dev == nullptr) return DRACO_EINVAL;
+    HIP_TRY(hipDeviceSynchronize());
+    HIP_TRY(hipMemcpy(words_host, p->spec_dev, kSpecWords * sizeof(int32_t), hipMemcpyDeviceToHost));
+    return DRACO_OK;
+}
+
 int draco_plan_kernel_time(draco_plan* p, int kind, double* total_ms, int* launches) {
     if (p == nullptr || kind < 0 || kind >= kKinds || total_ms == nullptr || launches == nullptr) return DRACO_EINVAL;
     Timer& t = p->timers[kind];

@@ -427,7 +427,7 @@ def test_cyc_speculative_single_pass_decode():
         ref.close()
 
 
-@pytest.mark.parametrize("d", [150_001, 600_001, 1_100_001])
+@pytest.mark.parametrize("d", [150_001, 400_001, 600_001, 1_100_001])
 @pytest.mark.parametrize("second", [False, "i8", "bf16", "f32"])
 def test_cyc_speculation_over_a_random_run_of_steps(second, d):
     """Twenty steps on one plan with the adversaries changing at random (none, some, enormous
