@@ -17,11 +17,6 @@ __device__ __forceinline__ int speculates_on(const CycSpec& spec) {
     return spec.state[kSpecClean] >= kCleanRun ? kSpecOnNobody : 0;
 }
 
-// The value that lane q (the same in every lane) holds.
-__device__ __forceinline__ double lane_value(double v, int q) {
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), q), __builtin_amdgcn_readlane(__double2loint(v), q));
-}
-
 // phi step 1: gamma'_j = sum_i f_i * r_j[i].  A lane owns K float4 (two complex numbers each) of
 // every row, keeps its slice of f in registers and has the next D rows in flight: a row's registers
 // are loaded again as soon as it is summed.  The 2 D fp64 sums of D rows are reduced over the

@@ -1,6 +1,8 @@
 // phi and the recombination vector on the device: the kernels around locate_device.hpp.
 #include "locate_device.hpp"
 
+#include <cmath>
+
 namespace draco {
 
 namespace {
@@ -47,28 +49,29 @@ __device__ __forceinline__ void load_projections(LocateSmem& sm, double2 (*part)
 
 }  // namespace
 
-// One kernel for the sample's locator and the last one, so that the second of a decode finds the code (50 KB)
+// One kernel for the sample's locator and the last one, so that the second of a decode finds the code
 // in the instruction cache (0.3 to 0.5 % of a step with a sample, little more than runs differ; the rest is its chain of
 // dependent steps, locate_device.hpp).
+// CH: chunks of 64 nodes.
+template <int CH>
 __global__ __launch_bounds__(kW * kSumWaves) void cyc_locate_kernel(
     const double2* __restrict__ sums, int tiles, const double2* __restrict__ roots, int P, int s, double tau,
-    const double2* __restrict__ b0, const CycSpec spec, const LocateOut out, int sample) {
+    double isq, const double2* __restrict__ b0, const CycSpec spec, const LocateOut out, int sample) {
     if (sample != 0 && !takes_sample(spec)) return;
     __shared__ LocateSmem sm;
     __shared__ double2 part[kSumWaves][kMaxNodes];
     load_projections(sm, part, sums, tiles, roots, P);
     if (threadIdx.x >= kW) return;
     const int lane = threadIdx.x;
-    const bool clean = locate_wave(sm, P, s, tau, b0, out, lane);
+    NodeSet<CH> flagged;
+    const bool clean = locate_wave<CH>(sm, P, s, tau, isq, b0, out, lane, flagged);
     if (sample == 0 && spec.state != nullptr) {
         // the flagged nodes are the ones speculated on
         const int now = spec.state[kSpecNow];
         bool same = now != 0;
-        for (int c = 0; c < P; c += kW) {
-            const int j = c + lane;
-            const unsigned long long found = __ballot(j < P && sm.mask[j] != 0);
-            const unsigned long long expected = now == kSpecOnSample ? spec.mask[c / kW] : 0ull;
-            same &= found == expected;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            if (c * kW < P) same &= flagged.word[c] == (now == kSpecOnSample ? spec.mask[c] : 0ull);
         }
         if (lane == 0) {
             spec.state[kSpecDone] = same ? 1 : 0;
@@ -91,12 +94,22 @@ __global__ __launch_bounds__(kW * kSumWaves) void cyc_locate_kernel(
     }
 }
 
+static void launch(int threads, const double2* sums, int tiles, const double2* roots, int P, int s, double tau,
+                   const double2* b0, const CycSpec& spec, const LocateOut& out, bool sample, hipStream_t stream) {
+    const double isq = 1.0 / std::sqrt((double)P);
+    auto go = [&](auto chunks) {
+        hipLaunchKernelGGL((cyc_locate_kernel<decltype(chunks)::value>), dim3(1), dim3(threads), 0, stream, sums, tiles, roots, P,
+                           s, tau, isq, b0, spec, out, sample ? 1 : 0);
+    };
+    if (P <= kW) go(std::integral_constant<int, 1>());
+    else go(std::integral_constant<int, kMaxNodes / kW>());
+}
+
 hipError_t launch_cyc_locate(const double2* sums, int64_t tiles, const double2* roots, int P, int s, double tau,
                              const double2* b0, uint64_t* mask_out, int32_t* status_out, double2* b_out,
                              int32_t* idx_out, int32_t* nu_out, const CycSpec& spec, hipStream_t stream) {
     const LocateOut out{mask_out, status_out, b_out, idx_out, nu_out, nullptr};
-    hipLaunchKernelGGL(cyc_locate_kernel, dim3(1), dim3(tiles > 0 ? kW * kSumWaves : kW), 0, stream, sums, (int)tiles, roots, P,
-                       s, tau, b0, spec, out, 0);
+    launch(tiles > 0 ? kW * kSumWaves : kW, sums, (int)tiles, roots, P, s, tau, b0, spec, out, false, stream);
     return hipGetLastError();
 }
 
@@ -104,8 +117,7 @@ hipError_t launch_cyc_locate_sample(const double2* partial, const double2* roots
                                     const double2* b0, double2* b_out, int32_t* idx_out, int32_t* nu_out,
                                     const CycSpec& spec, hipStream_t stream) {
     const LocateOut out{spec.mask, spec.state + kSpecStatus, b_out, idx_out, nu_out, spec.b};
-    hipLaunchKernelGGL(cyc_locate_kernel, dim3(1), dim3(kW * kSumWaves), 0, stream, partial, (int)kSampleTiles, roots, P, s, tau,
-                       b0, spec, out, 1);
+    launch(kW * kSumWaves, partial, (int)kSampleTiles, roots, P, s, tau, b0, spec, out, true, stream);
     return hipGetLastError();
 }
 

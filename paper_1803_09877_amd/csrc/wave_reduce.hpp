@@ -7,6 +7,10 @@
 namespace draco {
 namespace {
 
+// The value that lane q (the same in every lane) holds.
+__device__ __forceinline__ double lane_value(double v, int q) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), q), __builtin_amdgcn_readlane(__double2loint(v), q));
+}
 template <int CTRL>
 __device__ __forceinline__ double dpp_move(double v) {
     // every lane reads a lane of its own row of 16, so no previous value is kept (mov_dpp): one
@@ -58,6 +62,35 @@ __device__ __forceinline__ double group_sum(double v) {
     if constexpr (N >= 32) v = swap_add<16>(v, v);
     if constexpr (N >= 64) v = swap_add<32>(v, v);
     return v;
+}
+// The same for several values, a step of all of them before the next: one wavefront issues in order, and a step is three
+// dependent instructions.
+template <int N, int M>
+__device__ __forceinline__ void group_sums(double (&v)[M]) {
+    if constexpr (N >= 2) {
+#pragma unroll
+        for (int i = 0; i < M; ++i) v[i] += dpp_move<kDppXor1>(v[i]);
+    }
+    if constexpr (N >= 4) {
+#pragma unroll
+        for (int i = 0; i < M; ++i) v[i] += dpp_move<kDppXor2>(v[i]);
+    }
+    if constexpr (N >= 8) {
+#pragma unroll
+        for (int i = 0; i < M; ++i) v[i] += dpp_move<kDppHalfMirror>(v[i]);
+    }
+    if constexpr (N >= 16) {
+#pragma unroll
+        for (int i = 0; i < M; ++i) v[i] += dpp_move<kDppRor8>(v[i]);
+    }
+    if constexpr (N >= 32) {
+#pragma unroll
+        for (int i = 0; i < M; ++i) v[i] = swap_add<16>(v[i], v[i]);
+    }
+    if constexpr (N >= 64) {
+#pragma unroll
+        for (int i = 0; i < M; ++i) v[i] = swap_add<32>(v[i], v[i]);
+    }
 }
 template <int N>
 __device__ __forceinline__ double group_max(double v) {

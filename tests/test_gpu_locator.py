@@ -60,3 +60,41 @@ def test_located_sets_over_counts_and_placements(P, s):
                         assert np.linalg.norm(ug - uo) <= 1e-6 * np.linalg.norm(uo), what
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("P,s", [(9, 2), (45, 3), (45, 7), (65, 4), (24, 8)])
+def test_second_liar_around_the_thresholds(P, s):
+    """One lie the size of the messages and one whose syndromes are 0.05, 8, 300 and 10 000 times the zero threshold: a
+    column of the system that counts as dependent and accounts for everything, one that counts as dependent and does
+    not (the general form decides), and two beyond the 64-fold threshold.  Set and status equal the oracle's, which
+    knows the general form only."""
+    d = 96
+    w = synth.Workload(name="locator", code="cyc", P=P, s=s, d=d, sigma=1.0, attacks=(), placement="any",
+                       seed=synth.SEED_BASE + 77 * P + s)
+    c = Case(w, wide="f32")
+    rng = np.random.default_rng(P * 10 + s)
+    try:
+        c.encode()
+        f = c.f.cpu().numpy()
+        Z = c.Z[:, :c.mlen].double().cpu().numpy() + c.Zlo[:, :c.mlen].double().cpu().numpy()
+        rho = np.median(np.abs((Z[:, 0::2] + 1j * Z[:, 1::2]) @ f.astype(np.float64)))
+        for times in (0.05, 8.0, 300.0, 10_000.0):
+            a, b = rng.choice(P, size=2, replace=False).tolist()
+            c.receive()
+            R = Z.copy()
+            R[a] += rng.standard_normal(c.mlen) * np.sqrt(np.mean(Z[a] ** 2))
+            # in one coordinate: |h| = |f_0 delta| / sqrt(P)
+            R[b, 0] += times * o.TAU_H_WIDE * rho * np.sqrt(P) / abs(float(f[0]))
+            hi = R.astype(np.float32)
+            lo = (R - hi).astype(np.float32)
+            c.R[:, :c.mlen] = torch.from_numpy(hi).to(c.device)
+            c.Rlo[:, :c.mlen] = torch.from_numpy(lo).to(c.device)
+            uo, mo, so = o.decode_cyclic(hi.astype(np.float64) + lo, f, s, d, tau_h=o.TAU_H_WIDE)
+            assert mo[a] and mo[b] == (times > 1) and mo.sum() == 1 + (times > 1), (times, a, b, np.flatnonzero(mo))
+            mask, status = c.decode()
+            torch.cuda.synchronize()
+            assert status == so and np.array_equal(mask, mo), (times, a, b, np.flatnonzero(mo), np.flatnonzero(mask))
+            ug = c.u[:d].cpu().numpy().astype(np.float64)
+            assert np.linalg.norm(ug - uo) <= 1e-6 * np.linalg.norm(uo), (times, a, b)
+    finally:
+        c.close()
