@@ -25,7 +25,7 @@ SOURCES = [os.path.join(_HERE, "csrc", n) for n in (
     "locate.hip", "update.hip", "api.hip", "host_math.cpp")]
 HEADERS = [os.path.join(_HERE, "csrc", n) for n in (
     "kernels.hpp", "device_util.hpp", "cyc_encode_kernels.hpp", "cyc_encode_s.inc", "cyc_encode_narrow.hpp",
-    "cyc_encode_narrow_s.inc", "locate_device.hpp", "wave_reduce.hpp", "host_math.hpp", "projection_rng.hpp")] + [
+    "cyc_encode_narrow_s.inc", "locate_device.hpp", "recombine_device.hpp", "wave_reduce.hpp", "host_math.hpp", "projection_rng.hpp")] + [
     os.path.join(_ROOT, "include", "draco.h"), os.path.join(_ROOT, "include", "draco_bench.h")]
 BUILD_DIR = os.path.join(_HERE, "_build")
 

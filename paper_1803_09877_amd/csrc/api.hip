@@ -529,11 +529,13 @@ int decode_cyclic_async_impl(draco_plan* p, const float* hi_dev, const float* lo
     const int64_t d = paired_len(p), tiles = project_tiles(d, P, ld_m);
     const int fmt = lo_format(p);
     const double tau = tau_of(p, wide);
+    const bool inlined = tiles <= inline_tiles(P);
+    const int64_t message_bytes = P * message_len(p) * (wide ? wide_bytes(p) : 4);
     const uint64_t seed = f_dev == nullptr ? next_projection_seed(p) : 0;
-    CycSpec spec{p->speculation && project_speculates(d, P) ? p->spec_dev : nullptr, nullptr, nullptr};
+    CycSpec spec{p->speculation && !short_rows(d, P) ? p->spec_dev : nullptr, nullptr, nullptr};
     {
         Timed timed(p, kProject, st);
-        if (spec.state != nullptr && P * message_len(p) * (wide ? wide_bytes(p) : 4) >= kSampledMessages) {
+        if (spec.state != nullptr && message_bytes >= kSampledMessages) {
             spec.mask = p->spec_mask_dev;
             spec.b = p->spec_b_dev;
             HIP_TRY(launch_cyc_sample(hi_dev, lo, fmt, ld_m, f_dev, seed, p->sample_dev, spec, P, d, st));
@@ -542,13 +544,19 @@ int decode_cyclic_async_impl(draco_plan* p, const float* hi_dev, const float* lo
         }
         HIP_TRY(launch_cyc_project(hi_dev, lo, fmt, ld_m, f_dev, seed, p->partial_dev, p->b0_dev, sum_dev, unpacked(p),
                                    spec, P, d, st));
-        if (tiles > kInlineTiles) HIP_TRY(launch_cyc_reduce(p->partial_dev, p->gamma_dev, reduce_parts(tiles), P, tiles, st));
+        if (!inlined) HIP_TRY(launch_cyc_reduce(p->partial_dev, p->gamma_dev, reduce_parts(tiles), P, tiles, st));
+    }
+    const double2* const sums = inlined ? p->partial_dev : p->gamma_dev;
+    if (recombines_in_locator(P, d, message_bytes)) {
+        Timed timed(p, kRecombine, st);
+        HIP_TRY(launch_cyc_locate_recombine(sums, inlined ? tiles : reduce_parts(tiles), p->root_dev, P, p->s, tau, p->b0_dev,
+                                            mask_dev, status_dev, spec, hi_dev, lo, fmt, ld_m, sum_dev, unpacked(p), d, st));
+        return DRACO_OK;
     }
     {
         Timed timed(p, kLocateKind, st);
-        const bool inlined = tiles <= kInlineTiles;
         const int64_t left = inlined ? tiles : reduce_parts(tiles) > 1 ? reduce_parts(tiles) : 0;
-        HIP_TRY(launch_cyc_locate(inlined ? p->partial_dev : p->gamma_dev, left, p->root_dev, P, p->s, tau,
+        HIP_TRY(launch_cyc_locate(sums, left, p->root_dev, P, p->s, tau,
                                   p->b0_dev, mask_dev, status_dev, p->b_dev, p->idx_dev, p->idx_dev + P, spec, st));
     }
     {

@@ -3,6 +3,7 @@
 // used for calibration.
 #include "device_util.hpp"
 #include "projection_rng.hpp"
+#include "recombine_device.hpp"
 #include "wave_reduce.hpp"
 
 #include <algorithm>
@@ -361,12 +362,7 @@ __global__ __launch_bounds__(kBlock) void cyc_project_reduce_kernel(const double
     if (threadIdx.x == 0) sums[(int64_t)blockIdx.x * P + j] = sm[0];
 }
 
-// u = R_{.,U} b on packed complex messages, unpacked to reals: honest rows in
-// ascending node order, fp64 accumulation, one rounding to fp32.  Lane l of the wavefront holds the index and the
-// coefficient of the l-th honest row of 64 (a scalar load for each row would be waited for one by one, half of
-// the time on short rows).  UN rows in flight; no load is under a condition (cyc_project_body): with the last round's
-// under one, rows of no more than two rounds, a dozen nodes, had all of theirs there ((12, 2, 2 M), one word: 21.2 us,
-// 18.0 so).
+// u = R_{.,U} b on packed complex messages, unpacked to reals (recombine_device.hpp): 64 honest rows at a time.
 template <bool FULL, int LO, int UN, bool NT>
 __device__ __forceinline__ void cyc_recombine_body(const float* __restrict__ Rm, const float* __restrict__ Rlo,
                                                    int64_t ldm,
@@ -375,49 +371,13 @@ __device__ __forceinline__ void cyc_recombine_body(const float* __restrict__ Rm,
                                                    bool realout, int64_t d, int64_t c0) {
     const int nu = *nu_ptr;  // honest nodes; written by the locator (device) or copied in by the host path
     const int lane = threadIdx.x & 63;
-    const int64_t mlen = 2 * ((d + 1) / 2);
-    const int nin = FULL ? 4 : clamp4(mlen - c0);   // (all lanes stay: the others read their indices)
-    const int nout = FULL ? 4 : clamp4(d - c0);
-    double are0 = 0.0, aim0 = 0.0, are1 = 0.0, aim1 = 0.0;
+    const int nin = FULL ? 4 : clamp4(2 * ((d + 1) / 2) - c0);   // (all lanes stay: the others read their indices)
+    double sum[4] = {0.0, 0.0, 0.0, 0.0};
     for (int base = 0; base < nu; base += 64) {
         const int cnt = min(64, nu - base), mine = base + min(lane, cnt - 1);
-        const int my_row = idx[mine];
-        const double2 my_b = b[mine];
-        float4 x[UN];
-        lo_raw_t<LO> xl[LO != kLoNone ? UN : 1];
-        auto fetch = [&](int slot, int q) {
-            const int64_t off = (int64_t)__builtin_amdgcn_readlane(my_row, q) * ldm + c0;
-            x[slot] = ldx<FULL, NT>(Rm + off, nin);
-            if constexpr (LO != kLoNone) xl[slot] = ld_lo<FULL, LO, NT>(Rlo, off, nin);
-        };
-        auto use = [&](int slot, int q) {
-            const double br = lane_value(my_b.x, q), bi = lane_value(my_b.y, q);
-            const wire4 v = wire_value<LO>(x[slot], xl[LO != kLoNone ? slot : 0]);
-            cmac(br, bi, v.x, v.y, are0, aim0);
-            cmac(br, bi, v.z, v.w, are1, aim1);
-        };
-#pragma unroll
-        for (int i = 0; i < UN; ++i) fetch(i, min(i, cnt - 1));
-        int q = 0;
-        for (; q + UN < cnt; q += UN) {   // (behind the last row it is read again)
-#pragma unroll
-            for (int i = 0; i < UN; ++i) {
-                use(i, q + i);
-                fetch(i, min(q + UN + i, cnt - 1));
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < UN; ++i) {
-            if (q + i < cnt) use(i, q + i);
-        }
+        add_rows<FULL, LO, UN, NT>(Rm, Rlo, ldm, idx[mine], b[mine], cnt, c0, nin, sum);
     }
-    if (realout) {  // unpacked wire: the sum is the real part, one float per complex entry
-        const int64_t c = c0 / 2;
-        if (FULL || 2 * c < d) u[c] = (float)are0;
-        if (FULL || 2 * c + 2 < d) u[c + 1] = (float)are1;
-    } else {
-        stx<FULL>(u + c0, make_float4((float)are0, (float)aim0, (float)are1, (float)aim1), nout);
-    }
+    store_sum<FULL>(u, realout, d, c0, sum);
 }
 
 // If the projection pass speculated on the set that the locator found, the output already holds the
@@ -538,22 +498,12 @@ int64_t project_tiles(int64_t d, int P, int64_t ldm) {
     return t.whole + t.rest;
 }
 int64_t project_tiles_at_most(int64_t d, int P) { return std::max(project_tiles(d, P, 0), project_tiles(d, P, 4)); }
-// Nodes per workgroup: all of them, or groups of 8 where 4 KiB tiles alone leave CUs idle.
-static int project_rows(int64_t d, int P) {
-    return (d + 1) / 2 * 2 <= 255 * kBlock * 4 ? std::min(P, 8) : P;
+// Rows of fewer 4 KiB tiles than CUs are short: a workgroup takes 8 nodes of a tile, and nothing is speculated on.  Of 8 nodes
+// or fewer only those that the locator's kernel also recombines: beyond, a speculation that holds saves a launch there.
+bool short_rows(int64_t d, int P) {
+    return (d + 1) / 2 * 2 <= (P > 8 ? kShortTiles : kFusedTiles) * (kBlock * 4);
 }
-bool project_speculates(int64_t d, int P) { return project_rows(d, P) == P; }
 
-template <class F>
-static void with_format(const float* Rlo, int lo, F&& fn) {
-    if (Rlo == nullptr) fn(std::integral_constant<int, kLoNone>{});
-    else if (lo == kLoBf16) fn(std::integral_constant<int, kLoBf16>{});
-    else if (lo == kLoI8) fn(std::integral_constant<int, kLoI8>{});
-    else fn(std::integral_constant<int, kLoF32>{});
-}
-static int word_bytes(const float* Rlo, int lo) {
-    return Rlo == nullptr ? 4 : lo == kLoI8 ? 5 : lo == kLoBf16 ? 6 : 8;
-}
 
 hipError_t launch_cyc_project(const float* R, const float* Rlo, int lo, int64_t ldm, const float* f, uint64_t f_seed,
                               double2* partial, const double2* b0, float* u, bool realout, const CycSpec& spec, int P,
@@ -585,7 +535,7 @@ hipError_t launch_cyc_project(const float* R, const float* Rlo, int lo, int64_t 
             else if (K == 2) go(std::integral_constant<int, 2>{}, std::integral_constant<int, 2>{}, nt);
             else go(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{}, nt);
         };
-        if (!project_speculates(d, P)) {
+        if (short_rows(d, P)) {
             constexpr int rows = 8;   // (45, 3, 30 000) on the 5-byte wire: 18 us with all rows in one group, 9 in groups of 8
             const dim3 groups(grid.x, (unsigned)((P + rows - 1) / rows));
             if constexpr (LO == kLoI8 || LO == kLoBf16) {
@@ -646,7 +596,7 @@ hipError_t launch_cyc_recombine(const float* R, const float* Rlo, int lo, int64_
     // 32; two fp32 words, 45 nodes 20 000 floats 13 and 18, 250 000 25 and 21, 12 nodes 60 000 9.2 and 8.3; one word, 18
     // nodes 20 000 6.7 and 7.7.
     const int bytes = word_bytes(Rlo, lo);
-    const bool few = !project_speculates(d, P) && (bytes == 5 || bytes == 6 || (d <= 65536 && P >= 16));
+    const bool few = short_rows(d, P) && (bytes == 5 || bytes == 6 || (d <= 65536 && P >= 16));
     const bool stay = P * d * bytes <= kSmallMessages;   // see launch_cyc_project
     with_format(Rlo, lo, [&](auto fmt) {
         constexpr int LO = decltype(fmt)::value;
@@ -667,7 +617,7 @@ hipError_t launch_cyc_recombine(const float* R, const float* Rlo, int lo, int64_
         if (few)
             hipLaunchKernelGGL(cyc_recombine_few_kernel<LO>, dim3((unsigned)((d + 255) / 256)), block, 0, stream, R, Rlo, ldm, b,
                                idx, nu, u, realout ? 1 : 0, d);
-        else if (LO == kLoF32 && !project_speculates(d, P)) go(std::integral_constant<int, LO == kLoF32 ? 5 : UN>{}, std::false_type{}, lds);
+        else if (LO == kLoF32 && short_rows(d, P)) go(std::integral_constant<int, LO == kLoF32 ? 5 : UN>{}, std::false_type{}, lds);
         else if (stay) go(std::integral_constant<int, UN>{}, std::false_type{}, lds);
         else go(std::integral_constant<int, UN>{}, std::true_type{}, lds);
     });

@@ -9,6 +9,8 @@
 // footprint" below).
 #pragma once
 
+#include <type_traits>
+
 #include "kernels.hpp"
 
 namespace draco {
@@ -296,35 +298,35 @@ __device__ __forceinline__ int64_t whole_windows(int64_t len) { return len / kWi
 // First float this workgroup's wavefront 0 owns, and whether it owns window pieces.  Selects in 32 bits,
 // no branches: the kernel's arguments then arrive in one batch instead of three, which the kernels with one
 // workgroup per CU have nothing to hide behind ((P, s, d) = (9, 1, 25.6 M), repetition encoder 323 -> 314 us).
-__device__ __forceinline__ int64_t spread_base(int64_t len, bool& pieces, unsigned blocks) {
+__device__ __forceinline__ int64_t spread_base(int64_t len, bool& pieces, unsigned blocks, unsigned block) {
     const int windows = (int)((uint64_t)len / kWindow);
-    const int tile = (int)blockIdx.x - ((int)blocks - windows * (int)kTilesPerWindow);   // behind the contiguous ones
+    const int tile = (int)block - ((int)blocks - windows * (int)kTilesPerWindow);   // behind the contiguous ones
     pieces = tile >= 0;
     const int window = pieces ? tile / (int)kTilesPerWindow : windows;
-    const unsigned off = pieces ? (unsigned)tile % (unsigned)kTilesPerWindow * 256u : blockIdx.x * (kBlock * 4);
+    const unsigned off = pieces ? (unsigned)tile % (unsigned)kTilesPerWindow * 256u : block * (kBlock * 4);
     return (int64_t)window * kWindow + off;
 }
 // Column (float index within a row of len floats) of this lane's 4 floats; blocks: workgroups that share
 // the row.
 template <bool SPREAD>
-__device__ __forceinline__ int64_t lane_column(int64_t len, unsigned blocks = gridDim.x) {
+__device__ __forceinline__ int64_t lane_column(int64_t len, unsigned blocks = gridDim.x, unsigned block = blockIdx.x) {
     if constexpr (SPREAD) {
         bool pieces;
-        const int64_t base = spread_base(len, pieces, blocks);
+        const int64_t base = spread_base(len, pieces, blocks, block);
         return base + (int64_t)(threadIdx.x >> 6) * (pieces ? kWaveStride : 256) + (threadIdx.x & 63) * 4;
     } else {
-        return ((int64_t)blockIdx.x * kBlock + threadIdx.x) * 4;
+        return ((int64_t)block * kBlock + threadIdx.x) * 4;
     }
 }
 // True when every lane of the workgroup has its 4 floats inside [0, need), need <= len.
 template <bool SPREAD>
-__device__ __forceinline__ bool block_is_full(int64_t len, int64_t need) {
+__device__ __forceinline__ bool block_is_full(int64_t len, int64_t need, unsigned blocks = gridDim.x, unsigned block = blockIdx.x) {
     if constexpr (SPREAD) {
         bool pieces;
-        const int64_t base = spread_base(len, pieces, gridDim.x);
+        const int64_t base = spread_base(len, pieces, blocks, block);
         return base + 3 * (pieces ? kWaveStride : 256) + 256 <= need;
     } else {
-        return (int64_t)(blockIdx.x + 1) * (kBlock * 4) <= need;
+        return (int64_t)(block + 1) * (kBlock * 4) <= need;
     }
 }
 
@@ -367,6 +369,18 @@ __device__ __forceinline__ void cmul(double br, double bi, double x, double y, d
 
 inline unsigned grid_for(int64_t units_of_4_floats) {
     return (unsigned)((units_of_4_floats + kBlock - 1) / kBlock);
+}
+// Calls fn with the second word's format as a compile-time constant: none when there is no second slab, else the format
+// the caller named.
+template <class F>
+void with_format(const float* Rlo, int lo, F&& fn) {
+    if (Rlo == nullptr) fn(std::integral_constant<int, kLoNone>{});
+    else if (lo == kLoBf16) fn(std::integral_constant<int, kLoBf16>{});
+    else if (lo == kLoI8) fn(std::integral_constant<int, kLoI8>{});
+    else fn(std::integral_constant<int, kLoF32>{});
+}
+inline int word_bytes(const float* Rlo, int lo) {
+    return Rlo == nullptr ? 4 : lo == kLoI8 ? 5 : lo == kLoBf16 ? 6 : 8;
 }
 // Workgroups that cover a row of len floats with the footprint lane_column<SPREAD>() describes.
 template <bool SPREAD>

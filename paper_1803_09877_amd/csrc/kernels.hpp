@@ -94,7 +94,12 @@ struct CycSpec {
     double2* b;
 };
 constexpr int kSampleTiles = 64;      // of 1024 floats
-constexpr int kInlineTiles = 64;      // partial sums up to which the locator adds them itself
+constexpr int kShortTiles = 255;      // 4 KiB tiles of the longest rows that count as short,
+constexpr int kFusedTiles = 64;       // and of those that are located and recombined by one kernel: a workgroup per CU has 1 KiB each
+// Partial sums up to which the locator adds them itself; more of them take longer there than a launch (decodes with that
+// launch / without, us: 98 tiles of 8 nodes 17.3 / 14.6, 20 17.3 / 15.1, 45 20.0 / 19.2, 100 33.9 / 35.4; 127 of 20 17.4 / 15.9,
+// 45 21.0 / 20.9, 100 37.2 / 39.8).
+inline int64_t inline_tiles(int P) { return P <= 64 ? 128 : 64; }
 // Messages (both words, bytes) from which a decode may locate the adversaries on a sample first and
 // then project and recombine in ONE pass.  The sample and its locator take 15 to 30 us and the
 // joint pass 10 % more than a projection; the second pass they save runs at about 6.3 TB/s, so with
@@ -114,10 +119,10 @@ __device__ __forceinline__ bool takes_sample(const CycSpec& spec) {
 }
 
 // Number of workgroups (= rows of `partial`) the projection uses for gradient length d and row stride ldm, the most it
-// uses for any stride, and whether it can speculate there (short rows are split over the nodes: they cannot).
+// uses for any stride, and whether rows of d floats are short (the projection is split over the nodes and does not speculate).
 int64_t project_tiles(int64_t d, int P, int64_t ldm);
 int64_t project_tiles_at_most(int64_t d, int P);
-bool project_speculates(int64_t d, int P);
+bool short_rows(int64_t d, int P);
 // partial[tile][P] <- per-tile sums of f_i * R[j][i].  b0[P]: recombination vector for "no
 // adversary"; u: output written speculatively.
 // f == nullptr: the entries of f are generated from f_seed (projection_rng.hpp).
@@ -136,7 +141,7 @@ constexpr int kReduceParts = 8;
 inline int reduce_parts(int64_t tiles) { return tiles > 8 * kBlock ? kReduceParts : 1; }
 hipError_t launch_cyc_reduce(const double2* partial, double2* sums, int parts, int P, int64_t tiles, hipStream_t stream);
 // phi steps 2-4 and the recombination vector on the device (one wavefront, fp64; s <= kLocateMaxS):
-// gamma[P] (tiles == 0) or partial[tiles][P] (tiles <= kInlineTiles) -> mask words, status, and the
+// gamma[P] (tiles == 0) or partial[tiles][P] -> mask words, status, and the
 // honest nodes' (idx, b) compacted in ascending order with their count in *nu_out.
 // roots[k] = exp(2 pi i k / P), k < P.  tau: relative zero threshold for syndromes.  With no located
 // node the coefficients are copied from b0.  b is a function of the set of flagged nodes.
@@ -150,6 +155,20 @@ hipError_t launch_cyc_locate(const double2* sums, int64_t tiles, const double2* 
 hipError_t launch_cyc_locate_sample(const double2* partial, const double2* roots, int P, int s, double tau,
                                     const double2* b0, double2* b_out, int32_t* idx_out, int32_t* nu_out,
                                     const CycSpec& spec, hipStream_t stream);
+// Where the locator's kernel recombines too: rows that are one KiB per CU, and of at most 64 nodes (a locator's registers)
+// the rows that are not short (65 to 255 tiles: 17 us, 22 in one launch at (45, 3, 70 001), whose recombination
+// needs more wavefronts), in messages that stay in the memory-side cache.  Beyond, two workgroups per CU recombine up to 3 % slower
+// ((15, 2, 4 M) on the 6-byte wire: 119 and 121 us), and after a sample the locator alone finds its code in the instruction
+// cache ((45, 7, 6 M) on two fp32 words: a step of 962 us, 966 in one launch).
+inline bool one_chunk_per_cu(int64_t d) { return (d + 1) / 2 * 2 <= kFusedTiles * kBlock * 4; }
+inline bool recombines_in_locator(int P, int64_t d, int64_t message_bytes) {
+    return one_chunk_per_cu(d) || (P <= 64 && !short_rows(d, P) && message_bytes <= kSmallMessages);
+}
+// The locator on sums[tiles][P] and the recombination in one launch.
+hipError_t launch_cyc_locate_recombine(const double2* sums, int64_t tiles, const double2* roots, int P, int s, double tau,
+                                       const double2* b0, uint64_t* mask_out, int32_t* status_out, const CycSpec& spec,
+                                       const float* R, const float* Rlo, int lo, int64_t ldm, float* u, bool realout, int64_t d,
+                                       hipStream_t stream);
 // u <- unpack( sum_{q < *nu} b[q] * R[idx[q]] ); nu is read from device memory.  Nothing if
 // state[kSpecDone] is set (state may be nullptr).
 hipError_t launch_cyc_recombine(const float* R, const float* Rlo, int lo, int64_t ldm, const double2* b,

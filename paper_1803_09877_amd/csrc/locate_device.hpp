@@ -51,16 +51,24 @@ __device__ __forceinline__ void wave_sync() {
 // The same sizes, lane and node as far as the compiler can tell others: what a block derives from them it then computes
 // itself.  (Out of the loop over the passes it moves everything that does not change, the rare branches' shares too,
 // some 3000 cycles before the first sum.)
-__device__ __forceinline__ void only_here(int& P, int& s, int& lane) { asm volatile("" : "+s"(P), "+s"(s), "+v"(lane)); }
+__device__ __forceinline__ void only_here(int& P, int& s, int& lane) {
+    P = __builtin_amdgcn_readfirstlane(P);
+    s = __builtin_amdgcn_readfirstlane(s);
+    asm volatile("" : "+s"(P), "+s"(s), "+v"(lane));
+}
 __device__ __forceinline__ bool lane0_says(bool b) { return __builtin_amdgcn_readfirstlane(b ? 1 : 0) != 0; }
 
+// Several kernels locate, and b has to be the same from each: products and sums are fused here where they are written so and
+// nowhere else.
+#pragma clang fp contract(off)
+
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
-    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+    return make_double2(fma(-a.y, b.y, a.x * b.x), fma(a.y, b.x, a.x * b.y));
 }
 __device__ __forceinline__ double2 cconj(double2 a) { return make_double2(a.x, -a.y); }
 __device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
-__device__ __forceinline__ double cnorm2(double2 a) { return a.x * a.x + a.y * a.y; }
+__device__ __forceinline__ double cnorm2(double2 a) { return fma(a.y, a.y, a.x * a.x); }
 __device__ __forceinline__ double2 cscale(double2 a, double s) { return make_double2(a.x * s, a.y * s); }
 template <int N>
 __device__ __forceinline__ double2 group_sum_c(double2 a) {
@@ -144,15 +152,6 @@ struct NodeSet {
     }
 };
 
-// Where a located set goes.
-struct LocateOut {
-    uint64_t* mask;      // ceil(P/64) words
-    int32_t* status;
-    double2* b;          // honest nodes' coefficients, one behind the other
-    int32_t* idx;        // and their indices
-    int32_t* nu;         // how many
-    double2* dense;      // the coefficients by node (flagged ones untouched), or nullptr
-};
 
 template <class F, int... K>
 __device__ __forceinline__ void unroll_slots(F& f, int l, std::integer_sequence<int, K...>) {
@@ -207,6 +206,16 @@ __device__ __forceinline__ void recurrence_lds(LocateSmem& sm, int n, int P, int
         }
     }
 }
+
+// What the locator finds, in registers: the set and the status are the same in every lane, a lane holds the coefficients of
+// its nodes (the honest ones').
+template <int CH>
+struct Located {
+    NodeSet<CH> flagged;
+    int status;
+    double2 b[CH];
+    __device__ __forceinline__ bool clean() const { return flagged.count() == 0 && status == 0; }
+};
 
 // Orthonormal columns of length <= ROWS, at most kLocateMaxS (or 8 with ROWS = 16) of them: row r of
 // column i in lane r of lane group i % kGroups, register i / kGroups.
@@ -772,12 +781,13 @@ __device__ __forceinline__ double median_size2(LocateSmem& sm, const double (&sq
 }
 
 // Run by one wavefront (lane = 0 .. 63, all active) with sm.gam[0..P) and sm.root[0..P) filled; P <= 64 CH, isq =
-// 1 / sqrt(P).  flagged: the set found.  Returns whether the decode was clean: nobody flagged, status OK.
+// 1 / sqrt(P).
 template <int CH>
-__device__ __forceinline__ bool locate_wave(LocateSmem& sm, int P, int s, double tau, double isq,
-                                           const double2* __restrict__ b0, const LocateOut& out, int lane,
-                                           NodeSet<CH>& flagged) {
+__device__ __forceinline__ Located<CH> locate_wave(LocateSmem& sm, int P, int s, double tau, double isq,
+                                                  const double2* __restrict__ b0, int lane) {
     const int n = P - 2 * s;  // rows of C_L
+    Located<CH> out;
+    NodeSet<CH>& flagged = out.flagged;
     int status = 0;
 
     // A lane's nodes: j = lane, lane + 64, ...
@@ -911,45 +921,24 @@ __device__ __forceinline__ bool locate_wave(LocateSmem& sm, int P, int s, double
         Bv = s <= 8 ? solve_set<16, CH>(sm, flagged, P, s, n, isq, lane, nullptr)
                     : solve_set<32, CH>(sm, flagged, P, s, n, isq, lane, nullptr);
     }
-    // b_j = (1/sqrt P) (conj w^{(n-1) j} + sum_m conj w^{(n+m) j} Bv_m) on honest nodes, written
-    // one behind the other in ascending node order
-    double2 b[CH];
+    // b_j = (1/sqrt P) (conj w^{(n-1) j} + sum_m conj w^{(n+m) j} Bv_m) on honest nodes
 #pragma unroll
-    for (int c = 0; c < CH; ++c) b[c] = nv == 0 ? b_clean[c] : make_double2(0.0, 0.0);   // (the table the speculative pass used)
+    for (int c = 0; c < CH; ++c) out.b[c] = nv == 0 ? b_clean[c] : make_double2(0.0, 0.0);   // (the table the speculative pass used)
     if (nv > 0) {
         for (int m = 2 * s - 1; m >= 0; --m) {
             const double2 free_m = make_double2(lane_value(Bv.x, m), lane_value(Bv.y, m));
 #pragma unroll
-            for (int c = 0; c < CH; ++c) b[c] = cfma(cconj(root[c]), b[c], free_m);
+            for (int c = 0; c < CH; ++c) out.b[c] = cfma(cconj(root[c]), out.b[c], free_m);
         }
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
             const int j = c * kW + lane;
-            b[c] = cfma(cconj(root[c]), b[c], make_double2(1.0, 0.0));
-            if (j < P) b[c] = cscale(cmul(cconj(sm.root[mulmod(n - 1, j, P)]), b[c]), isq);
+            out.b[c] = cfma(cconj(root[c]), out.b[c], make_double2(1.0, 0.0));
+            if (j < P) out.b[c] = cscale(cmul(cconj(sm.root[mulmod(n - 1, j, P)]), out.b[c]), isq);
         }
     }
-    int nu = 0;
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        if (c * kW >= P) break;
-        const int j = c * kW + lane;
-        const bool honest = j < P && !flagged.has(c, lane);
-        const unsigned long long bal = __ballot(honest);
-        if (honest) {
-            const int pos = nu + __popcll(bal & ((1ull << lane) - 1ull));
-            out.idx[pos] = j;
-            out.b[pos] = b[c];
-            if (out.dense != nullptr) out.dense[j] = b[c];
-        }
-        if (lane == 0) out.mask[c] = flagged.word[c];
-        nu += __popcll(bal);
-    }
-    if (lane == 0) {
-        *out.nu = nu;
-        *out.status = status;
-    }
-    return nu == P && status == 0;
+    out.status = status;
+    return out;
 }
 
 }  // namespace
