@@ -209,10 +209,18 @@ def _check(status: int) -> None:
 def _stream_ptr(stream) -> int:
     if stream is None:
         import torch
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)   # 0.2 us; a Stream object takes 3 to make
+        if raw is not None and torch.cuda.is_initialized():
+            return raw(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
+
+
+def _lo_dtype(second_word: int):
+    import torch
+    return {SECOND_WORD_BF16: torch.bfloat16, SECOND_WORD_I8: torch.int8}.get(second_word, torch.float32)
 
 
 def _ptr_or_null(t):
@@ -223,8 +231,18 @@ def mask_words(P: int) -> int:
     return (P + 63) // 64
 
 
+def _mask_buffer(P: int):
+    """Zeroed mask words for the library to fill (a ctypes array: an array's address takes a microsecond to ask for)."""
+    return (ctypes.c_uint64 * mask_words(P))()
+
+
 def mask_to_bool(words: np.ndarray, P: int) -> np.ndarray:
-    return np.array([(int(words[j >> 6]) >> (j & 63)) & 1 for j in range(P)], dtype=bool)
+    w = np.ascontiguousarray(words if isinstance(words, np.ndarray) else np.array(words, dtype=np.uint64))
+    if w.dtype.itemsize != 8:
+        w = w.astype(np.uint64)
+    if 64 * w.size < P:
+        raise IndexError(f"{w.size} mask words for {P} nodes")
+    return np.unpackbits(w.view(np.uint8), bitorder="little", count=P).astype(bool)   # (little-endian hosts)
 
 
 def bool_to_mask(mask, P: int) -> np.ndarray:
@@ -307,18 +325,18 @@ class Plan:
                                        message.data_ptr(), _stream_ptr(stream)))
 
     def encode_node_wide(self, node: int, node_grads, hi, lo, stream=None) -> None:
-        want = {SECOND_WORD_BF16: "torch.bfloat16", SECOND_WORD_I8: "torch.int8"}.get(self._second_word, "torch.float32")
-        assert str(lo.dtype) == want, (lo.dtype, want)
+        want = _lo_dtype(self._second_word)
+        assert lo.dtype is want, (lo.dtype, want)
         _check(lib().draco_encode_node_wide(self._h, node, node_grads.data_ptr(), node_grads.stride(0), hi.data_ptr(),
                                             lo.data_ptr(), _stream_ptr(stream)))
 
     def decode_repetition(self, messages, out_sum, stream=None):
         """-> (mask bool[P], status); the sum is written to ``out_sum``."""
-        words = np.zeros(mask_words(self.P), dtype=np.uint64)
+        words = _mask_buffer(self.P)
         status = lib().draco_decode_repetition(self._h, messages.data_ptr(), messages.stride(0),
-                                               out_sum.data_ptr(), words.ctypes.data, _stream_ptr(stream))
+                                               out_sum.data_ptr(), words, _stream_ptr(stream))
         _check(status)
-        return mask_to_bool(words, self.P), status
+        return mask_to_bool(np.frombuffer(words, dtype=np.uint64), self.P), status
 
     def decode_repetition_async(self, messages, out_sum, mask_dev, status_dev, stream=None) -> None:
         _check(lib().draco_decode_repetition_async(self._h, messages.data_ptr(), messages.stride(0),
@@ -326,18 +344,18 @@ class Plan:
                                                    status_dev.data_ptr(), _stream_ptr(stream)))
 
     def decode_cyclic(self, messages, f, out_sum, stream=None):
-        words = np.zeros(mask_words(self.P), dtype=np.uint64)
+        words = _mask_buffer(self.P)
         status = lib().draco_decode_cyclic(self._h, messages.data_ptr(), messages.stride(0), _ptr_or_null(f),
-                                           out_sum.data_ptr(), words.ctypes.data, _stream_ptr(stream))
+                                           out_sum.data_ptr(), words, _stream_ptr(stream))
         _check(status)
-        return mask_to_bool(words, self.P), status
+        return mask_to_bool(np.frombuffer(words, dtype=np.uint64), self.P), status
 
     def decode_cyclic_hostphi(self, messages, f, out_sum, stream=None):
-        words = np.zeros(mask_words(self.P), dtype=np.uint64)
+        words = _mask_buffer(self.P)
         status = lib().draco_decode_cyclic_hostphi(self._h, messages.data_ptr(), messages.stride(0), _ptr_or_null(f),
-                                                   out_sum.data_ptr(), words.ctypes.data, _stream_ptr(stream))
+                                                   out_sum.data_ptr(), words, _stream_ptr(stream))
         _check(status)
-        return mask_to_bool(words, self.P), status
+        return mask_to_bool(np.frombuffer(words, dtype=np.uint64), self.P), status
 
     def decode_cyclic_async(self, messages, f, out_sum, mask_dev, status_dev, stream=None) -> None:
         _check(lib().draco_decode_cyclic_async(self._h, messages.data_ptr(), messages.stride(0), _ptr_or_null(f),
@@ -361,11 +379,11 @@ class Plan:
 
     def decode_cyclic_wide(self, hi, lo, f, out_sum, stream=None):
         self._check_lo(hi, lo)
-        words = np.zeros(mask_words(self.P), dtype=np.uint64)
+        words = _mask_buffer(self.P)
         status = lib().draco_decode_cyclic_wide(self._h, hi.data_ptr(), lo.data_ptr(), hi.stride(0), _ptr_or_null(f),
-                                                out_sum.data_ptr(), words.ctypes.data, _stream_ptr(stream))
+                                                out_sum.data_ptr(), words, _stream_ptr(stream))
         _check(status)
-        return mask_to_bool(words, self.P), status
+        return mask_to_bool(np.frombuffer(words, dtype=np.uint64), self.P), status
 
     def decode_cyclic_wide_async(self, hi, lo, f, out_sum, mask_dev, status_dev, stream=None) -> None:
         self._check_lo(hi, lo)
@@ -384,8 +402,8 @@ class Plan:
 
     def _check_lo(self, hi, lo) -> None:
         """The second slab has the first one's row stride in elements and the plan's element type."""
-        want = {SECOND_WORD_BF16: "torch.bfloat16", SECOND_WORD_I8: "torch.int8"}.get(self._second_word, "torch.float32")
-        assert hi.stride(0) == lo.stride(0) and str(lo.dtype) == want, (lo.dtype, want)
+        want = _lo_dtype(self._second_word)
+        assert hi.stride(0) == lo.stride(0) and lo.dtype is want, (lo.dtype, want)
 
     def set_projection_seed(self, seed: int) -> None:
         _check(lib().draco_plan_set_projection_seed(self._h, seed))
@@ -489,13 +507,13 @@ def decode_repetition(messages, P: int, s: int):
     import torch
     assert messages.shape[0] == P
     d = messages.shape[1]
-    words = np.zeros(mask_words(P), dtype=np.uint64)
+    words = _mask_buffer(P)
     with torch.cuda.device(messages.device):
         out = torch.empty(_row_stride(d), dtype=torch.float32, device=messages.device)
         status = lib().draco_decode_repetition_oneshot(messages.data_ptr(), messages.stride(0), P, s, d, out.data_ptr(),
-                                                       words.ctypes.data, _stream_ptr(None))
+                                                       words, _stream_ptr(None))
     _check(status)
-    return out[:d], mask_to_bool(words, P), status
+    return out[:d], mask_to_bool(np.frombuffer(words, dtype=np.uint64), P), status
 
 
 def decode_cyclic(messages, P: int, s: int, d: int):
@@ -503,10 +521,10 @@ def decode_cyclic(messages, P: int, s: int, d: int):
     drawn inside the library, afresh for every call."""
     import torch
     assert messages.shape[0] == P
-    words = np.zeros(mask_words(P), dtype=np.uint64)
+    words = _mask_buffer(P)
     with torch.cuda.device(messages.device):
         out = torch.empty(_row_stride(d), dtype=torch.float32, device=messages.device)
         status = lib().draco_decode_cyclic_oneshot(messages.data_ptr(), messages.stride(0), P, s, d, out.data_ptr(),
-                                                   words.ctypes.data, _stream_ptr(None))
+                                                   words, _stream_ptr(None))
     _check(status)
-    return out[:d], mask_to_bool(words, P), status
+    return out[:d], mask_to_bool(np.frombuffer(words, dtype=np.uint64), P), status

@@ -321,3 +321,16 @@ def test_thresholds_and_formats_agree_across_header_binding_and_oracle():
         mask, _, st = plan.cyclic_locate(g)
         omask, _, ost = o.phi_from_projection(g, s)
         assert st == ost and np.array_equal(mask, omask), factor
+
+
+@pytest.mark.parametrize("P", [1, 15, 63, 64, 65, 130, 256])
+def test_mask_words_unpack_to_nodes(P):
+    """Words of either sign, more of them than P needs and lists of them; too few are an error."""
+    mask = np.random.default_rng(P).random(P) < 0.4
+    mask[-1] = True
+    words = B.bool_to_mask(mask, P)
+    for w in (words, words.view(np.int64), np.concatenate([words, words]), [int(x) for x in words], np.repeat(words, 2)[::2]):
+        got = B.mask_to_bool(w, P)
+        assert got.dtype == bool and got.flags.writeable and np.array_equal(got, mask)
+    with pytest.raises(IndexError):
+        B.mask_to_bool(words[:-1], P)
