@@ -69,46 +69,62 @@ __global__ __launch_bounds__(kBlock) void encode_rep_kernel(const float* __restr
 
 // Any number of rows per group (also the one-node form with groups = 1, copies = 1, and
 // the B > P form where a group sums its r*(B/P) consecutive per-sample rows): rows are
-// added in ascending order, eight fetched at a time.
-template <bool FULL>
+// added in ascending order, the next UN of them in flight.
+template <bool FULL, int UN>
 __device__ __forceinline__ void encode_rep_generic_body(const float* __restrict__ G, int64_t ldg,
                                                         float* __restrict__ Z, int64_t ldm, int groups, int rows,
                                                         int copies, int64_t d, int64_t c0) {
-    constexpr int UN = 8;
     if (!FULL && c0 >= d) return;
     const int n = FULL ? 4 : clamp4(d - c0);
     {
         const int g = (int)blockIdx.y;   // one group per workgroup (grid.y = groups)
         if (g >= groups) return;
-        const float* src = G + (int64_t)g * rows * ldg + c0;
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int i0 = 0; i0 < rows; i0 += UN) {   // (the last round's loads are in flight together too)
-            float4 x[UN];
+        const float* src = G + (int64_t)g * rows * ldg + c0;   // the next row to fetch
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), x[UN];
+        auto fetch = [&](int i) {
+            x[i] = ldx<FULL>(src, n);
+            src += ldg;
+        };
+        auto add = [&](int i) {
+            acc.x += x[i].x;
+            acc.y += x[i].y;
+            acc.z += x[i].z;
+            acc.w += x[i].w;
+        };
 #pragma unroll
-            for (int i = 0; i < UN; ++i)
-                if (i0 + i < rows) x[i] = ldx<FULL>(src + (int64_t)(i0 + i) * ldg, n);
+        for (int i = 0; i < UN; ++i)
+            if (i < rows) fetch(i);
+        int left = rows;   // rows not added yet, the first UN of them in flight
+        for (; left >= 2 * UN; left -= UN) {   // no load under a condition: the compiler then waits for one row at a time
 #pragma unroll
             for (int i = 0; i < UN; ++i) {
-                if (i0 + i < rows) {
-                    acc.x += x[i].x;
-                    acc.y += x[i].y;
-                    acc.z += x[i].z;
-                    acc.w += x[i].w;
-                }
+                add(i);
+                fetch(i);
             }
         }
+#pragma unroll
+        for (int i = 0; i < UN; ++i) {
+            if (i < left) add(i);
+            if (i + UN < left) fetch(i);
+        }
+#pragma unroll
+        for (int i = 0; i < UN; ++i)
+            if (i + UN < left) add(i);
         float* dst = Z + (int64_t)g * copies * ldm + c0;
         for (int i = 0; i < copies; ++i) stx<FULL>(dst + (int64_t)i * ldm, acc, n);
     }
 }
 
-template <bool SPREAD>
+// Four rows in flight; eight where a launch leaves CUs idle.  Encoder in us, eight at a time / so: (45, 2, B = 180, 1 663 371)
+// 258 / 253, (45, 1, B = 180, 400 001) 62.6 / 59.3, (10, 2, B = 160, 200 000) 22.7 / 21.2; (10, 2, B = 160, 50 001), 98 workgroups,
+// 13.8 / 13.0 (with four 15.9).  One workgroup per CU, which suits r rows in and r out (below), loses 4 to 60 % here.
+template <bool SPREAD, int UN>
 __global__ __launch_bounds__(kBlock) void encode_rep_generic_kernel(const float* __restrict__ G, int64_t ldg,
                                                                     float* __restrict__ Z, int64_t ldm,
                                                                     int groups, int rows, int copies, int64_t d) {
     const int64_t c0 = lane_column<SPREAD>(d);
-    if (block_is_full<SPREAD>(d, d)) encode_rep_generic_body<true>(G, ldg, Z, ldm, groups, rows, copies, d, c0);
-    else encode_rep_generic_body<false>(G, ldg, Z, ldm, groups, rows, copies, d, c0);
+    if (block_is_full<SPREAD>(d, d)) encode_rep_generic_body<true, UN>(G, ldg, Z, ldm, groups, rows, copies, d, c0);
+    else encode_rep_generic_body<false, UN>(G, ldg, Z, ldm, groups, rows, copies, d, c0);
 }
 
 // Majority candidate among R bit patterns of one coordinate (the streaming vote of
@@ -418,15 +434,20 @@ bool on_lines(int64_t ldm) { return ldm % 32 == 0; }
 // Sums of `rows` rows per group, stored `copies` times (copies = 1: one row, its stride does not matter).
 void launch_generic(const float* G, int64_t ldg, float* Z, int64_t ldm, int groups, int rows, int copies, int per_cu,
                     int64_t d, hipStream_t stream) {
-    auto go = [&](auto spread) {
+    auto go = [&](auto spread, auto ahead) {
         constexpr bool SPREAD = decltype(spread)::value;
+        constexpr int UN = decltype(ahead)::value;
         const dim3 grid(grid_cols<SPREAD>(d), (unsigned)groups);
-        allow_large_lds<encode_rep_generic_kernel<SPREAD>>();
-        hipLaunchKernelGGL(encode_rep_generic_kernel<SPREAD>, grid, dim3(kBlock), throttle_lds(per_cu, 0, 0), stream, G, ldg, Z,
-                           ldm, groups, rows, copies, d);
+        allow_large_lds<encode_rep_generic_kernel<SPREAD, UN>>();
+        hipLaunchKernelGGL((encode_rep_generic_kernel<SPREAD, UN>), grid, dim3(kBlock), throttle_lds(per_cu, 0, 0), stream, G, ldg,
+                           Z, ldm, groups, rows, copies, d);
     };
-    if (on_lines(ldm)) go(std::true_type{});
-    else go(std::false_type{});
+    auto depth = [&](auto spread) {
+        if ((int64_t)grid_for((d + 3) / 4) * groups < 256) go(spread, std::integral_constant<int, 8>{});
+        else go(spread, std::integral_constant<int, 4>{});
+    };
+    if (on_lines(ldm)) depth(std::true_type{});
+    else depth(std::false_type{});
 }
 
 }  // namespace
@@ -439,13 +460,16 @@ void launch_groups(const float* G, int64_t ldg, float* Z, int64_t ldm, int P, in
     const unsigned tiles = grid_cols<SPREAD>(d);
     const dim3 block(kBlock);
     bool generic = false;
+    // Three copies: two workgroups per CU on the line grid ((45, 1, 11.2 M) 612 us, 631 with one), one off it (5 M + 1: 312, 323 with
+    // two).  Five copies: two, but for long launches off it ((45, 2, 1 663 371) 100 us, 103 with two; 500 001 32 and 31).
+    const int three = SPREAD ? 2 : 1, five = !SPREAD && (int64_t)tiles * groups >= 12000 ? 1 : 2;
 #define DRACO_LAUNCH(R, GU, BPC)                                                                                \
     {                                                                                                           \
         allow_large_lds<encode_rep_kernel<R, GU, SPREAD>>();                                                    \
         hipLaunchKernelGGL((encode_rep_kernel<R, GU, SPREAD>), dim3(tiles, (unsigned)((groups + GU - 1) / GU)), \
                            block, throttle_lds(BPC, 0, 0), stream, G, ldg, Z, ldm, groups, d);                  \
     }
-    DRACO_REP_DISPATCH(DRACO_LAUNCH, 8, 2, 1, 1, 2, 1, 1, 1)
+    DRACO_REP_DISPATCH(DRACO_LAUNCH, 8, 2, three, 1, five, 1, 1, 1)
 #undef DRACO_LAUNCH
     if (generic) launch_generic(G, ldg, Z, ldm, groups, r, r, 2, d, stream);
 }
