@@ -259,7 +259,8 @@ __global__ __launch_bounds__(kBlock) void cyc_project_burst_kernel(const float* 
 // the 5-byte wire the joint pass takes 885 us so and 955 with K * 4 KiB contiguously.  Rows off the line grid
 // are read contiguously all the same (windows: K * 4 KiB), because both ends of every piece are parts of lines that
 // another die reads too ((32, 4, 3 000 003) on the 6-byte wire: 134 us against 140).
-template <int LO, int K, int D, bool NT>
+// NT: streaming loads; NT_JOINT: in the joint pass.
+template <int LO, int K, int D, bool NT, bool NT_JOINT>
 __global__ __launch_bounds__(kBlock) void cyc_project_kernel(const float* __restrict__ Rm,
                                                              const float* __restrict__ Rlo, int64_t ldm,
                                                              const float* __restrict__ f, uint64_t f_seed,
@@ -286,7 +287,7 @@ __global__ __launch_bounds__(kBlock) void cyc_project_kernel(const float* __rest
     if (blockIdx.x < rest) {
         const int64_t unit = contiguous != 0 ? kBlock * 4 * K : kWindow, first = mlen / unit * unit;
         const int64_t c1[1] = {first + ((int64_t)blockIdx.x * kBlock + threadIdx.x) * 4};
-        if (b != nullptr) cyc_project_body<LO, 1, 8, NT, true, false>(Rm, Rlo, ldm, f, f_seed, b, flagged, u, realout != 0, c1, j0, j1, d, wsum);
+        if (b != nullptr) cyc_project_body<LO, 1, 8, NT_JOINT, true, false>(Rm, Rlo, ldm, f, f_seed, b, flagged, u, realout != 0, c1, j0, j1, d, wsum);
         else cyc_project_body<LO, 1, 8, NT, false, false>(Rm, Rlo, ldm, f, f_seed, b, flagged, u, false, c1, j0, j1, d, wsum);
     } else {
         constexpr unsigned per = kWindow / (kBlock * 4 * K);   // tiles per window
@@ -300,7 +301,7 @@ __global__ __launch_bounds__(kBlock) void cyc_project_kernel(const float* __rest
 #pragma unroll
             for (int k = 0; k < K; ++k) c[k] = ((int64_t)tile * K * kBlock + k * kBlock + threadIdx.x) * 4;
         }
-        if (b != nullptr) cyc_project_body<LO, K, D, NT, true, true>(Rm, Rlo, ldm, f, f_seed, b, flagged, u, realout != 0, c, j0, j1, d, wsum);
+        if (b != nullptr) cyc_project_body<LO, K, D, NT_JOINT, true, true>(Rm, Rlo, ldm, f, f_seed, b, flagged, u, realout != 0, c, j0, j1, d, wsum);
         else cyc_project_body<LO, K, D, NT, false, true>(Rm, Rlo, ldm, f, f_seed, b, flagged, u, false, c, j0, j1, d, wsum);
     }
     store_wave_sums(wsum, partial + (int64_t)blockIdx.x * P, j0, j1);
@@ -512,28 +513,29 @@ hipError_t launch_cyc_project(const float* R, const float* Rlo, int lo, int64_t 
     const bool contiguous = ldm % 32 != 0;
     const ProjectTiles t = tiles_of(d, P, contiguous);
     const dim3 grid((unsigned)(t.whole + t.rest));
-    // the second pass finds messages of this size in the memory-side cache (kernels.hpp)
-    const bool stay = P * d * word_bytes(Rlo, lo) <= kSmallMessages;
+    // A second pass finds messages of this size in the memory-side cache (kernels.hpp); a joint pass expects none.
+    const int64_t bytes = P * d * word_bytes(Rlo, lo);
+    const bool stay = bytes <= kSmallMessages, stay_joint = bytes <= kCachedMessages;
     with_format(Rlo, lo, [&](auto fmt) {
         constexpr int LO = decltype(fmt)::value;
-        auto go = [&](auto k, auto ahead, auto nt) {
+        auto go = [&](auto k, auto ahead, auto nt, auto nt_joint) {
             constexpr int N = decltype(k)::value, D = decltype(ahead)::value;
-            constexpr bool NT = decltype(nt)::value;
+            constexpr bool NT = decltype(nt)::value, NTJ = decltype(nt_joint)::value;
             constexpr size_t fixed = (kBlock / 64) * kMaxNodes * sizeof(double2);   // wsum
             // four pieces: two workgroups per CU ((15, 2, 4 M): 46 us, 49 unlimited)
             size_t lds = 0;
             if constexpr (N == 4) {
-                allow_large_lds<cyc_project_kernel<LO, N, D, NT>>(fixed);
+                allow_large_lds<cyc_project_kernel<LO, N, D, NT, NTJ>>(fixed);
                 lds = throttle_lds(2, fixed, 0);
             }
-            hipLaunchKernelGGL((cyc_project_kernel<LO, N, D, NT>), grid, dim3(kBlock), lds, stream, R, Rlo, ldm, f, f_seed,
+            hipLaunchKernelGGL((cyc_project_kernel<LO, N, D, NT, NTJ>), grid, dim3(kBlock), lds, stream, R, Rlo, ldm, f, f_seed,
                                partial, b0, u, realout ? 1 : 0, spec, P, (unsigned)t.rest, contiguous ? 1 : 0, d);
         };
         // rows in flight: two of K = 4 or 2 pieces (four gain nothing), four of one
-        auto shape = [&](auto nt) {
-            if (K == 4) go(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{}, nt);
-            else if (K == 2) go(std::integral_constant<int, 2>{}, std::integral_constant<int, 2>{}, nt);
-            else go(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{}, nt);
+        auto shape = [&](auto nt, auto nt_joint) {
+            if (K == 4) go(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{}, nt, nt_joint);
+            else if (K == 2) go(std::integral_constant<int, 2>{}, std::integral_constant<int, 2>{}, nt, nt_joint);
+            else go(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{}, nt, nt_joint);
         };
         if (short_rows(d, P)) {
             constexpr int rows = 8;   // (45, 3, 30 000) on the 5-byte wire: 18 us with all rows in one group, 9 in groups of 8
@@ -551,8 +553,9 @@ hipError_t launch_cyc_project(const float* R, const float* Rlo, int lo, int64_t 
             }
             return;
         }
-        if (stay) shape(std::false_type{});
-        else shape(std::true_type{});
+        if (stay_joint) shape(std::false_type{}, std::false_type{});
+        else if (stay) shape(std::false_type{}, std::true_type{});
+        else shape(std::true_type{}, std::true_type{});
     });
     return hipGetLastError();
 }

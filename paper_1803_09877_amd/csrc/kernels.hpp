@@ -18,6 +18,10 @@ constexpr int kVoteWords = kMaskWords + 1;   // and the vote's count of workgrou
 // Messages of a whole step (both words, bytes) up to which kernels count on the 256 MiB memory-side
 // cache: measured wins at 216 and 270 MB, losses at 450 MB and beyond.
 constexpr int64_t kSmallMessages = 320ll << 20;
+// Messages up to which the joint pass leaves its rows there as well.  It is the only pass if the speculation holds, and larger
+// messages that come from elsewhere stream faster: steps over states in turn / over the same messages again, plain loads 1:
+// 120 to 145 MB 0.94 to 1.02 / 1.01 to 1.10, 160 to 270 MB 0.94 to 1.00 / 0.97 to 1.02 ((45, 3, 1 200 001), 5 bytes: 193 -> 182 us).
+constexpr int64_t kCachedMessages = 144ll << 20;
 constexpr int kLocateMaxS = 16;       // largest s the on-device locator handles
 
 // Which kernel families spread a workgroup's wavefronts over a 128 KiB window of each row
