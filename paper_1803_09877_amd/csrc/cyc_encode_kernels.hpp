@@ -239,10 +239,11 @@ __global__ __launch_bounds__(kBlock, PER_CU) void encode_cyc_rounds_kernel(const
     else encode_cyc_rounds_body<S, NB, false, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, c0, head);
 }
 
-// The same encoder for rows too short to fill the chip.  There the walk down P rows is
+// The same encoder for short rows, up to 1.25 M floats (node_segment).  There the walk down P rows is
 // latency: a workgroup (4 KiB contiguous, neighbours on one die) takes only `seg`
 // nodes, blockIdx.y the segment, and the rows that neighbouring segments share (2s of them) come
-// from the caches; no LDS, so the registers alone bound the workgroups per CU.  The window's rows
+// from the die's L2; no LDS, so the registers alone bound the workgroups per CU.  The tiles of a segment run before the next
+// segment's: the chip streams few rows at a time.  The window's rows
 // and the first round are in flight together.  Same taps in the same order: identical bits.
 // Streaming stores: plain ones end the kernel sooner but leave the messages for the next kernel to
 // wait for (whole step unsplit, split with plain stores, split: (45, 3, 500 001) on the 5-byte wire 116,
@@ -319,7 +320,12 @@ __global__ __launch_bounds__(kBlock) void encode_cyc_small_kernel(const float* _
                                                                   float* __restrict__ Z, float* __restrict__ Zlo,
                                                                   int64_t ldm, const CycTaps tab, int P, int seg,
                                                                   int64_t d) {
-    const int64_t tile = xcd_tile();
+    // A segment of the launch has a whole number of workgroups per die (gridDim.x, a multiple of 8), so that all segments of a
+    // tile run on one die and find in its L2 the rows that they share; a die has tiles/8 neighbouring tiles, or one more.
+    const unsigned tiles = (unsigned)((2 * ((d + 1) / 2) + kBlock * 4 - 1) / (kBlock * 4));
+    const unsigned die = blockIdx.x % 8, at = blockIdx.x / 8, more = tiles % 8;
+    if (at >= tiles / 8 + (die < more ? 1 : 0)) return;
+    const int64_t tile = die * (tiles / 8) + min(die, more) + at;
     const int64_t c0 = (tile * kBlock + threadIdx.x) * 4;
     const int first = (int)blockIdx.y * seg, last = min(P, first + seg);
     if ((tile + 1) * (kBlock * 4) <= d)
