@@ -482,9 +482,13 @@ __global__ __launch_bounds__(kBlock) void copy_probe_kernel(const float* __restr
 // which live longer (more columns per lane share the sums over the wavefront).  Project and sample in us, K = 4, 2 and 1:
 // 45 rows of the 5-byte wire 25.6 M floats 926, 950 and 983; 1.9 M 99, 106 and 111; 1.2 M 70, 63 and 65; 500 000 35, 34
 // and 38; 15 rows of one word 4 M 46, 49 and 53; 2 M 29.4, 28.1 and 29.9; 500 000 16, 14.4 and 13.6.
+// But one where the wider lanes' last workgroups leave that many more of the CUs idle: decodes over states in turn, K = 2 and
+// 1, (45, 3) on the 5-byte wire 1 200 001, 586 workgroups and 1172, 63.6 and 60.2 us, 600 001, 293 and 586, 40.2 and 38.9.
 static int project_width(int64_t d, int P) {
     const int64_t nvec = ((d + 1) / 2 + 1) / 2;
-    return nvec >= (P >= 24 ? 440 : 880) * kBlock * 4 ? 4 : nvec >= 240 * kBlock * 2 ? 2 : 1;
+    const int wide = nvec >= (P >= 24 ? 440 : 880) * kBlock * 4 ? 4 : nvec >= 240 * kBlock * 2 ? 2 : 1;
+    auto turns = [&](int k) { return (nvec + 256ll * kBlock * k - 1) / (256ll * kBlock * k) * k; };   // of one float4 per lane
+    return 5 * turns(wide) >= 6 * turns(1) ? 1 : wide;
 }
 // Tiles of whole windows, and of 4 KiB contiguously for the rest of a row (see cyc_project_kernel).
 struct ProjectTiles {
