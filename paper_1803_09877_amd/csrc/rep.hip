@@ -207,6 +207,17 @@ __global__ __launch_bounds__(64) void decode_rep_finish_kernel(const VoteOut out
 // the last workgroup to do so finishes the vote; a kernel of its own for that costs 4 us, an eighth of
 // the smallest step ((P, s, d) = (15, 1, 10 000): 32 us against 33).  A large launch cannot: the count
 // is one address and takes about 40 ns a workgroup, so 11 000 of them would need 440 us.
+//
+// A liar is mostly seen by every workgroup, and those of the first turn end within a microsecond of each
+// other: all saw the bit unset, and 500 to 1000 ORs of one address, 9 ns each, stood at its end.  So one
+// workgroup in sixteen of each die sets its bits at once and the others look up to three more times, 0.4 us
+// apart, before they do.  A bit that no other workgroup sets costs its own workgroup 3 us, and only that one.  One liar, before
+// and after: (6, 1, 600 000) 14.8 -> 10.5 us, (10, 2, 1.1 M) 21.3 -> 15.0, (10, 2, 5 M) 46.2 -> 39.1, (45, 1, 600 000) 29.4
+// -> 28.1, (45, 1, 11.2 M) 315 both; no liar the same.  One in eight, 0.2 us apart: 1.5 % behind; one in thirty-two, 0.6 us: the same.  A look
+// at the start of the walk, to spare the one at its end, costs calls without a liar 2 to 7 %.
+constexpr unsigned kVoteLeaders = 16;
+constexpr int kVoteLooks = 3;
+constexpr int kVoteNap = 16;      // s_sleep units of 64 clocks
 template <bool FINISH>
 __device__ __forceinline__ void publish_flags(const WaveFlags& wf, const VoteOut& out) {
     __shared__ unsigned long long sflags[kMaskWords];
@@ -224,8 +235,15 @@ __device__ __forceinline__ void publish_flags(const WaveFlags& wf, const VoteOut
         const unsigned long long mine = sflags[w];
         if (mine) {
             // (few workgroups: no look first, which would be a round trip of its own: (15, 1, 10 000) vote 7.6 us, 8.2 with)
-            const unsigned long long cur =
+            unsigned long long cur =
                 FINISH ? 0ull : __hip_atomic_load(flags + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if constexpr (!FINISH) {
+                const bool waits = (blockIdx.x >> 3) % kVoteLeaders != 0;   // (workgroup b runs on die b mod 8)
+                for (int look = 0; waits && (mine & ~cur) && look < kVoteLooks; ++look) {
+                    __builtin_amdgcn_s_sleep(kVoteNap);
+                    cur = __hip_atomic_load(flags + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            }
             if (mine & ~cur) (void)__hip_atomic_fetch_or(flags + w, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     };
