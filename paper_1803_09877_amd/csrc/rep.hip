@@ -449,6 +449,11 @@ namespace {
 // Which footprint the encoders take: see encode_rep_kernel.
 bool on_lines(int64_t ldm) { return ldm % 32 == 0; }
 
+// With two workgroups per CU, 513 to 768 of them would be one full turn and one nearly empty: four per CU make it one.  Sums over more
+// than r rows: (28, 3, 135 681), two samples a node, 12.1 -> 10.4 us, (15, 2, 180 907), sixteen, 41.4 -> 35.6; from 900 workgroups on
+// four are 0 to 6 % behind.  Three copies: (6, 1, 767 936) 8.2 -> 7.2 us; five copies have no such step (four: 4 to 9 % behind).
+bool spills_two_per_cu(int64_t workgroups) { return workgroups > 512 && workgroups <= 768; }
+
 // Sums of `rows` rows per group, stored `copies` times (copies = 1: one row, its stride does not matter).
 void launch_generic(const float* G, int64_t ldg, float* Z, int64_t ldm, int groups, int rows, int copies, int per_cu,
                     int64_t d, hipStream_t stream) {
@@ -456,6 +461,7 @@ void launch_generic(const float* G, int64_t ldg, float* Z, int64_t ldm, int grou
         constexpr bool SPREAD = decltype(spread)::value;
         constexpr int UN = decltype(ahead)::value;
         const dim3 grid(grid_cols<SPREAD>(d), (unsigned)groups);
+        if (per_cu == 2 && spills_two_per_cu((int64_t)grid.x * grid.y)) per_cu = 4;
         allow_large_lds<encode_rep_generic_kernel<SPREAD, UN>>();
         hipLaunchKernelGGL((encode_rep_generic_kernel<SPREAD, UN>), grid, dim3(kBlock), throttle_lds(per_cu, 0, 0), stream, G, ldg,
                            Z, ldm, groups, rows, copies, d);
@@ -480,14 +486,20 @@ void launch_groups(const float* G, int64_t ldg, float* Z, int64_t ldm, int P, in
     bool generic = false;
     // Three copies: two workgroups per CU on the line grid ((45, 1, 11.2 M) 612 us, 631 with one), one off it (5 M + 1: 312, 323 with
     // two).  Five copies: two, but for long launches off it ((45, 2, 1 663 371) 100 us, 103 with two; 500 001 32 and 31).
-    const int three = SPREAD ? 2 : 1, five = !SPREAD && (int64_t)tiles * groups >= 12000 ? 1 : 2;
+    // Seven copies and more: one; but seven and nine two in launches of a few turns, whose last one is a large part ((42, 3, 85 334)
+    // 7.2 -> 6.3 us, (42, 3, 170 667) 12.6 -> 12.1, (45, 4, 161 793) 13.1 -> 12.4; in more workgroups the same or 1 to 4 %
+    // behind, nine copies in less than two turns 2 %, eleven and more 1 to 4 % at any length).
+    const int64_t all = (int64_t)tiles * groups;
+    const int three = spills_two_per_cu((int64_t)tiles * ((groups + 1) / 2)) ? 4 : SPREAD ? 2 : 1;
+    const int five = !SPREAD && all >= 12000 ? 1 : 2;
+    const int seven = all > 256 && all <= 1280 ? 2 : 1, more = s == 4 && all > 512 && all <= 1536 ? 2 : 1;
 #define DRACO_LAUNCH(R, GU, BPC)                                                                                \
     {                                                                                                           \
         allow_large_lds<encode_rep_kernel<R, GU, SPREAD>>();                                                    \
         hipLaunchKernelGGL((encode_rep_kernel<R, GU, SPREAD>), dim3(tiles, (unsigned)((groups + GU - 1) / GU)), \
                            block, throttle_lds(BPC, 0, 0), stream, G, ldg, Z, ldm, groups, d);                  \
     }
-    DRACO_REP_DISPATCH(DRACO_LAUNCH, 8, 2, three, 1, five, 1, 1, 1)
+    DRACO_REP_DISPATCH(DRACO_LAUNCH, 8, 2, three, 1, five, 1, seven, more)
 #undef DRACO_LAUNCH
     if (generic) launch_generic(G, ldg, Z, ldm, groups, r, r, 2, d, stream);
 }
