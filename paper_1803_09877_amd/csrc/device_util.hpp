@@ -337,9 +337,9 @@ __device__ __forceinline__ bool block_is_full(int64_t len, int64_t need, unsigne
 // the contiguous one a single run: there the encoders and the projection own 4 KiB contiguously.
 //
 // Neighbours on one die (workgroup b runs on accelerator die b mod 8; tile xcd_tile() gives each die one
-// contiguous range of tiles) share such lines in its L2.  That helps where all workgroups of a launch are resident, as in
-// the kernels for short rows, and with several rows of loads for one of stores (B a multiple of 4P); in longer launches for
-// B = P it gains at some lengths and loses as much at others.  (Time alone says that shared lines are the cause; no run of
+// contiguous range of tiles) share such lines in its L2.  That helps where all workgroups of a launch are resident (the
+// encoder for short rows has its own mapping, a launch that gives every die as many tiles), and with several rows of loads for
+// one of stores (B a multiple of 4P); in longer launches for B = P it gains at some lengths and loses as much at others.  (Time alone says that shared lines are the cause; no run of
 // the byte counters has compared the two footprints.)
 __device__ __forceinline__ int64_t xcd_tile(unsigned blocks = gridDim.x) {
     const int64_t per = blocks / 8, b = blockIdx.x;
