@@ -237,12 +237,13 @@ def _mask_buffer(P: int):
 
 
 def mask_to_bool(words: np.ndarray, P: int) -> np.ndarray:
-    w = np.ascontiguousarray(words if isinstance(words, np.ndarray) else np.array(words, dtype=np.uint64))
-    if w.dtype.itemsize != 8:
-        w = w.astype(np.uint64)
-    if 64 * w.size < P:
-        raise IndexError(f"{w.size} mask words for {P} nodes")
-    return np.unpackbits(w.view(np.uint8), bitorder="little", count=P).astype(bool)   # (little-endian hosts)
+    if not (isinstance(words, np.ndarray) and words.ndim == 1 and words.dtype.kind in "ui" and words.dtype.itemsize == 8 and
+            words.dtype.isnative):   # lists, tensors on a device, other types: word by word, 0.2 us a node and more
+        return np.array([(int(words[j >> 6]) >> (j & 63)) & 1 for j in range(P)], dtype=bool)
+    if 64 * words.size < P:
+        raise IndexError(f"{words.size} mask words for {P} nodes")
+    bits = np.unpackbits(np.ascontiguousarray(words).view(np.uint8), bitorder="little", count=P)   # (little-endian hosts)
+    return bits.astype(bool)
 
 
 def bool_to_mask(mask, P: int) -> np.ndarray:

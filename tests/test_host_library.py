@@ -334,3 +334,26 @@ def test_mask_words_unpack_to_nodes(P):
         assert got.dtype == bool and got.flags.writeable and np.array_equal(got, mask)
     with pytest.raises(IndexError):
         B.mask_to_bool(words[:-1], P)
+
+
+def test_mask_words_of_any_kind_unpack_as_whole_numbers():
+    """What an indexing loop over the words takes: lists with negative numbers (an int64 mask with node 63 set), a tensor's
+    words read one by one (a device tensor is no array), arrays of other types and byte orders."""
+    P = 130
+    mask = np.random.default_rng(7).random(P) < 0.4
+    mask[[0, 63, 127]] = True
+    words = B.bool_to_mask(mask, P)
+
+    class Indexable:
+        def __getitem__(self, i):
+            return int(words[i])
+
+        def __array__(self, *args, **kwargs):
+            raise TypeError("no array")
+
+    small = np.array([True, False, True] + [False] * 50)
+    for w, want in ((words.view(np.int64).tolist(), mask), (Indexable(), mask), (words.astype(object), mask),
+                    (words.astype(words.dtype.newbyteorder()), mask), ([5.0], small), (np.array([5.0]), small),
+                    (np.array([5], dtype=np.int32), small), (torch.from_numpy(words.view(np.int64).copy()), mask)):
+        got = B.mask_to_bool(w, len(want))
+        assert got.dtype == bool and np.array_equal(got, want), w
