@@ -249,7 +249,7 @@ __global__ __launch_bounds__(kBlock, 2) void cyc_locate_walk_kernel(
     __shared__ double2 part[kBlock / kW][kMaxNodes];
     __shared__ double2 b[kW];
     __shared__ int idx[kW];
-    __shared__ int honest_rows;   // 0: nothing left to do
+    __shared__ int honest_rows;   // -1: the output holds their sum already
     const int lane = threadIdx.x % kW;
     load_projections<kBlock / kW>(sm, part, sums, tiles, roots, P);
     if (threadIdx.x < kW) {
@@ -262,7 +262,7 @@ __global__ __launch_bounds__(kBlock, 2) void cyc_locate_walk_kernel(
             b[pos] = found.b[0];
         }
         const bool done = spec.state != nullptr && holds_speculation(spec, found, P);
-        if (lane == 0) honest_rows = done ? 0 : __popcll(bal);
+        if (lane == 0) honest_rows = done ? -1 : __popcll(bal);
         if (blockIdx.x == 0) {
             if (lane == 0) {
                 mask[0] = found.flagged.word[0];
@@ -273,7 +273,13 @@ __global__ __launch_bounds__(kBlock, 2) void cyc_locate_walk_kernel(
     }
     __syncthreads();
     const int cnt = __builtin_amdgcn_readfirstlane(honest_rows);
-    if (cnt == 0) return;
+    if (cnt < 0) return;
+    if (cnt == 0) {   // every message is broken: a sum of nothing
+        const double none[4] = {0.0, 0.0, 0.0, 0.0};
+        for (unsigned block = blockIdx.x; block < blocks; block += gridDim.x)
+            store_sum<false>(u, realout != 0, d, lane_column<kSpreadRecombine>(d, blocks, block), none);
+        return;
+    }
     const int mine = min(lane, cnt - 1), my_row = idx[mine];
     const double2 my_b = b[mine];
     for (unsigned block = blockIdx.x; block < blocks; block += gridDim.x) {
