@@ -137,7 +137,7 @@ __global__ __launch_bounds__(kW * kSumWaves) void cyc_locate_kernel(
 
 // The locator and the recombination of short rows in one launch (a launch behind another is 4 us): every
 // workgroup runs the locator for itself, with its first rows already in flight, and adds its columns with the coefficients
-// out of LDS.  A workgroup owns 1 KiB of the rows at a time, its eight wavefronts take every eighth row, kAhead in flight,
+// out of LDS.  A workgroup owns 1 KiB of the rows, its eight wavefronts take every eighth row, kAhead in flight,
 // and their sums are added in order.  Decodes in us, two launches and one: (45, 3, 30 000) on the 5-byte wire, nobody and
 // three lie, 13.9 / 11.6 and 17.3 / 14.8, (20, 4, 10 001) 13.8 / 11.0 and 15.8 / 14.3, (45, 7, 65 000) on the 6-byte one 18.6 /
 // 14.2 and 26.9 / 23.3.  Beyond 64 tiles, more KiB than CUs, it gains nothing ((45, 3, 180 000): 24.5 and 24.6 us).
@@ -182,14 +182,13 @@ __global__ __launch_bounds__(kW * kSumWaves) void cyc_locate_recombine_kernel(
     __shared__ double2 b[kMaxNodes];
     __shared__ uint64_t flagged[kMaskWords];
     const int lane = threadIdx.x % kW, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kW);
-    const int64_t mlen = 2 * ((d + 1) / 2), chunks = (d + kW * 4 - 1) / (kW * 4);
+    const int64_t mlen = 2 * ((d + 1) / 2), c0 = ((int64_t)blockIdx.x * kW + lane) * 4;
     ShortRows<LO> rows;
-    auto fetch = [&](int64_t chunk, int first) {
-        const int64_t c0 = (chunk * kW + lane) * 4;
-        if ((chunk + 1) * (kW * 4) <= d) rows.template load<true>(Rm, Rlo, ldm, c0, 4, first, P);
+    auto fetch = [&](int first) {
+        if ((int64_t)(blockIdx.x + 1) * (kW * 4) <= d) rows.template load<true>(Rm, Rlo, ldm, c0, 4, first, P);
         else rows.template load<false>(Rm, Rlo, ldm, c0, clamp4(mlen - c0), first, P);
     };
-    if constexpr (CH == 1) fetch(blockIdx.x, wave);   // (four chunks leave no registers for them)
+    if constexpr (CH == 1) fetch(wave);   // (four chunks leave no registers for them)
     load_projections<kSumWaves>(sm, part.tile_sums, sums, tiles, roots, P);
     if (wave == 0) {
         const Located<CH> found = locate_wave<CH>(sm, P, s, tau, isq, b0, lane);
@@ -202,37 +201,23 @@ __global__ __launch_bounds__(kW * kSumWaves) void cyc_locate_recombine_kernel(
         if (lane == 0 && blockIdx.x == 0) *status = found.status;
     }
     __syncthreads();
-    if constexpr (CH != 1) fetch(blockIdx.x, wave);
-    for (int64_t chunk = blockIdx.x;;) {
-        double sum[4] = {0.0, 0.0, 0.0, 0.0};
-        rows.add(b, flagged, wave, P, sum);
-        for (int first = wave + kAhead * kSumWaves; first < P; first += kAhead * kSumWaves) {
-            fetch(chunk, first);
-            rows.add(b, flagged, first, P, sum);
-        }
-        const int64_t c0 = (chunk * kW + lane) * 4, next = chunk + gridDim.x;
-        if (next < chunks) fetch(next, wave);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) part.row_sums[wave][i][lane] = sum[i];
-        __syncthreads();
-        if (wave == 0) {
-#pragma unroll
-            for (int w = 1; w < kSumWaves; ++w) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) sum[i] += part.row_sums[w][i][lane];
-            }
-            if (realout != 0) {
-                const int64_t c = c0 / 2;
-                if (2 * c < d) u[c] = (float)sum[0];
-                if (2 * c + 2 < d) u[c + 1] = (float)sum[2];
-            } else {
-                stx<false>(u + c0, make_float4((float)sum[0], (float)sum[1], (float)sum[2], (float)sum[3]), clamp4(d - c0));
-            }
-        }
-        if (next >= chunks) break;
-        __syncthreads();   // (row_sums are read out)
-        chunk = next;
+    if constexpr (CH != 1) fetch(wave);
+    double sum[4] = {0.0, 0.0, 0.0, 0.0};
+    rows.add(b, flagged, wave, P, sum);
+    for (int first = wave + kAhead * kSumWaves; first < P; first += kAhead * kSumWaves) {
+        fetch(first);
+        rows.add(b, flagged, first, P, sum);
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) part.row_sums[wave][i][lane] = sum[i];
+    __syncthreads();
+    if (wave != 0) return;
+#pragma unroll
+    for (int w = 1; w < kSumWaves; ++w) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum[i] += part.row_sums[w][i][lane];
+    }
+    store_sum<false>(u, realout != 0, d, c0, sum);
 }
 
 // The same for longer rows of messages that stay in the memory-side cache: every workgroup runs the locator, and if the output
