@@ -69,62 +69,78 @@ __global__ __launch_bounds__(kBlock) void encode_rep_kernel(const float* __restr
 
 // Any number of rows per group (also the one-node form with groups = 1, copies = 1, and
 // the B > P form where a group sums its r*(B/P) consecutive per-sample rows): rows are
-// added in ascending order, the next UN of them in flight.
-template <bool FULL, int UN>
+// added in ascending order, UN at a time.  The first HEAD of them, 1 to UN, make the others whole rounds: their number is known
+// where the loads are issued, since a load under a condition makes the compiler wait for everything before each sum (one
+// node's message of 15 rows, 168 113 floats: 6.5 us so, 4.0 now; (30, 1, B = 60, 909 408) 59.4 and 51.8).
+template <bool FULL, int UN, int HEAD>
+__device__ __forceinline__ float4 sum_rows(const float* __restrict__ src, int64_t ldg, int rows, int n) {
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), head[HEAD], x[UN];
+    auto fetch = [&](auto& row) {
+#pragma unroll
+        for (auto& v : row) {
+            v = ldx<FULL>(src, n);
+            src += ldg;
+        }
+    };
+    auto add = [&](const float4& v) {
+        acc.x += v.x;
+        acc.y += v.y;
+        acc.z += v.z;
+        acc.w += v.w;
+    };
+    // a round is added and the next one fetched, row by row
+    auto rounds = [&](auto& row, int left) {
+        for (; left > UN; left -= UN) {
+            // Four rows are waited for together: (15, 2, B = 240, 180 907) 36.1 us, 37.9 one by one, long launches the same.
+            if constexpr (UN == 4) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+            for (auto& v : row) {
+                add(v);
+                v = ldx<FULL>(src, n);
+                src += ldg;
+            }
+        }
+#pragma unroll
+        for (auto& v : row) add(v);
+    };
+    fetch(head);
+    if constexpr (UN == 4 && HEAD == UN) {   // whole rounds of four as they are: eight in flight at first cost 1 to 4 %
+        rounds(head, rows);
+    } else if (rows == HEAD) {
+#pragma unroll
+        for (auto& v : head) add(v);
+    } else {
+        fetch(x);
+#pragma unroll
+        for (auto& v : head) add(v);
+        rounds(x, rows - HEAD);
+    }
+    return acc;
+}
+template <bool FULL, int UN, int HEAD>
 __device__ __forceinline__ void encode_rep_generic_body(const float* __restrict__ G, int64_t ldg,
                                                         float* __restrict__ Z, int64_t ldm, int groups, int rows,
                                                         int copies, int64_t d, int64_t c0) {
     if (!FULL && c0 >= d) return;
     const int n = FULL ? 4 : clamp4(d - c0);
-    {
-        const int g = (int)blockIdx.y;   // one group per workgroup (grid.y = groups)
-        if (g >= groups) return;
-        const float* src = G + (int64_t)g * rows * ldg + c0;   // the next row to fetch
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), x[UN];
-        auto fetch = [&](int i) {
-            x[i] = ldx<FULL>(src, n);
-            src += ldg;
-        };
-        auto add = [&](int i) {
-            acc.x += x[i].x;
-            acc.y += x[i].y;
-            acc.z += x[i].z;
-            acc.w += x[i].w;
-        };
-#pragma unroll
-        for (int i = 0; i < UN; ++i)
-            if (i < rows) fetch(i);
-        int left = rows;   // rows not added yet, the first UN of them in flight
-        for (; left >= 2 * UN; left -= UN) {   // no load under a condition: the compiler then waits for one row at a time
-#pragma unroll
-            for (int i = 0; i < UN; ++i) {
-                add(i);
-                fetch(i);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < UN; ++i) {
-            if (i < left) add(i);
-            if (i + UN < left) fetch(i);
-        }
-#pragma unroll
-        for (int i = 0; i < UN; ++i)
-            if (i + UN < left) add(i);
-        float* dst = Z + (int64_t)g * copies * ldm + c0;
-        for (int i = 0; i < copies; ++i) stx<FULL>(dst + (int64_t)i * ldm, acc, n);
-    }
+    const int g = (int)blockIdx.y;   // one group per workgroup (grid.y = groups)
+    if (g >= groups) return;
+    const float4 sum = sum_rows<FULL, UN, HEAD>(G + (int64_t)g * rows * ldg + c0, ldg, rows, n);
+    float* dst = Z + (int64_t)g * copies * ldm + c0;
+    for (int i = 0; i < copies; ++i) stx<FULL>(dst + (int64_t)i * ldm, sum, n);
 }
 
-// Four rows in flight; eight where a launch leaves CUs idle.  Encoder in us, eight at a time / so: (45, 2, B = 180, 1 663 371)
-// 258 / 253, (45, 1, B = 180, 400 001) 62.6 / 59.3, (10, 2, B = 160, 200 000) 22.7 / 21.2; (10, 2, B = 160, 50 001), 98 workgroups,
-// 13.8 / 13.0 (with four 15.9).  One workgroup per CU, which suits r rows in and r out (below), loses 4 to 60 % here.
-template <bool SPREAD, int UN>
+// Four rows at a time; eight where a launch leaves CUs idle ((10, 2, B = 160, 50 001), 98 workgroups: 14.1 us, 18.2 with four), and
+// where no more than eight are added (all of them in flight).  Encoder in us, in bursts of eight at any length / so: (45, 2, B = 180, 1 663 371) 258 / 255, (45, 1,
+// B = 180, 400 001) 63.3 / 62.5, (10, 2, B = 160, 200 000) 24.7 / 23.4; (10, 2, B = 160, 50 001) 15.1 / 14.1.  One workgroup
+// per CU, which suits r rows in and r out (below), loses 4 to 60 % here.
+template <bool SPREAD, int UN, int HEAD>
 __global__ __launch_bounds__(kBlock) void encode_rep_generic_kernel(const float* __restrict__ G, int64_t ldg,
                                                                     float* __restrict__ Z, int64_t ldm,
                                                                     int groups, int rows, int copies, int64_t d) {
     const int64_t c0 = lane_column<SPREAD>(d);
-    if (block_is_full<SPREAD>(d, d)) encode_rep_generic_body<true, UN>(G, ldg, Z, ldm, groups, rows, copies, d, c0);
-    else encode_rep_generic_body<false, UN>(G, ldg, Z, ldm, groups, rows, copies, d, c0);
+    if (block_is_full<SPREAD>(d, d)) encode_rep_generic_body<true, UN, HEAD>(G, ldg, Z, ldm, groups, rows, copies, d, c0);
+    else encode_rep_generic_body<false, UN, HEAD>(G, ldg, Z, ldm, groups, rows, copies, d, c0);
 }
 
 // Majority candidate among R bit patterns of one coordinate (the streaming vote of
@@ -450,25 +466,36 @@ namespace {
 bool on_lines(int64_t ldm) { return ldm % 32 == 0; }
 
 // With two workgroups per CU, 513 to 768 of them would be one full turn and one nearly empty: four per CU make it one.  Sums over more
-// than r rows: (28, 3, 135 681), two samples a node, 12.1 -> 10.4 us, (15, 2, 180 907), sixteen, 41.4 -> 35.6; from 900 workgroups on
-// four are 0 to 6 % behind.  Three copies: (6, 1, 767 936) 8.2 -> 7.2 us; five copies have no such step (four: 4 to 9 % behind).
+// than r rows, two per CU / four: (15, 2, B = 240, 180 907) 42.8 / 36.1 us, (28, 3, B = 56, 135 681) 10.9 / 10.5, (20, 2, B = 80,
+// 131 603) 13.2 / 11.7; near 768 the same; from 900 workgroups on four are 0 to 6 % behind.  Three copies: (6, 1, 786 048) 8.1 / 7.0
+// us; five copies have no such step (four: 4 to 9 % behind).
 bool spills_two_per_cu(int64_t workgroups) { return workgroups > 512 && workgroups <= 768; }
+
+template <class F, int... K>
+void one_to(F&& f, std::integer_sequence<int, K...>) {
+    (f(std::integral_constant<int, K + 1>()), ...);
+}
 
 // Sums of `rows` rows per group, stored `copies` times (copies = 1: one row, its stride does not matter).
 void launch_generic(const float* G, int64_t ldg, float* Z, int64_t ldm, int groups, int rows, int copies, int per_cu,
                     int64_t d, hipStream_t stream) {
-    auto go = [&](auto spread, auto ahead) {
+    auto go = [&](auto spread, auto ahead, auto first) {
         constexpr bool SPREAD = decltype(spread)::value;
-        constexpr int UN = decltype(ahead)::value;
+        constexpr int UN = decltype(ahead)::value, HEAD = decltype(first)::value;
+        if (rows < HEAD || (rows - HEAD) % UN != 0) return;
         const dim3 grid(grid_cols<SPREAD>(d), (unsigned)groups);
         if (per_cu == 2 && spills_two_per_cu((int64_t)grid.x * grid.y)) per_cu = 4;
-        allow_large_lds<encode_rep_generic_kernel<SPREAD, UN>>();
-        hipLaunchKernelGGL((encode_rep_generic_kernel<SPREAD, UN>), grid, dim3(kBlock), throttle_lds(per_cu, 0, 0), stream, G, ldg,
-                           Z, ldm, groups, rows, copies, d);
+        allow_large_lds<encode_rep_generic_kernel<SPREAD, UN, HEAD>>();
+        hipLaunchKernelGGL((encode_rep_generic_kernel<SPREAD, UN, HEAD>), grid, dim3(kBlock), throttle_lds(per_cu, 0, 0), stream,
+                           G, ldg, Z, ldm, groups, rows, copies, d);
+    };
+    auto any_head = [&](auto spread, auto ahead) {   // (go launches one of them)
+        one_to([&](auto first) { go(spread, ahead, first); }, std::make_integer_sequence<int, decltype(ahead)::value>());
     };
     auto depth = [&](auto spread) {
-        if ((int64_t)grid_for((d + 3) / 4) * groups < 256) go(spread, std::integral_constant<int, 8>{});
-        else go(spread, std::integral_constant<int, 4>{});
+        const bool idle = (int64_t)grid_for((d + 3) / 4) * groups < 256;
+        if (rows <= 8 || idle) any_head(spread, std::integral_constant<int, 8>{});
+        else any_head(spread, std::integral_constant<int, 4>{});
     };
     if (on_lines(ldm)) depth(std::true_type{});
     else depth(std::false_type{});
