@@ -270,8 +270,9 @@ int draco_decode_repetition_static(int P, int s, int64_t d, const float* message
  * the rounding of an enormous one.
  * Returns DRACO_LOCATE_FAILED if no set of at most s nodes explains the
  * syndromes.  For s <= 16 the small linear
- * algebra of phi and b runs in one fp64 wavefront between the two streaming
- * kernels, so the whole call is stream-ordered and waits for `stream` only
+ * algebra of phi and b runs on the device in fp64, in a kernel of one wavefront
+ * between the two streaming kernels or at the head of the second one's
+ * workgroups, so the whole call is stream-ordered and waits for `stream` only
  * once, at the end, to fetch mask and status; for larger s it is
  * draco_decode_cyclic_hostphi. */
 int draco_decode_cyclic(draco_plan* plan, const float* messages_dev, int64_t ld_m,
@@ -305,8 +306,8 @@ int draco_projection_vector(const draco_plan* plan, uint64_t seed, float* f_host
  * sum (bit-identical to what the second pass would give) and the second pass over
  * the messages is skipped, which halves the decode.  Messages below 384 MiB: the
  * prediction is "nobody", made when the plan's previous decode was clean (the first
- * call counts as one); rows split over the nodes (fewer than 256 tiles of 1024 floats and
- * more than 8 nodes) are not speculated on.  Larger ones: the set that phi finds on a
+ * call counts as one); short rows (fewer than 256 tiles of 1024 floats on more than 8
+ * nodes, up to 64 tiles on 8 or fewer) are not speculated on.  Larger ones: the set that phi finds on a
  * sample of the columns of this call's messages (which columns is drawn from f), so
  * adversaries that lie everywhere cost no second pass, persistent or not; after 8 clean decodes
  * in a row "nobody", without a sample, until a decode finds somebody.  A lie that the sample does not

@@ -34,8 +34,9 @@ int draco_copy_probe(const float* src_dev, float* dst_dev, int rows, int64_t row
  * kind: 0 encode, 1 repetition vote, 2 cyclic projection (with its small
  * reduction), 3 cyclic recombination (and the locator where one kernel does
  * both: rows of up to 65 536 floats, and messages of at most 320 MiB of at most
- * 64 nodes whose rows have 256 tiles of 1024 floats or more), 4 the cyclic
- * locator (phi steps 2-4 and b, one wavefront) as a kernel of its own. */
+ * 64 nodes whose rows have 256 tiles of 1024 floats or more, 65 or more on up to
+ * 8 nodes), 4 the cyclic locator (phi steps 2-4 and b, one wavefront) as a
+ * kernel of its own. */
 int draco_plan_set_timing(draco_plan* plan, int max_records);
 int draco_plan_kernel_time(draco_plan* plan, int kind, double* total_ms, int* launches);
 int draco_plan_kernel_times(draco_plan* plan, int kind, double* ms_host, int capacity,
