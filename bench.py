@@ -60,6 +60,19 @@ def algorithmic_bytes(w, mlen, n_honest, words):
     }
 
 
+def settle_recombination(times, abytes, d, held):
+    """What the recombination's record stands for.  held: the last decode recombined while it projected (what the plan
+    speculated on was the set found): one pass reads the messages and writes the sum, the recombination returns at once.
+    Where one kernel locates and recombines, no record of a locator exists, and the time goes by both names."""
+    if held:
+        abytes["project"] += d * 4
+        del abytes["recombine"]
+    if len(times["recombine"]) and not len(times["locate"]):
+        times["locate_recombine"] = times.pop("recombine")
+        if "recombine" in abytes:
+            abytes["locate_recombine"] = abytes.pop("recombine")
+
+
 def measured_traffic(workload, kind):
     """HBM bytes per launch of one kernel kind from the committed rocprofv3 --pmc summary of
     this workload (FETCH_SIZE and WRITE_SIZE scaled by the copy kernel), or None."""
@@ -237,11 +250,8 @@ def measure(w, wire, steps, warmup, headline):
         rec["decode_only"] = {"ms": dec_ms, "GBps_consumed": consumed / (dec_ms * 1e-3) / 1e9}
 
     abytes = algorithmic_bytes(w, c.mlen, n_honest, words)
-    if len(times["recombine"]) and np.median(times["recombine"]) < 0.1 * np.median(times["project"]):
-        # the decode recombined while it projected (adversaries located on a sample first): one pass
-        # reads the messages and writes the sum, the recombination kernel returns at once
-        abytes["project"] += w.d * 4
-        del abytes["recombine"]
+    settle_recombination(times, abytes, w.d,
+                         w.decode and w.code == "cyc" and w.s <= 16 and bool(c.plan.speculation_state()[2]))
     kernels = {}
     for kname, ms in times.items():
         if len(ms) == 0:

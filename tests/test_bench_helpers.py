@@ -57,3 +57,20 @@ def test_traffic_is_read_from_the_committed_profile(workload, kind, idx, words):
     assert abs(got / want - 1.0) < 0.01
     assert bench.measured_traffic("no_such_workload", kind) is None
     assert bench.measured_traffic(workload, "locate") is None
+
+
+@pytest.mark.parametrize("held", [False, True])
+@pytest.mark.parametrize("fused", [False, True])
+def test_recombination_is_priced_by_what_its_record_holds(held, fused):
+    """Whether the second pass ran comes from the plan, not from a ratio of times (a launch that returns at once takes 5 us, a
+    tenth of the projection on rows of a million floats), and a kernel that locates too is not named after half of its work."""
+    w = synth.scaled(synth.WORKLOADS[4], 1_000_000)
+    times = {"encode": [100.0], "vote": [], "project": [50.0], "recombine": [5.4 if held else 45.0], "locate": [] if fused else [7.0]}
+    abytes = bench.algorithmic_bytes(w, w.d, w.P - 3, 1.25)
+    second, project = abytes["recombine"], abytes["project"]
+    bench.settle_recombination(times, abytes, w.d, held)
+    name = "locate_recombine" if fused else "recombine"
+    assert name in times and len({"recombine", "locate_recombine"} & set(times)) == 1
+    assert abytes["project"] == project + (w.d * 4 if held else 0)
+    assert {"recombine", "locate_recombine"} & set(abytes) == (set() if held else {name})
+    assert held or abytes[name] == second
