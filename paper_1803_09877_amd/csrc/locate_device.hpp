@@ -22,9 +22,10 @@
 //   * orthonormal columns are kept in registers, spread over the lane groups, and a new column is
 //     made orthogonal to all of them at once (classical Gram-Schmidt, twice);
 //   * sums over lanes are DPP row operations and v_permlane swaps, never LDS.
-// Measured, one call in cycles at 2.3 GHz, the general form alone (with sums and medians out of LDS) and now: (P, s,
-// liars) = (45, 3, 0) 10 100 and 4 600, (45, 3, 3) 32 400 and 13 800, (45, 7, 4) 42 000 and 18 400, (15, 2, 2) 22 000 and 10 100,
-// (32, 4, 1) 21 600 and 8 500.  Of the 13 800 the median takes 2 200, the QR 2 000, the basis 4 600.
+// Measured with the code in the instruction cache (the first call of a kernel takes 1 200 to 6 000 cycles more), one call in cycles at
+// 2.3 GHz: (P, s, liars) = (45, 3, 0) 3 700, (45, 3, 1) 7 600, (45, 3, 3) 13 900, (45, 7, 4) 17 500, (15, 2, 2) 9 100, (32, 4, 1) 7 400,
+// (40, 8, 3) 29 900, (45, 10, 5) 250 000.  Of the 13 900 the median takes 1 800 and locate_exact 9 200, b's coefficients included, for
+// which the general form takes 22 800 (QR 5 800); of the 250 000 the Jacobi sweeps 222 000 and the recurrence 5 400.
 // Limits: P <= 256, s <= kLocateMaxS.
 #pragma once
 
@@ -191,19 +192,22 @@ __device__ __forceinline__ void recurrence(LocateSmem& sm, int n, int P, int lan
     };
     unroll_slots(rest, l, std::make_integer_sequence<int, S>());
 }
-// The same out of LDS, for windows too long to unroll.
-__device__ __forceinline__ void recurrence_lds(LocateSmem& sm, int n, int P, int s, int lane) {
-    if (lane == 0) {
-        for (int l = 0; l < n; ++l) {
-            double2 acc = make_double2(0.0, 0.0);
-            int e = l - s;
-            if (e < 0) e += P;
-            for (int u = 0; u < s; ++u) {
-                acc = cadd(acc, cmul(sm.beta[u], sm.h[e]));
-                e = addmod(e, 1, P);
-            }
-            sm.h[l] = acc;
-        }
+// The same for windows too long to unroll (s <= 16): lane i of each row of 16 holds what is known of h_{l+i}.  A new value
+// is lane 0's; the others move down a lane and each takes its term.  (One lane that gathers s values out of LDS for
+// each new one, 160 cycles a term: decodes of 7 000 floats with one liar, (256, 16) 401 us, 143 so, (200, 9) 211 and 93.)
+__device__ __forceinline__ void recurrence_lanes(LocateSmem& sm, int n, int P, int s, int lane) {
+    const int i = lane % 16;
+    const double2 beta = i < s ? sm.beta[s - 1 - i] : make_double2(0.0, 0.0);
+    const double2 known = sm.h[P - s + min(i, s - 1)];   // h_{-s} .. h_{-1}
+    double2 next = make_double2(0.0, 0.0);
+    auto enter = [&](double2 v) {
+        next = cfma(beta, v, make_double2(dpp_move<kDppShl1>(next.x), dpp_move<kDppShl1>(next.y)));
+    };
+    for (int w = 0; w < s; ++w) enter(make_double2(lane_value(known.x, w), lane_value(known.y, w)));
+    for (int l = 0; l < n; ++l) {
+        const double2 v = make_double2(lane_value(next.x, 0), lane_value(next.y, 0));
+        sm.h[l] = v;   // (every lane the same)
+        enter(v);
     }
 }
 
@@ -331,9 +335,10 @@ __device__ __forceinline__ void solve_beta(LocateSmem& sm, int P, int s, double 
                     aq = M[q * kLocateMaxS];
                 }
                 const double2 gp = cmul(cconj(ap), aq);
-                const double alpha = group_sum<GL>(isV ? 0.0 : cnorm2(ap));
-                const double bet = group_sum<GL>(isV ? 0.0 : cnorm2(aq));
-                const double2 gd = make_double2(group_sum<GL>(isV ? 0.0 : gp.x), group_sum<GL>(isV ? 0.0 : gp.y));
+                double sums[4] = {isV ? 0.0 : cnorm2(ap), isV ? 0.0 : cnorm2(aq), isV ? 0.0 : gp.x, isV ? 0.0 : gp.y};
+                group_sums<GL>(sums);
+                const double alpha = sums[0], bet = sums[1];
+                const double2 gd = make_double2(sums[2], sums[3]);
                 const double ag2 = cnorm2(gd);
                 // columns that both end below the cutoff are dropped from the solution: no need
                 // to make them orthogonal to each other
@@ -351,8 +356,8 @@ __device__ __forceinline__ void solve_beta(LocateSmem& sm, int P, int s, double 
                     const double c = rsqrt_pos(fma(t, t, 1.0)), sn = c * t;
                     const double2 aqr = cmul(aq, ph);
                     if (live) {
-                        M[p * kLocateMaxS] = csub(cscale(ap, c), cscale(aqr, sn));
-                        M[q * kLocateMaxS] = cadd(cscale(ap, sn), cscale(aqr, c));
+                        M[p * kLocateMaxS] = make_double2(fma(ap.x, c, -(aqr.x * sn)), fma(ap.y, c, -(aqr.y * sn)));
+                        M[q * kLocateMaxS] = make_double2(fma(aqr.x, c, ap.x * sn), fma(aqr.y, c, ap.y * sn));
                     }
                 }
                 rotated |= __ballot(!skip) != 0ull;
@@ -388,8 +393,8 @@ __device__ __forceinline__ void solve_beta(LocateSmem& sm, int P, int s, double 
 // m > 1024 zero and the rest as dropped if m sqrt(s - k) <= zero; in between (nearly dependent
 // columns) it returns false and the Jacobi form decides.  The minimum-norm solution of the kept rows
 // is the truncated one up to the size of what was dropped.
-// (P, s, liars) = (45, 7, 4): 10 000 cycles against 55 000 for the tournament and 141 000 for Jacobi
-// sweeps one pair at a time; (45, 3, 3): 7 000 against 18 000 and 17 000.
+// Cycles against the tournament's: (P, s, liars) = (45, 7, 4) 8 100 and 46 700, (45, 3, 3) 5 800 and 14 100, (40, 8, 3) 6 100 and
+// 51 800.
 __device__ __forceinline__ bool solve_beta_qr(LocateSmem& sm, int P, int s, double zero2, int lane) {
     const int g = lane >> 3, row = lane & 7;
     double2 col = make_double2(0.0, 0.0), rhs = col;
@@ -572,8 +577,9 @@ __device__ __forceinline__ void with_count(int a, F&& f) {
 // the relation between them, a polynomial of degree a, vanishes.  Columns 0 .. s (the last is the right-hand side), one per
 // lane group of 8, are made orthogonal in turn; one whose remainder is below 64 times the zero threshold counts as
 // dependent.  Nothing here has to be right: the set is taken only if it accounts for the syndromes and none of its nodes can
-// be left out, which makes it the shortest leading part of the ranking; else false, and the general form decides.
-// (45, 3, 3 liars): 8 300 cycles with the coefficients of b, the general form 22 300.
+// be left out; else false, and the general form decides.  For lies well above the threshold no other set of up to s nodes
+// accounts for them (any 2s columns are independent), so that set is the ranking's shortest leading part; near it both forms
+// may settle on different sets that account for the syndromes.
 template <int CH>
 __device__ __forceinline__ bool locate_exact(LocateSmem& sm, const double2 (&root)[CH], int P, int s, int n, double isq,
                                              double zero2, int lane, NodeSet<CH>& found, double2& Bv) {
@@ -688,7 +694,7 @@ __device__ __forceinline__ bool locate_general(LocateSmem& sm, const double2 (&r
         case 6: recurrence<6>(sm, n, P, lane); break;
         case 7: recurrence<7>(sm, n, P, lane); break;
         case 8: recurrence<8>(sm, n, P, lane); break;
-        default: recurrence_lds(sm, n, P, s, lane);
+        default: recurrence_lanes(sm, n, P, s, lane);
     }
     wave_sync();
     // ---- t = C h, ranking by |t_j| (descending, ties to the lower index)

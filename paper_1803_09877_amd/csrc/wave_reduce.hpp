@@ -13,7 +13,7 @@ __device__ __forceinline__ double lane_value(double v, int q) {
 }
 template <int CTRL>
 __device__ __forceinline__ double dpp_move(double v) {
-    // every lane reads a lane of its own row of 16, so no previous value is kept (mov_dpp): one
+    // every lane reads a lane of its own row of 16, or 0 behind its end, so no previous value is kept (mov_dpp): one
     // instruction per word
     const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true);
     const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true);
@@ -23,6 +23,7 @@ constexpr int kDppXor1 = 0xB1;         // quad_perm [1, 0, 3, 2]
 constexpr int kDppXor2 = 0x4E;         // quad_perm [2, 3, 0, 1]
 constexpr int kDppHalfMirror = 0x141;  // lane i <-> 7 - i within each 8 lanes
 constexpr int kDppRor8 = 0x128;        // lane i <-> i ^ 8 within each 16 lanes
+constexpr int kDppShl1 = 0x101;        // lane i <- i + 1 within each 16 lanes, 0 into the last
 
 // Swaps lanes 32-63 of a with lanes 0-31 of b (WIDTH = 32), or the odd rows of 16 lanes of a with
 // the even rows of b (WIDTH = 16).

@@ -98,3 +98,64 @@ def test_second_liar_around_the_thresholds(P, s):
             assert np.linalg.norm(ug - uo) <= 1e-6 * np.linalg.norm(uo), (times, a, b)
     finally:
         c.close()
+
+
+def test_wide_windows_recur_without_gathering():
+    """One liar among 200 nodes, s = 8 (QR, eight values in registers) and 9 (Jacobi, a value per lane).  With the terms of the
+    recurrence gathered out of LDS by one lane the second took 3.4 times as long, now 1.5 times; 2.2 is the bound."""
+    P, d, times = 200, 7_000, []
+    for s in (8, 9):
+        w = synth.Workload(name="locator", code="cyc", P=P, s=s, d=d, sigma=1.0, attacks=(), placement="any",
+                           seed=synth.SEED_BASE + s)
+        c = Case(w, wide="i8")
+        try:
+            c.encode()
+            c.receive()
+            c.R[17, :c.mlen] *= -100.0
+            mask_dev = torch.zeros(4, dtype=torch.int64, device="cuda:0")
+            status_dev = torch.zeros(1, dtype=torch.int32, device="cuda:0")
+            for _ in range(3):
+                c.plan.decode_cyclic_wide_async(c.R, c.Rlo, c.f, c.u, mask_dev, status_dev)
+            torch.cuda.synchronize()
+            assert status_dev.item() == B.OK and mask_dev.tolist() == [1 << 17, 0, 0, 0]
+            spans = []
+            for _ in range(12):
+                e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                e0.record()
+                for _ in range(20):
+                    c.plan.decode_cyclic_wide_async(c.R, c.Rlo, c.f, c.u, mask_dev, status_dev)
+                e1.record()
+                torch.cuda.synchronize()
+                spans.append(e0.elapsed_time(e1))
+            times.append(min(spans))
+        finally:
+            c.close()
+    assert times[1] <= 2.2 * times[0], times
+
+
+@pytest.mark.parametrize("P,s", [(65, 9), (128, 16), (129, 10), (129, 16), (200, 12)])
+def test_wide_windows_over_the_chunks_of_nodes(P, s):
+    """s > 8 on 65 to 256 nodes, whose values come from a recurrence of up to 176 steps: one liar, half and all of them, evenly
+    spread (the sizes of the messages and 100 times that).  Sets and statuses equal the oracle's."""
+    d = 64
+    w = synth.Workload(name="locator", code="cyc", P=P, s=s, d=d, sigma=1.0, attacks=(), placement="any",
+                       seed=synth.SEED_BASE + 5 * P + s)
+    c = Case(w, wide="f32")
+    rng = np.random.default_rng(P + s)
+    try:
+        c.encode()
+        f = c.f.cpu().numpy()
+        for k in (1, s // 2, s):
+            liars = [(3 + i * P // k) % P for i in range(k)]
+            c.receive()
+            for i, j in enumerate(liars):
+                row = c.Z[j, :c.mlen].cpu().numpy()
+                lie = rng.standard_normal(c.mlen) * np.sqrt(np.mean(row.astype(np.float64) ** 2)) * (100.0 if i % 2 else 1.0)
+                c.R[j, :c.mlen] = torch.from_numpy((row + lie).astype(np.float32)).to(c.device)
+            Rw = c.R[:, :c.mlen].double().cpu().numpy() + c.Rlo[:, :c.mlen].double().cpu().numpy()
+            _, mo, so = o.decode_cyclic(Rw, f, s, d, tau_h=o.TAU_H_WIDE)
+            mask, status = c.decode()
+            torch.cuda.synchronize()
+            assert status == so and np.array_equal(mask, mo), (k, np.flatnonzero(mo), np.flatnonzero(mask), so, status)
+    finally:
+        c.close()
