@@ -81,6 +81,6 @@ def test_locators_that_recombine_keep_their_rows_in_registers(kernels):
     """Two wavefronts per SIMD: a workgroup of eight (short rows), two workgroups of four (longer ones).  Rows in flight that
     spill go through memory and back while the locator runs."""
     short, walk = (arguments(kernels, "cyc_locate_" + n + "_kernel") for n in ("recombine", "walk"))
-    assert {lo for lo, _ in short} == {lo for lo, _ in walk} and {chunks for _, chunks in short} == {1, 4}
+    assert {lo for lo, _ in short} == {lo for lo, _ in walk} and {chunks for _, chunks in short} == {1, 2, 4}
     for form, (registers, scratch) in list(short.items()) + list(walk.items()):
         assert registers <= 256 and scratch == 0, (form, registers, scratch)
