@@ -239,7 +239,7 @@ __global__ __launch_bounds__(kBlock, PER_CU) void encode_cyc_rounds_kernel(const
     else encode_cyc_rounds_body<S, NB, false, LO>(G, ldg, Z, Zlo, ldm, tab, P, d, c0, head);
 }
 
-// The same encoder for short rows, up to 1.25 M floats (node_segment).  There the walk down P rows is
+// The same encoder for short rows (node_segment says which).  There the walk down P rows is
 // latency: a workgroup (4 KiB contiguous, neighbours on one die) takes only `seg`
 // nodes, blockIdx.y the segment, and the rows that neighbouring segments share (2s of them) come
 // from the die's L2; no LDS, so the registers alone bound the workgroups per CU.  The tiles of a segment run before the next
