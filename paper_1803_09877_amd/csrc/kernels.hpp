@@ -161,7 +161,8 @@ hipError_t launch_cyc_locate_sample(const double2* partial, const double2* roots
                                     const CycSpec& spec, hipStream_t stream);
 // Where the locator's kernel recombines too: rows that are one KiB per CU, and of at most 64 nodes (a locator's registers)
 // the rows that are not short (65 to 255 tiles: 17 us, 22 in one launch at (45, 3, 70 001), whose recombination
-// needs more wavefronts), in messages that stay in the memory-side cache.  Beyond, two workgroups per CU recombine up to 3 % slower
+// needs more wavefronts; on 8 nodes or fewer it does not: 222 decodes of such rows take 0.63 to 0.93 of the time in two launches with
+// the general locator, (8, 2, 117 459) with two liars 21.7 -> 17.0 us, (8, 1, 206 494) with none 14.5 -> 12.0), in messages that stay in the memory-side cache.  Beyond, two workgroups per CU recombine up to 3 % slower
 // ((15, 2, 4 M) on the 6-byte wire: 119 and 121 us), and after a sample the locator alone finds its code in the instruction
 // cache ((45, 7, 6 M) on two fp32 words: a step of 962 us, 966 in one launch).
 inline bool one_chunk_per_cu(int64_t d) { return (d + 1) / 2 * 2 <= kFusedTiles * kBlock * 4; }

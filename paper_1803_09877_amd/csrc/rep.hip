@@ -576,7 +576,8 @@ void launch_vote(const float* R, int64_t ldm, float* u, const VoteOut& out, int6
         // 54; (18, 1, 6 M) 75 -> 73; but (45, 1, 4 M) 109 -> 111).  Short ones: as many as put them into one turn, where a second one
         // would be nearly empty: four up to 1024 workgroups ((45, 1, 600 000) 26.9 -> 21.6), r >= 7, whose second turn costs
         // less, up to 768 ((45, 4, 700 001) 27.9 -> 26.0; at 950 000 32.4 and 33.4), and six up to 1280 where one turn of them is well
-        // filled ((45, 1, 1.3 M) 42.4 -> 39.9, (45, 2, 1 200 001) 47.1 -> 41.8; at 1.5 M 48.0 and 50.8, 51.4 and 50.4).
+        // filled ((45, 1, 1.3 M) 42.4 -> 39.9, (45, 2, 1 200 001) 47.1 -> 41.8; at 1.5 M 48.0 and 50.8, 51.4 and 50.4);
+        // (6, 1) with a liar loses 0.5 of 11 and 13 us at 1.0 and 1.3 M).
         const unsigned c = grid.x;
         const int three = c <= 1024 ? 4 : c <= 1280 ? 6 : groups <= 6 ? 4 : 2;
         const int five = c > 1024 && c <= 1280 ? 6 : 4, more = c <= 768 ? 4 : 2;
