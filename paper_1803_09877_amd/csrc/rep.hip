@@ -91,8 +91,12 @@ __device__ __forceinline__ float4 sum_rows(const float* __restrict__ src, int64_
     // a round is added and the next one fetched, row by row
     auto rounds = [&](auto& row, int left) {
         for (; left > UN; left -= UN) {
-            // Four rows are waited for together: (15, 2, B = 240, 180 907) 36.1 us, 37.9 one by one, long launches the same.
-            if constexpr (UN == 4) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            // Four rows are waited for together, before the first sum ((15, 2, B = 240, 180 907) 37.1 us, 38.9 one by one; with the
+            // wait behind the first sum 37.6, and (45, 1, B = 180, 400 001) 65.6 instead of 63.3).
+            if constexpr (UN == 4)
+                asm volatile("" : "+v"(row[0].x), "+v"(row[0].y), "+v"(row[0].z), "+v"(row[0].w), "+v"(row[1].x), "+v"(row[1].y),
+                             "+v"(row[1].z), "+v"(row[1].w), "+v"(row[2].x), "+v"(row[2].y), "+v"(row[2].z), "+v"(row[2].w),
+                             "+v"(row[3].x), "+v"(row[3].y), "+v"(row[3].z), "+v"(row[3].w));
 #pragma unroll
             for (auto& v : row) {
                 add(v);
