@@ -105,9 +105,9 @@ constexpr int kFusedTiles = 64;       // and of those that are located and recom
 // 45 21.0 / 20.9, 100 37.2 / 39.8).
 inline int64_t inline_tiles(int P) { return P <= 64 ? 128 : 64; }
 // Messages (both words, bytes) from which a decode may locate the adversaries on a sample first and
-// then project and recombine in ONE pass.  The sample and its locator take 15 to 30 us and the
+// then project and recombine in ONE pass.  The sample and its locator take 11 to 20 us and the
 // joint pass 10 % more than a projection; the second pass they save runs at about 6.3 TB/s, so with
-// adversaries it breaks even near 250 MB.
+// adversaries it broke even near 250 MB when the sample and its locator took 15 to 30 (the line has not been measured again since).
 constexpr int64_t kSampledMessages = 384ll << 20;
 // A plan that saw kCleanRun clean decodes in a row expects nobody and takes no sample (15 to 20 us, 8 % of a
 // clean step at (15, 2, 8 M)); until then, and after a decode that found somebody, it samples.  A
