@@ -182,6 +182,7 @@ int prepare(draco_plan* p) {
             const int32_t init[kSpecWords] = {1};  // optimistic: as after one clean decode
             HIP_TRY(hipMemcpy(p->spec_dev, init, sizeof(init), hipMemcpyHostToDevice));
         }
+        if (p->s <= kLocateMaxS) HIP_TRY(load_locator());
         HIP_TRY(hipMalloc(&p->idx_dev, (P + 1) * sizeof(int32_t)));
         HIP_TRY(hipHostMalloc(&p->gamma_pin, 2 * P * sizeof(double), hipHostMallocDefault));
         HIP_TRY(hipHostMalloc(&p->b_pin, 2 * P * sizeof(double), hipHostMallocDefault));

@@ -169,6 +169,9 @@ inline bool one_chunk_per_cu(int64_t d) { return (d + 1) / 2 * 2 <= kFusedTiles 
 inline bool recombines_in_locator(int P, int64_t d, int64_t message_bytes) {
     return one_chunk_per_cu(d) || (P <= 64 && !short_rows(d, P) && message_bytes <= kSmallMessages);
 }
+// Brings the locators' code to the device, which their first launch would do otherwise: 0.3 to 1.7 ms of a process's first decode,
+// in the record of the kernel that recombines too.
+hipError_t load_locator();
 // The locator on sums[tiles][P] and the recombination in one launch.
 hipError_t launch_cyc_locate_recombine(const double2* sums, int64_t tiles, const double2* roots, int P, int s, double tau,
                                        const double2* b0, uint64_t* mask_out, int32_t* status_out, const CycSpec& spec,

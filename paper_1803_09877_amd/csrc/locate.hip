@@ -300,6 +300,11 @@ static void launch(int threads, const double2* sums, int tiles, const double2* r
     with_chunks(P, go);
 }
 
+hipError_t load_locator() {
+    hipFuncAttributes of{};
+    return hipFuncGetAttributes(&of, reinterpret_cast<const void*>(&cyc_locate_walk_kernel<kLoNone, 6>));
+}
+
 hipError_t launch_cyc_locate_recombine(const double2* sums, int64_t tiles, const double2* roots, int P, int s, double tau,
                                        const double2* b0, uint64_t* mask_out, int32_t* status_out, const CycSpec& spec,
                                        const float* R, const float* Rlo, int lo, int64_t ldm, float* u, bool realout, int64_t d,

@@ -6,6 +6,10 @@ decoded sums within relative L2 1e-5 (repetition) / 1e-4 (cyclic) of the fp64
 oracle on the SAME received messages; encoded messages within relative L2 1e-6
 per node of the oracle's fp64 messages (the wire is fp32: one rounding is
 6e-8); repetition copies bit-identical within a group."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -1286,3 +1290,23 @@ def test_alignment_and_argument_errors():
                                      words.ctypes.data, st) == B.EINVAL          # wrong code for the call
     finally:
         c.close()
+
+
+def test_first_decode_of_a_process_records_its_kernel_alone():
+    """In a process of its own: the first decode of (33, 3, 400 001) on one word, whose second kernel locates and recombines, 20 us.
+    With the kernel's code brought to the device by that launch the record held 300 to 1700 us; 150 is the bound."""
+    code = (
+        "import torch\n"
+        "from paper_1803_09877_amd import binding as B\n"
+        "plan = B.Plan(B.CODE_CYCLIC, 33, 3, 400_001)\n"
+        "plan.prepare()\n"
+        "plan.set_timing(4)\n"
+        "Z = torch.randn((33, 400_004), device='cuda:0')\n"
+        "u = torch.zeros(400_004, device='cuda:0')\n"
+        "torch.cuda.synchronize()\n"
+        "plan.decode_cyclic(Z, None, u)\n"
+        "print('us', plan.kernel_times(B.KIND_RECOMBINE)[0] * 1e3)\n")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    res = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True, timeout=100)
+    assert res.returncode == 0, res.stderr[-500:]
+    assert float(res.stdout.split("us")[-1]) <= 150.0, res.stdout
