@@ -135,7 +135,7 @@ __device__ __forceinline__ void encode_rep_generic_body(const float* __restrict_
 }
 
 // Four rows at a time; eight where a launch leaves CUs idle ((10, 2, B = 160, 50 001), 98 workgroups: 14.1 us, 18.2 with four), and
-// where no more than eight are added (all of them in flight).  Encoder in us, in bursts of eight at any length / so: (45, 2, B = 180, 1 663 371) 258 / 255, (45, 1,
+// where five to eight are added (all of them in flight).  Encoder in us, in bursts of eight at any length / so: (45, 2, B = 180, 1 663 371) 258 / 255, (45, 1,
 // B = 180, 400 001) 63.3 / 62.5, (10, 2, B = 160, 200 000) 24.7 / 23.4; (10, 2, B = 160, 50 001) 15.1 / 14.1.  One workgroup
 // per CU, which suits r rows in and r out (below), loses 4 to 60 % here.
 template <bool SPREAD, int UN, int HEAD>
@@ -498,7 +498,8 @@ void launch_generic(const float* G, int64_t ldg, float* Z, int64_t ldm, int grou
     };
     auto depth = [&](auto spread) {
         const bool idle = (int64_t)grid_for((d + 3) / 4) * groups < 256;
-        if (rows <= 8 || idle) any_head(spread, std::integral_constant<int, 8>{});
+        // (up to four rows are all in flight either way, and fewer registers let more workgroups onto a CU)
+        if ((rows > 4 && rows <= 8) || idle) any_head(spread, std::integral_constant<int, 8>{});
         else any_head(spread, std::integral_constant<int, 4>{});
     };
     if (on_lines(ldm)) depth(std::true_type{});
